@@ -99,8 +99,7 @@ __global__ void __launch_bounds__(kFwdThreads) k_blend_fwd(RenderConst rc, const
                                                            char* ctx, CtxLayout L, asgs_images out, BlendL1 l1) {
   constexpr int CS = 4 + NF;
   constexpr int CS4 = CS / 4;
-  uint4* binfo = ctx_ptr<uint4>(ctx, L.binfo);
-  const uint4 bi = binfo[blockIdx.x];  // longest lists first
+  const uint4 bi = ctx_ptr<const uint4>(ctx, L.binfo)[blockIdx.x];  // longest lists first
   const int tile = (int)bi.x;
   const int view = find_view(views, rc.n_views, tile);
   const ViewDev& V = views[view];
@@ -123,15 +122,13 @@ __global__ void __launch_bounds__(kFwdThreads) k_blend_fwd(RenderConst rc, const
   const float4* geom = ctx_ptr<const float4>(ctx, L.geom);
   const float4* chan4 = ctx_ptr<const float4>(ctx, L.chan);
   uint8_t* pmask = ctx_ptr<uint8_t>(ctx, L.pmask);
-  // lists walked by several backward workgroups: staged kSeg entries at a
-  // time, with the pixel's state recorded at every segment boundary
-  static_assert(kSeg * 2 == kTilePix && split_floats(CS) == ((kSegMax - 1) * split_first(CS) + split_final(CS)) * kTilePix,
-                "segment layout");
-  const uint32_t sl = ctx_ptr<const uint32_t>(ctx, L.bslot)[tile];  // 1 + split-record slot, or 0
-  const int nseg = sl ? split_segments(rg.y - rg.x) : 1;
-  const uint32_t rstep = nseg > 1 ? (uint32_t)kSeg : (uint32_t)kTilePix;  // entries staged per round
-  constexpr int SA = split_first(CS), SF = split_final(CS);
-  float* sp = ctx_ptr<float>(ctx, L.split) + (size_t)(sl ? sl - 1u : 0u) * split_floats(CS);
+  // lists walked by several backward workgroups: rounds end at the segment
+  // boundaries, and the pixel's state is recorded at the end of every segment
+  // but the last
+  const uint32_t sl = ctx_ptr<const uint32_t>(ctx, L.bslot)[tile];
+  const uint32_t seglen = sl ? segment_length(rg.y - rg.x, sl >> 20) : rg.y - rg.x;
+  constexpr int SA = split_first(CS);
+  float* sp = ctx_ptr<float>(ctx, L.split) + (size_t)(sl ? (sl & kSplitSlotMask) - 1u : 0u) * split_floats(CS);
 
   __shared__ float4 sg[kTilePix * 2];
   __shared__ float4 sc[kTilePix * CS4];
@@ -213,11 +210,14 @@ __global__ void __launch_bounds__(kFwdThreads) k_blend_fwd(RenderConst rc, const
     }
   };
   // the Gaussian ids of the next round are read while this round is staged
-  uint32_t gid_next = t < rstep && rg.x + t < rg.y ? pairgid[rg.x + t] : 0u;
+  uint32_t gid_next = t < kTilePix && rg.x + t < rg.y ? pairgid[rg.x + t] : 0u;
+  uint32_t seg = 0u, segend = rg.x + seglen;  // current segment and its end
+  uint32_t rstep = 0u;                        // entries of the round
   for (uint32_t base = rg.x; base < rg.y; base += rstep) {
     if (__syncthreads_count(!done) == 0) break;
     const uint32_t p = base + t;
-    if (t < rstep && p < rg.y) {
+    rstep = min((uint32_t)kTilePix, min(segend, rg.y) - base);
+    if (t < rstep) {
       const uint32_t gid = gid_next;
       const float4 g0 = geom[2 * (size_t)gid];
       const float4 g1 = geom[2 * (size_t)gid + 1];
@@ -228,14 +228,14 @@ __global__ void __launch_bounds__(kFwdThreads) k_blend_fwd(RenderConst rc, const
       const uint8_t m = (uint8_t)quarter_mask(g0, g1, x0, y0);
       smask[t] = m;
       pmask[p] = m;  // reused by the backward
-      if (p + rstep < rg.y) gid_next = pairgid[p + rstep];
     }
+    if (t < kTilePix && p + rstep < rg.y) gid_next = pairgid[p + rstep];
     {
       const uint64_t dm = __ballot(done);
       if (!back && lane == 0) qdone[qd] = dm;
     }
     __syncthreads();
-    const int cnt = (int)min(rstep, rg.y - base);
+    const int cnt = (int)rstep;
     // the quarter's entries of the round (those that can reach one of its
     // pixels), in list order, compacted into swl (the same list on both waves)
     int n = 0;
@@ -277,10 +277,11 @@ __global__ void __launch_bounds__(kFwdThreads) k_blend_fwd(RenderConst rc, const
       }
       if (__ballot(fix)) run(nf, n, base, fix, true);
     }
-    const int bnd = (int)((base - rg.x) / kSeg) + 1;  // segment boundary after this round
-    if (nseg > 1 && !back && bnd < nseg) {
-      // state after the first bnd * kSeg entries
-      float* rp = sp + ((size_t)(bnd - 1) * kTilePix + tq) * SA;
+    const bool ends = base + rstep == segend;
+    if (ends && !back && segend < rg.y) {
+      // T at the end of a segment and the segment's own channels; the next
+      // segment accumulates from zero
+      float* rp = sp + (size_t)seg * split_floats(CS) + (size_t)tq * SA;
       float r[SA];
       r[0] = T;
 #pragma unroll
@@ -290,27 +291,40 @@ __global__ void __launch_bounds__(kFwdThreads) k_blend_fwd(RenderConst rc, const
 #pragma unroll
       for (int c4 = 0; c4 < SA / 4; ++c4)
         reinterpret_cast<float4*>(rp)[c4] = make_float4(r[4 * c4], r[4 * c4 + 1], r[4 * c4 + 2], r[4 * c4 + 3]);
+#pragma unroll
+      for (int c = 0; c < CS; ++c) acc[c] = 0.f;
+    }
+    if (ends) {
+      ++seg;
+      segend += seglen;
     }
   }
-  if (nseg > 1 && !back) {
-    // the final channels (the entries after a boundary add C_final - C_boundary)
-    float* rp = sp + (size_t)(kSegMax - 1) * kTilePix * SA + (size_t)tq * SF;
-    float r[SF];
+  // Back to front over the records passed: a record's channels become the sum
+  // of the later segments', what the entries after its boundary add (summed
+  // from small to large, without the cancellation of C_final - C_boundary),
+  // and acc the whole list's.
+  if (sl && !back)
+    for (int b = (int)min(seg, (rg.y - rg.x - 1u) / seglen) - 1; b >= 0; --b) {
+      float* rp = sp + (size_t)b * split_floats(CS) + (size_t)tq * SA;
+      float r[SA];
 #pragma unroll
-    for (int c = 0; c < SF; ++c) r[c] = c < CS ? acc[c < CS ? c : 0] : 0.f;
+      for (int c4 = 0; c4 < SA / 4; ++c4) {
+        const float4 v = reinterpret_cast<const float4*>(rp)[c4];
+        r[4 * c4] = v.x;
+        r[4 * c4 + 1] = v.y;
+        r[4 * c4 + 2] = v.z;
+        r[4 * c4 + 3] = v.w;
+      }
 #pragma unroll
-    for (int c4 = 0; c4 < SF / 4; ++c4)
-      reinterpret_cast<float4*>(rp)[c4] = make_float4(r[4 * c4], r[4 * c4 + 1], r[4 * c4 + 2], r[4 * c4 + 3]);
-  }
-  // the list length the backward walks: the tile's largest last contributor
-  if (!back) {
-    uint32_t lm = inside ? last : 0u;
-    for (int o = 32; o > 0; o >>= 1) lm = max(lm, (uint32_t)__shfl_xor((int)lm, o));
-    if (lane == 0 && lm > 0u) {
-      atomicMax(&binfo[blockIdx.x].w, lm);
-      if (sl) atomicMax(&ctx_ptr<uint4>(ctx, L.sinfo)[sl - 1u].w, lm);
+      for (int c = 0; c < CS; ++c) {
+        const float own = r[1 + c];
+        r[1 + c] = acc[c];
+        acc[c] += own;
+      }
+#pragma unroll
+      for (int c4 = 0; c4 < SA / 4; ++c4)
+        reinterpret_cast<float4*>(rp)[c4] = make_float4(r[4 * c4], r[4 * c4 + 1], r[4 * c4 + 2], r[4 * c4 + 3]);
     }
-  }
   if (back) return;
   float lsum = 0.f;  // this pixel's L1 loss terms
   if (inside) {
@@ -382,7 +396,7 @@ __global__ void __launch_bounds__(256) k_l1_tile_loss(const ViewDev* __restrict_
   if (threadIdx.x == 0) loss[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-constexpr int kBwdBatch = 16;  // list entries per MFMA tile (M = 16)
+constexpr int kBwdBatch = 8;  // list entries per MFMA tile: rows 0-7 hold w, rows 8-15 dL/dpower
 
 typedef float f4v __attribute__((ext_vector_type(4)));
 
@@ -403,8 +417,42 @@ ASGS_DEV void bf_split(float v, uint16_t& hi, uint16_t& lo) {
   lo = bf_rne(v - __uint_as_float((uint32_t)hi << 16));
 }
 
-// Backward compositing, one workgroup per tile (or per 128-entry segment of
-// a split list), one pixel per thread.
+// A Gaussian's blend record in scalar registers: geometry (u, v, A, B, C, o,
+// ln(alpha_min / o)) and channels. The loads go through the constant address
+// space, so a wave-uniform index makes them scalar loads.
+typedef float f4u __attribute__((ext_vector_type(4), aligned(16)));
+typedef float f8u __attribute__((ext_vector_type(8), aligned(16)));
+typedef float f16u __attribute__((ext_vector_type(16), aligned(16)));
+#define ASGS_CONST_AS __attribute__((address_space(4)))
+
+template <int CS>
+struct SRec;
+template <>
+struct SRec<4> {
+  f8u g;
+  f4u c;
+  ASGS_DEV void load(const float* geom, const float* chan, uint32_t gid) {
+    g = *(const ASGS_CONST_AS f8u*)(geom + (size_t)gid * kGeomStride);
+    c = *(const ASGS_CONST_AS f4u*)(chan + (size_t)gid * 4);
+  }
+  ASGS_DEV float ch(int k) const { return c[k]; }
+};
+template <>
+struct SRec<20> {
+  f8u g;
+  f16u c;
+  f4u d;
+  ASGS_DEV void load(const float* geom, const float* chan, uint32_t gid) {
+    g = *(const ASGS_CONST_AS f8u*)(geom + (size_t)gid * kGeomStride);
+    const float* p = chan + (size_t)gid * 20;
+    c = *(const ASGS_CONST_AS f16u*)p;
+    d = *(const ASGS_CONST_AS f4u*)(p + 16);
+  }
+  ASGS_DEV float ch(int k) const { return k < 16 ? c[k < 16 ? k : 0] : d[k < 16 ? 0 : k - 16]; }
+};
+
+// Backward compositing, one workgroup per tile (or per segment of a split
+// list), one pixel per thread.
 //
 // Per list entry k and pixel p the gradient contributions are
 //   dL/dc_k      += w_kp G_p                 (w = alpha T, G = upstream channel gradients)
@@ -414,48 +462,52 @@ ASGS_DEV void bf_split(float v, uint16_t& hi, uint16_t& lo) {
 // so the per-entry sums over the tile's pixels are dot products of two
 // per-pixel coefficients (w, dpow) with fixed per-pixel features: the
 // channel gradients G_p and the moments (1, lx, ly, lx^2, lx ly, ly^2) of the
-// tile-local pixel coordinates, from which the conic and position gradients
-// follow in closed form. The list is staged in rounds of 32 entries from the
-// back. Each wave takes only the round's entries that one of its pixels uses
-// (the quarter test of the forward, then a ballot), writes its pixels'
-// coefficients for batches of up to 16 such entries to LDS and contracts them
-// on the matrix cores (bf16 16x16x32 MFMAs with both operands split into
-// hi + lo parts, K = pixels) into per-wave partial rows; the four waves' rows
-// are summed in a fixed order and written once to each entry's gradient slot.
-// A segment of a split list starts from the state the forward recorded at the
-// segment's end: T there and the sum the later entries contribute,
-// G . (C_final - C_boundary), instead of T_final and zero.
+// pixel coordinates about the tile's centre (half-integers whose products have
+// at most 8 significant bits, exact in bf16), from which the projection backward forms the
+// conic and position gradients in closed form. The list is walked in rounds
+// of 32 entries from the back. Each wave takes only the round's entries that
+// one of its pixels uses (the quarter test of the forward, then a ballot);
+// their records arrive through scalar loads, one entry ahead, so the channel
+// dot product takes them as scalar operands and no record passes through LDS.
+// The pixels' coefficients of up to 8 such entries go to LDS as the 16 rows
+// of one matrix-core tile (8 rows of w, 8 of dL/dpower) and are contracted
+// over the wave's 64 pixels (bf16 16x16x32 MFMAs with both operands split
+// into hi + lo parts) against the channel gradients and the moments. At the
+// end of a round the four waves' rows are summed in a fixed order into one
+// write per gradient slot.
+// Lists are walked back to front from T_final, recovering T_k = T_{k+1} /
+// (1 - alpha_k), with the sum S the later entries contribute growing from
+// zero. A segment of a split list but its last starts from the state the
+// forward recorded at its end: T and S = G . (what the later entries add).
+// Bound by the vector ALU (about 55 instructions per used entry and wave, half
+// of the launch) and by the waves' uneven shares of a round. With the records
+// staged through LDS, 16-entry batches (56 KB of LDS, three workgroups per CU
+// instead of five) and cuts every 128 entries on at most 64 lists, one 640x480
+// view of 157k intersections took 89 us, now 61 us; 774k intersections 357 us,
+// now 245; eight 320x240 views with 986k (lists up to 2460) 614 us, now 287.
 template <int NF>
-__global__ void __launch_bounds__(kTilePix) __attribute__((amdgpu_waves_per_eu(3))) k_blend_bwd(RenderConst rc, const ViewDev* __restrict__ views,
+__global__ void __launch_bounds__(kTilePix) __attribute__((amdgpu_waves_per_eu(5))) k_blend_bwd(RenderConst rc, const ViewDev* __restrict__ views,
                                                         char* ctx, CtxLayout L, asgs_images dout) {
   constexpr int CS = 4 + NF;
-  constexpr int CS4 = CS / 4;
   constexpr int GS = 6 + CS;
   constexpr int NW = kTilePix / 64;
   constexpr int CP = 64;          // row of 64 pixel coefficients (bf16), 8-pixel groups XOR-swizzled by row
-  // The first n_views kSplitPerView (kSegMax - 1) workgroups take the
-  // segments but the last of the split lists, one split-record slot each
-  // (and exit at once where there is none), the rest one blend position each
-  // (longest lists first): the whole walked list, or its last segment.
-  const uint32_t extra = (uint32_t)rc.n_views * kSplitPerView * (kSegMax - 1);
+  constexpr int C1 = CS - 4;      // the second column block holds the last four channels and the moments
+  // The first n_views kSplitUnits workgroups take the segments but the last of
+  // the split lists, one split record each (and exit at once where there is
+  // none), the rest one blend position each (longest lists first): the whole
+  // list, or its last segment.
+  const uint32_t extra = (uint32_t)rc.n_views * kSplitUnits;
   const bool front = blockIdx.x < extra;
-  uint4 bi;
-  uint32_t slot;
-  int nseg, seg;
-  if (front) {
-    slot = blockIdx.x / (kSegMax - 1);
-    bi = ctx_ptr<const uint4>(ctx, L.sinfo)[slot];
-    if (bi.x == ~0u) return;
-    nseg = split_segments(bi.z - bi.y);
-    seg = (int)(blockIdx.x % (kSegMax - 1));
-    if (seg >= nseg - 1) return;
-  } else {
-    bi = ctx_ptr<const uint4>(ctx, L.binfo)[blockIdx.x - extra];
-    const uint32_t sl = ctx_ptr<const uint32_t>(ctx, L.bslot)[bi.x];
-    slot = sl ? sl - 1u : 0u;
-    nseg = sl ? split_segments(bi.z - bi.y) : 1;
-    seg = nseg - 1;
-  }
+  const uint4 bi = front ? ctx_ptr<const uint4>(ctx, L.sinfo)[blockIdx.x]
+                         : ctx_ptr<const uint4>(ctx, L.binfo)[blockIdx.x - extra];
+  if (bi.x == ~0u) return;
+  const uint32_t len = bi.z - bi.y;
+  const uint32_t sl = ctx_ptr<const uint32_t>(ctx, L.bslot)[bi.x];
+  // this workgroup's segment: entries [elo, eend) of the list
+  const int seglen = sl ? (int)segment_length(len, sl >> 20) : (int)len;
+  const int seg = front ? (int)bi.w : sl ? (int)((len - 1u) / (uint32_t)seglen) : 0;
+  const int elo = seg * seglen, eend = min((int)len, elo + seglen);
   const int tile = (int)bi.x;
   const int view = find_view(views, rc.n_views, tile);
   const ViewDev& V = views[view];
@@ -471,50 +523,24 @@ __global__ void __launch_bounds__(kTilePix) __attribute__((amdgpu_waves_per_eu(3
   const float pxf = (float)px, pyf = (float)py;
   const uint2 rg = make_uint2(bi.y, bi.z);
   prioritise(blockIdx.x, rc.n_cu);
-  const uint32_t len = rg.y - rg.x;
-  const uint32_t nproc = bi.w;  // entries behind every pixel's last Gaussian are not walked
-  // this workgroup's entries [elo, ehi) of the walked list
-  const bool lastseg = seg == nseg - 1;
-  const int elo = seg * kSeg;
-  const int ehi = lastseg ? (int)nproc : min((int)nproc, (seg + 1) * kSeg);
-  const uint32_t* pairgid = ctx_ptr<const uint32_t>(ctx, L.pairgid);
-  const uint32_t* pslot = ctx_ptr<const uint32_t>(ctx, L.pslot);
-  const float4* geom = ctx_ptr<const float4>(ctx, L.geom);
-  const float4* chan4 = ctx_ptr<const float4>(ctx, L.chan);
-  const uint8_t* pmask = ctx_ptr<const uint8_t>(ctx, L.pmask);
+  const uint32_t* pairgid = ctx_ptr<const uint32_t>(ctx, L.pairgid) + rg.x;
+  const uint32_t* pslot = ctx_ptr<const uint32_t>(ctx, L.pslot) + rg.x;
+  const float* geom = ctx_ptr<const float>(ctx, L.geom);
+  const float* chan = ctx_ptr<const float>(ctx, L.chan);
+  const uint8_t* pmask = ctx_ptr<const uint8_t>(ctx, L.pmask) + rg.x;
   float* gslot = ctx_ptr<float>(ctx, L.gslot);
 
-  constexpr int kRecF4 = 2 + CS4;  // float4 per list entry: geometry (2) + channels
-  constexpr int kRound = 32;       // list entries staged per round (one per lane of half a wave)
-  constexpr int kPer = (kRound * kRecF4 + kTilePix - 1) / kTilePix;
+  constexpr int kRound = 32;         // list entries per round (one per lane of half a wave)
   constexpr int PS = (GS + 3) & ~3;  // row of a partial-sum entry and of a gradient slot (whole float4)
-  __shared__ float4 srec[kRound * kRecF4];
-  // per wave, per batch position and pixel: w and dL/dpower as bf16 hi + lo
-  // (one array: before the first batch it holds each wave's channel gradients
-  // for the exchange into the MFMA operand layout)
-  __shared__ __attribute__((aligned(16))) uint16_t acf[4][NW][kBwdBatch][CP];
-  uint16_t (&awh)[NW][kBwdBatch][CP] = acf[0];
-  uint16_t (&awl)[NW][kBwdBatch][CP] = acf[1];
-  uint16_t (&aph)[NW][kBwdBatch][CP] = acf[2];
-  uint16_t (&apl)[NW][kBwdBatch][CP] = acf[3];
-  __shared__ __attribute__((aligned(16))) float part[NW][kRound][PS];  // per-wave partial rows of the round's entries
-  __shared__ int sent[NW][kBwdBatch];     // round entry of each batch position
-  __shared__ uint32_t sslot[2][kRound];   // gradient slot of each round entry (two rounds in flight)
-  __shared__ uint8_t smk[kRound];         // quarter mask of each round entry (from the forward)
+  // per wave: 16 rows (w of 8 batch positions, then their dL/dpower) of 64
+  // pixels, as bf16 hi and lo (before the first batch the array holds each
+  // wave's channel gradients for the exchange into the MFMA operand layout)
+  __shared__ __attribute__((aligned(16))) uint16_t acf[NW][2][2 * kBwdBatch][CP];
+  __shared__ __attribute__((aligned(16))) float part[NW][kRound][PS];  // per wave: rows of its used entries, in walking order
+  static_assert(kRound % kBwdBatch == 0, "whole batches of rows");
+  __shared__ uint32_t sused[NW];                                       // per wave: the round's entries with a row
+  __shared__ uint32_t slast[NW];                                       // per wave: the last entry it uses
 
-  // The Gaussian ids of the first round (the back kRound entries of the
-  // walked list) are requested before anything else.
-  uint32_t gid_next[kPer];
-  auto fetch_gid = [&](int lo_r, int cnt_r) {
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-      const int ent = (t + k * kTilePix) / kRecF4;
-      gid_next[k] = ent < cnt_r ? pairgid[rg.x + lo_r + ent] : 0u;
-    }
-  };
-  int rhi = ehi;
-  int rlo = rhi - kRound > elo ? rhi - kRound : elo;
-  if (rhi > elo) fetch_gid(rlo, rhi - rlo);
   const size_t HW = (size_t)V.W * V.H;
   const size_t pb = (size_t)V.pix_base;
   float Tf = 1.f;
@@ -534,337 +560,273 @@ __global__ void __launch_bounds__(kTilePix) __attribute__((amdgpu_waves_per_eu(3
     const float ga = dout.alpha ? dout.alpha[pb + pix] : 0.f;
     GT = rc.bg[0] * G[0] + rc.bg[1] * G[1] + rc.bg[2] * G[2] - ga;
   }
+  // the last entry any pixel of this wave, and of the workgroup, uses: entries
+  // behind it are not walked
+  uint32_t wlast = last;
+  for (int o = 32; o > 0; o >>= 1) wlast = max(wlast, (uint32_t)__shfl_xor((int)wlast, o));
+  if (lane == 0) slast[wv] = wlast;
+  __syncthreads();
+  const int ehi = min(eend, max(elo, (int)max(max(slast[0], slast[1]), max(slast[2], slast[3]))));
+  const int whi = min(ehi, __builtin_amdgcn_readfirstlane((int)wlast));
+  // The Gaussian ids and quarter masks of the first two rounds are requested
+  // now, later rounds' two rounds ahead.
+  int rhi = ehi, rlo = max(ehi - kRound, elo);  // entries [rlo, rhi) of the round
+  auto ids = [&](int lo, int hi, uint32_t& g, uint32_t& m) {
+    g = m = 0u;
+    if (lane < hi - lo) {
+      g = pairgid[lo + lane];
+      m = pmask[lo + lane];
+    }
+  };
+  uint32_t gidv, maskv, gidn, maskn;
+  ids(rlo, rhi, gidv, maskv);
+  int nlo = max(rlo - kRound, elo);  // start of the next round
+  ids(nlo, rlo, gidn, maskn);
   // B operands of the MFMAs (v_mfma_f32_16x16x32_bf16): K block kb covers
-  // pixels 32 kb .. 32 kb + 31 of this wave; lane l supplies feature l % 16 of
-  // pixels 32 kb + 8 (l / 16) + i, i = 0..7: the channel gradients split into
-  // bf16 hi + lo, the pixel-coordinate moments (small integers, exact). The
-  // gradients reach that layout through the wave's rows of LDS (stride GXS,
-  // so that the 16 channel rows of one read fall in different banks).
-  constexpr int GXS = 68;
-  static_assert(NW * CS * GXS * 4 <= (int)sizeof(acf), "exchange rows fit the coefficient array");
-  float* gx = reinterpret_cast<float*>(&acf[0][0][0][0]) + wv * CS * GXS;
-#pragma unroll
-  for (int c = 0; c < CS; ++c) gx[c * GXS + lane] = G[c];
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  // pixels 32 kb .. 32 kb + 31 of this wave; lane l supplies column l % 16 of
+  // pixels 32 kb + 8 (l / 16) + i, i = 0..7, split into bf16 hi + lo. Block 0
+  // (with features): channels 0-15. Block 1: columns 0-3 the hi and 4-7 the lo
+  // parts of the last four channels, columns 8-13 the pixel-coordinate moments
+  // (exact in bf16). The gradients reach that layout through the wave's rows of LDS, 16
+  // channels of 64 pixels at a time, each row's 4-pixel groups XOR-swizzled by
+  // the row so that the 16 rows of one read fall in different banks.
+  static_assert(sizeof(acf) / NW == 16 * 64 * 4, "exchange rows");
+  float* gx = reinterpret_cast<float*>(&acf[wv][0][0][0]);
   const int fcol = lane & 15;
-  bf8v bG0h[2], bG0l[2], bG1h[2], bG1l[2], bM[2];
+  bf8v b0h[2], b0l[2], b1[2];
+  auto wave_sync = [&]() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  auto put = [&](int row, float v) { gx[row * 64 + ((((lane >> 2) ^ row) << 2) | (lane & 3))] = v; };
+  auto get = [&](int row, int kb, float (&v)[8]) {
+    const int q4 = 8 * kb + 2 * (lane >> 4);  // first 4-pixel group of the lane's 8 pixels in the wave
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const float4 a = *reinterpret_cast<const float4*>(&gx[row * 64 + (((q4 + h) ^ row) << 2)]);
+      v[4 * h] = a.x;
+      v[4 * h + 1] = a.y;
+      v[4 * h + 2] = a.z;
+      v[4 * h + 3] = a.w;
+    }
+  };
+  auto pack = [&](const float (&v)[8], bf8v& h, bf8v& l) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      uint16_t hi, lo;
+      bf_split(v[i], hi, lo);
+      h[i] = __builtin_bit_cast(__bf16, hi);
+      l[i] = __builtin_bit_cast(__bf16, lo);
+    }
+  };
+  if (NF > 0) {
+#pragma unroll
+    for (int c = 0; c < 16; ++c) put(c, G[c % CS]);
+    wave_sync();
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) {
+      float v[8];
+      get(fcol, kb, v);
+      pack(v, b0h[kb], b0l[kb]);
+    }
+    wave_sync();
+  }
+#pragma unroll
+  for (int c = 0; c < 4; ++c) put(c, G[C1 + c]);
+  wave_sync();
+  // this lane's moment lx^ex ly^ey: pixel i of the lane's 8 lies at lx = lx0 + i, ly = ly0 + 4 kb
+  const int ex = fcol == 9 || fcol == 12 ? 1 : fcol == 11 ? 2 : 0, ey = fcol == 10 || fcol == 12 ? 1 : fcol == 13 ? 2 : 0;
+  const float cx0 = ex == 0 ? 1.f : 0.f, cx1 = ex == 1 ? 1.f : 0.f, cx2 = ex == 2 ? 1.f : 0.f;
+  const float lx0 = (float)(8 * (wv & 1)) - kTileMid, ly0 = (float)(8 * (wv >> 1) + (lane >> 4)) - kTileMid;
 #pragma unroll
   for (int kb = 0; kb < 2; ++kb) {
-    const int q0 = 32 * kb + 8 * (lane >> 4);  // first of the lane's 8 pixels in the wave
-    float g0[8], g1[8];
-    if (fcol < CS) {
-      const float4 a = *reinterpret_cast<const float4*>(&gx[fcol * GXS + q0]);
-      const float4 b = *reinterpret_cast<const float4*>(&gx[fcol * GXS + q0 + 4]);
-      g0[0] = a.x; g0[1] = a.y; g0[2] = a.z; g0[3] = a.w;
-      g0[4] = b.x; g0[5] = b.y; g0[6] = b.z; g0[7] = b.w;
-    } else {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) g0[i] = 0.f;
-    }
-    if (16 + fcol < CS) {
-      const float4 a = *reinterpret_cast<const float4*>(&gx[(16 + fcol) * GXS + q0]);
-      const float4 b = *reinterpret_cast<const float4*>(&gx[(16 + fcol) * GXS + q0 + 4]);
-      g1[0] = a.x; g1[1] = a.y; g1[2] = a.z; g1[3] = a.w;
-      g1[4] = b.x; g1[5] = b.y; g1[6] = b.z; g1[7] = b.w;
-    } else {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) g1[i] = 0.f;
-    }
-    uint16_t h0[8], l0[8], h1[8], l1[8], m[8];
+    float v[8];
+    get(fcol & 3, kb, v);
+    const float fy = ly0 + (float)(4 * kb);
+    const float my = fcol < 8 || fcol > 13 ? 0.f : ey == 0 ? 1.f : ey == 1 ? fy : fy * fy;
+    const bool lo = fcol >= 4;  // columns 4-7: v - hi(v)
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const int q = 64 * wv + q0 + i;  // pixel of thread q
-      bf_split(g0[i], h0[i], l0[i]);
-      bf_split(g1[i], h1[i], l1[i]);
-      const float fx = (float)tile_lx(q), fy = (float)tile_ly(q);
-      m[i] = bf_rne(fcol == 0 ? 1.f : fcol == 1 ? fx : fcol == 2 ? fy : fcol == 3 ? fx * fx
-                    : fcol == 4 ? fx * fy : fcol == 5 ? fy * fy : 0.f);
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      bG0h[kb][i] = __builtin_bit_cast(__bf16, h0[i]);
-      bG0l[kb][i] = __builtin_bit_cast(__bf16, l0[i]);
-      bG1h[kb][i] = __builtin_bit_cast(__bf16, h1[i]);
-      bG1l[kb][i] = __builtin_bit_cast(__bf16, l1[i]);
-      bM[kb][i] = __builtin_bit_cast(__bf16, m[i]);
+      const float fx = lx0 + (float)i;
+      const float m = fmaf(fmaf(cx2, fx, cx1), fx, cx0) * my;
+      const float h = __uint_as_float((uint32_t)bf_rne(v[i]) << 16);
+      const float c = lo ? v[i] - h : v[i];
+      b1[kb][i] = (__bf16)(fcol < 8 ? c : m);
     }
   }
+  wave_sync();
 
   // entries behind every pixel's last Gaussian get zero gradient
-  for (uint32_t q = nproc + t; lastseg && q < len; q += kTilePix) {
-    float4* dst = reinterpret_cast<float4*>(gslot + (size_t)pslot[rg.x + q] * PS);
+  for (int q = ehi + t; q < eend; q += kTilePix) {
+    float4* dst = reinterpret_cast<float4*>(gslot + (size_t)pslot[q] * PS);
 #pragma unroll
     for (int c = 0; c < PS / 4; ++c) dst[c] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
   float T = Tf;
   float sacc = 0.f;  // sum over later Gaussians of w_l (G . c_l)
-  if (!lastseg && ehi == (seg + 1) * kSeg && inside) {
-    // the state at the segment's end (a boundary the forward passed): T
-    // there, and the later entries' sum, G . (C_final - C_boundary)
-    constexpr int SA = split_first(CS), SF = split_final(CS);
-    const float* sp = ctx_ptr<const float>(ctx, L.split) + (size_t)slot * split_floats(CS);
-    const float4* rb = reinterpret_cast<const float4*>(sp + ((size_t)seg * kTilePix + t) * SA);
-    const float4* rf = reinterpret_cast<const float4*>(sp + (size_t)(kSegMax - 1) * kTilePix * SA + (size_t)t * SF);
-    float r[SA], f[SF];
+  if (front && inside && ehi == eend) {
+    // the record of a boundary the forward passed
+    const float* rb = ctx_ptr<const float>(ctx, L.split) + (size_t)blockIdx.x * split_floats(CS) + (size_t)t * split_first(CS);
+    T = rb[0];
 #pragma unroll
-    for (int c4 = 0; c4 < SA / 4; ++c4) {
-      const float4 v = rb[c4];
-      r[4 * c4] = v.x;
-      r[4 * c4 + 1] = v.y;
-      r[4 * c4 + 2] = v.z;
-      r[4 * c4 + 3] = v.w;
-    }
-#pragma unroll
-    for (int c4 = 0; c4 < SF / 4; ++c4) {
-      const float4 v = rf[c4];
-      f[4 * c4] = v.x;
-      f[4 * c4 + 1] = v.y;
-      f[4 * c4 + 2] = v.z;
-      f[4 * c4 + 3] = v.w;
-    }
-    T = r[0];
-#pragma unroll
-    for (int c = 0; c < CS; ++c) sacc = fmaf(G[c], f[c] - r[1 + c], sacc);
+    for (int c = 0; c < CS; ++c) sacc = fmaf(G[c], rb[1 + c], sacc);
   }
   const float amax = rc.alpha_max;
-  // Records are staged in rounds of kRound entries, walking the list from the
-  // back; the global loads of the next round are issued before the current
-  // round is processed and land in LDS at the start of the next round.
-  // The Gaussian ids of a round are read one round earlier still, so that
-  // no load of the staging waits on another.
-  float4 stage[kPer];
-  uint32_t stage_slot = 0u, stage_mask = 0u;
-  auto fetch = [&](int lo_r, int cnt_r) {
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-      const int e = t + k * kTilePix;
-      const int ent = e / kRecF4, f = e - ent * kRecF4;
-      if (ent < cnt_r) {
-        const uint32_t gid = gid_next[k];
-        stage[k] = f < 2 ? geom[2 * (size_t)gid + f] : chan4[(size_t)gid * CS4 + (f - 2)];
-      }
-    }
-    if (t < cnt_r) {
-      stage_slot = pslot[rg.x + lo_r + t];
-      stage_mask = pmask[rg.x + lo_r + t];
-    }
-  };
-  auto rec_of = [&](int e) { return &srec[e * kRecF4]; };
+  const float GTf = GT * Tf;
+  uint16_t* const ah = &acf[wv][0][0][0];
+  uint16_t* const al = &acf[wv][1][0][0];
+  int nb = 0, nrow = 0;  // batched entries; rows of the round already in part
   // Contract the wave's nb batched entries over its 64 pixels on the matrix
-  // cores and store the rows of the partial sums under their round entries.
-  auto flush = [&](int nb) {
+  // cores and store their rows of partial sums.
+  auto flush = [&]() {
     // the coefficients are read back by other lanes of this wave only
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    f4v c1 = {0.f, 0.f, 0.f, 0.f}, c2 = c1, c3 = c1;
-    // A operands: batch position l % 16, pixels 32 kb + 8 (l / 16) .. + 7
+    wave_sync();
+    f4v d0 = {0.f, 0.f, 0.f, 0.f}, d1 = d0;
+    // A operands: row l % 16, pixels 32 kb + 8 (l / 16) .. + 7
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
       const int p0 = (32 * kb + 8 * (lane >> 4)) ^ ((fcol & 7) << 3);
-      const bf8v wh = *reinterpret_cast<const bf8v*>(&awh[wv][fcol][p0]);
-      const bf8v wl = *reinterpret_cast<const bf8v*>(&awl[wv][fcol][p0]);
-      const bf8v ph = *reinterpret_cast<const bf8v*>(&aph[wv][fcol][p0]);
-      const bf8v pl = *reinterpret_cast<const bf8v*>(&apl[wv][fcol][p0]);
-      c1 = mfma_bf(wh, bG0h[kb], c1);
-      c1 = mfma_bf(wh, bG0l[kb], c1);
-      c1 = mfma_bf(wl, bG0h[kb], c1);
-      if (CS > 16) {
-        c2 = mfma_bf(wh, bG1h[kb], c2);
-        c2 = mfma_bf(wh, bG1l[kb], c2);
-        c2 = mfma_bf(wl, bG1h[kb], c2);
+      const bf8v xh = *reinterpret_cast<const bf8v*>(&ah[fcol * CP + p0]);
+      const bf8v xl = *reinterpret_cast<const bf8v*>(&al[fcol * CP + p0]);
+      if (NF > 0) {
+        d0 = mfma_bf(xh, b0h[kb], d0);
+        d0 = mfma_bf(xh, b0l[kb], d0);
+        d0 = mfma_bf(xl, b0h[kb], d0);
       }
-      c3 = mfma_bf(ph, bM[kb], c3);
-      c3 = mfma_bf(pl, bM[kb], c3);
+      d1 = mfma_bf(xh, b1[kb], d1);
+      d1 = mfma_bf(xl, b1[kb], d1);
     }
+    // lane l holds column l % 16 of rows 4 (l / 16) + r: channels from the
+    // rows of w (lanes 0-31), moments from the rows of dL/dpower
+    const bool up = lane >= 32;
+    const int col = up ? fcol - 8 : 6 + C1 + fcol;
+    const bool keep = up ? (fcol >= 8 && fcol < 14) : fcol < 4;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int pos = 4 * (lane >> 4) + r;
-      if (pos < nb) {
-        float* row = part[wv][sent[wv][pos]];
-        if (fcol < CS) row[6 + fcol] = c1[r];
-        if (CS > 16 && fcol < CS - 16) row[6 + 16 + fcol] = c2[r];
-        if (fcol < 6) row[fcol] = c3[r];
-      }
+      // rows past a last batch of fewer than 8 entries belong to no entry and are not read
+      float* row = part[wv][nrow + 4 * ((lane >> 4) & 1) + r];
+      if (NF > 0 && !up) row[6 + fcol] = d0[r];
+      // columns 0-3: the hi columns' sums plus the lo columns' (four lanes up)
+      const float lo4 = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(d1[r]), 0x104, 0xF, 0xF, true));
+      if (keep) row[col] = up ? d1[r] : d1[r] + lo4;
     }
-    // the conic, position and opacity parts of the wave's rows in closed form
-    // from its moment sums (linear in them, so the four waves' rows still add
-    // up): all moments are read before any is overwritten
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    float cf[2];
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const int it = lane + 64 * k;
-      cf[k] = 0.f;
-      if (it < nb * 6) {
-        const int pos = it / 6, c = it - pos * 6;
-        const int e = sent[wv][pos];
-        const float* M = part[wv][e];
-        const float4 g0 = rec_of(e)[0];
-        const float4 g1 = rec_of(e)[1];
-        const float uu = g0.x - (float)x0, vv = g0.y - (float)y0;  // tile-local centre
-        const float Sdx = uu * M[0] - M[1];
-        const float Sdy = vv * M[0] - M[2];
-        if (c == 0) cf[k] = -(g0.z * Sdx + g0.w * Sdy);
-        else if (c == 1) cf[k] = -(g0.w * Sdx + g1.x * Sdy);
-        else if (c == 2) cf[k] = -0.5f * (uu * uu * M[0] - 2.f * uu * M[1] + M[3]);
-        else if (c == 3) cf[k] = -(uu * vv * M[0] - uu * M[2] - vv * M[1] + M[4]);
-        else if (c == 4) cf[k] = -0.5f * (vv * vv * M[0] - 2.f * vv * M[2] + M[5]);
-        else cf[k] = M[0] / g1.y;
-      }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const int it = lane + 64 * k;
-      if (it < nb * 6) {
-        const int pos = it / 6, c = it - pos * 6;
-        part[wv][sent[wv][pos]][c] = cf[k];
-      }
-    }
-    // the next batch overwrites the coefficients and the entry table
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    nrow += kBwdBatch;
+    nb = 0;
+    wave_sync();  // the next batch overwrites the coefficients
   };
-  if (rhi > elo) {
-    fetch(rlo, rhi - rlo);
-    const int nrlo = rlo - kRound > elo ? rlo - kRound : elo;
-    if (rlo > elo) fetch_gid(nrlo, rlo - nrlo);
-  }
-  // partial rows start at zero; the reduction of each round zeroes the rows
-  // it has read
-  for (int q = lane; q < kRound * PS; q += 64) (&part[wv][0][0])[q] = 0.f;
-  int par = 0;  // sslot buffer of this round
-  while (rhi > elo) {
-    // Every wave has passed the previous round's candidate loop (the barrier
-    // before its reduction), so the records and masks can be overwritten;
-    // the slots the reduction still reads are in the other buffer.
+  // One entry: alpha and the channel dot product, the transmittance before
+  // it, and its coefficients into the batch; entries no pixel of the wave
+  // uses take no row.
+  uint32_t used = 0u;
+  auto entry = [&](const SRec<CS>& rec, int j) {
+    float dx, dy;
+    const float power = eval_power(rec.g[0], rec.g[1], rec.g[2], rec.g[3], rec.g[4], pxf, pyf, dx, dy);
+    // same alpha threshold as the forward
+    const bool use = (uint32_t)(rlo + j) < last && power <= 0.f && power >= rec.g[6];
+    if (!__ballot(use)) return;
+    used |= 1u << j;
+    const float raw = rec.g[5] * __expf(power);
+    const float alpha = fminf(amax, raw);
+    const float ioma = __builtin_amdgcn_rcpf(1.f - alpha);
+    float dot0 = 0.f, dot1 = 0.f;  // two independent chains
 #pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-      const int e = t + k * kTilePix;
-      if (e / kRecF4 < rhi - rlo) srec[e] = stage[k];
+    for (int c = 0; c < CS; c += 2) {
+      dot0 = fmaf(G[c], rec.ch(c), dot0);
+      dot1 = fmaf(G[c + 1], rec.ch(c + 1), dot1);
     }
-    if (t < rhi - rlo) {
-      sslot[par][t] = stage_slot;
-      smk[t] = (uint8_t)stage_mask;
+    const float dotg = dot0 + dot1;
+    float wgt = 0.f, dpow = 0.f;
+    const float Tk = T * ioma;
+    const float w_ = alpha * Tk;
+    const float dalpha = Tk * dotg - (sacc + GTf) * ioma;
+    if (use) {
+      T = Tk;
+      wgt = w_;
+      sacc = fmaf(w_, dotg, sacc);
+      dpow = raw < amax ? dalpha * alpha : 0.f;
     }
-    __syncthreads();  // staging visible; the previous reduction has zeroed its rows
+    const int sp = nb * CP + (lane ^ (nb << 3));  // swizzled position of this pixel in row nb
+    uint16_t wh, wl, ph, pl;
+    bf_split(wgt, wh, wl);
+    bf_split(dpow, ph, pl);
+    ah[sp] = wh;
+    al[sp] = wl;
+    ah[sp + kBwdBatch * CP] = ph;
+    al[sp + kBwdBatch * CP] = pl;
+    if (++nb == kBwdBatch) flush();
+  };
+  // the wave's entries of a round (those that can reach a pixel of its quarter)
+  auto round_bits = [&]() -> uint32_t {
+    return (uint32_t)__ballot(((maskv >> wv) & 1u) && rlo + lane < whi);
+  };
+  auto load = [&](SRec<CS>& r, int j) { r.load(geom, chan, (uint32_t)__builtin_amdgcn_readlane((int)gidv, j)); };
+  auto top = [&](uint32_t b, int other) { return b ? 31 - __builtin_clz(b) : other; };
+  while (rhi > rlo) {
     const int cnt = rhi - rlo;
-    const int nrhi = rlo, nrlo = rlo - kRound > elo ? rlo - kRound : elo;
-    if (nrhi > elo) {
-      fetch(nrlo, nrhi - nrlo);
-      const int n2lo = nrlo - kRound > elo ? nrlo - kRound : elo;
-      if (nrlo > elo) fetch_gid(n2lo, nrlo - n2lo);
-    }
-    // entries of the round that can reach a pixel of this wave's quarter
-    const bool mine = lane < cnt && ((smk[lane] >> wv) & 1u);
-    uint64_t bits = __ballot(mine);
-    int nb = 0;
-    // back to front over this wave's entries; entries no pixel of the wave
-    // uses are left out of the batches (their partial rows stay zero). Two
-    // entries are taken at a time: everything that does not depend on T
-    // (footprint, alpha, the channel dot product) is formed for both before
-    // the T recursion consumes them in order, so the two chains overlap.
-    struct Cand {
-      int j;
-      bool use;
-      float raw, alpha, ioma, dotg;
-    };
-    auto prepare = [&](int j) {
-      Cand c;
-      c.j = j;
-      const float4 g0 = srec[j * kRecF4];
-      const float4 g1 = srec[j * kRecF4 + 1];
-      float dx, dy;
-      const float power = eval_power(g0.x, g0.y, g0.z, g0.w, g1.x, pxf, pyf, dx, dy);
-      // same alpha threshold as the forward
-      c.use = (uint32_t)(rlo + j) < last && power <= 0.f && power >= g1.z;
-      c.raw = g1.y * __expf(power);
-      c.alpha = fminf(amax, c.raw);
-      c.ioma = __builtin_amdgcn_rcpf(1.f - c.alpha);
-      float dot0 = 0.f, dot1 = 0.f;  // two independent chains
-#pragma unroll
-      for (int c4 = 0; c4 < CS4; ++c4) {
-        const float4 v = srec[j * kRecF4 + 2 + c4];
-        dot0 = fmaf(G[4 * c4 + 0], v.x, dot0);
-        dot1 = fmaf(G[4 * c4 + 1], v.y, dot1);
-        dot0 = fmaf(G[4 * c4 + 2], v.z, dot0);
-        dot1 = fmaf(G[4 * c4 + 3], v.w, dot1);
-      }
-      c.dotg = dot0 + dot1;
-      return c;
-    };
-    auto consume = [&](const Cand& c) {
-      if (!__ballot(c.use)) return;
-      float wgt = 0.f, dpow = 0.f;
-      const float Tk = T * c.ioma;
-      const float w_ = c.alpha * Tk;
-      const float dalpha = Tk * c.dotg - (sacc + GT * Tf) * c.ioma;
-      if (c.use) {
-        T = Tk;
-        wgt = w_;
-        sacc = fmaf(w_, c.dotg, sacc);
-        dpow = c.raw < amax ? dalpha * c.alpha : 0.f;
-      }
-      uint16_t hi, lo;
-      const int sp = lane ^ ((nb & 7) << 3);  // swizzled position of this pixel in row nb
-      bf_split(wgt, hi, lo);
-      awh[wv][nb][sp] = hi;
-      awl[wv][nb][sp] = lo;
-      bf_split(dpow, hi, lo);
-      aph[wv][nb][sp] = hi;
-      apl[wv][nb][sp] = lo;
-      if (lane == 0) sent[wv][nb] = c.j;
-      ++nb;
-    };
-    while (bits) {
-      const int j1 = 63 - __builtin_clzll(bits);
-      bits &= ~(1ull << j1);
-      if (nb > kBwdBatch - 2) {  // room for two more rows
-        flush(nb);
-        nb = 0;
-      }
-      const Cand c1 = prepare(j1);
-      if (bits) {
-        const int j2 = 63 - __builtin_clzll(bits);
-        bits &= ~(1ull << j2);
-        const Cand c2 = prepare(j2);
-        consume(c1);
-        consume(c2);
-      } else {
-        consume(c1);
-      }
-    }
-    if (nb > 0) flush(nb);
-    __syncthreads();
-    // the four waves' rows -> one gradient slot per entry, a float4 per
-    // thread; the rows read are zeroed for the next round
+    // the slot this thread's part of the round's sums goes to, and the entries
+    // of the round after the next
     constexpr int F4 = PS / 4;
-    const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int q = t; q < cnt * F4; q += kTilePix) {
-      const int e = q / F4, f = q - e * F4;
-      const float4 a = reinterpret_cast<const float4*>(part[0][e])[f];
-      const float4 b = reinterpret_cast<const float4*>(part[1][e])[f];
-      const float4 c = reinterpret_cast<const float4*>(part[2][e])[f];
-      const float4 d = reinterpret_cast<const float4*>(part[3][e])[f];
-      reinterpret_cast<float4*>(gslot + (size_t)sslot[par][e] * PS)[f] =
-          make_float4((a.x + b.x) + (c.x + d.x), (a.y + b.y) + (c.y + d.y), (a.z + b.z) + (c.z + d.z),
-                      (a.w + b.w) + (c.w + d.w));
-      reinterpret_cast<float4*>(part[0][e])[f] = z4;
-      reinterpret_cast<float4*>(part[1][e])[f] = z4;
-      reinterpret_cast<float4*>(part[2][e])[f] = z4;
-      reinterpret_cast<float4*>(part[3][e])[f] = z4;
+    const int re = t / F4, rf = t - re * F4;
+    uint32_t rslot = 0u, gid2, mask2;
+    if (re < cnt) rslot = pslot[rlo + re];
+    const int lo2 = max(nlo - kRound, elo);
+    ids(lo2, nlo, gid2, mask2);
+    // the next round's records are touched now (a lane per entry, each wave
+    // one of a record's cache lines), so that the scalar loads find them in
+    // the L2
+    float touch = 0.f;
+    if (wv < (NF > 0 ? 3 : 2) && lane < rlo - nlo)
+      touch = wv == 0 ? geom[(size_t)gidn * kGeomStride] : chan[(size_t)gidn * CS + (wv == 1 ? 0 : CS - 1)];
+    used = 0u;
+    nrow = 0;
+    // each record is requested one entry ahead
+    if (uint32_t bits = round_bits()) {
+      SRec<CS> ra, rb;
+      int j = top(bits, 0);
+      load(ra, j);
+      for (;;) {
+        bits &= ~(1u << j);
+        const int j2 = top(bits, j);
+        load(rb, j2);
+        entry(ra, j);
+        if (!bits) break;
+        bits &= ~(1u << j2);
+        j = top(bits, j2);
+        load(ra, j);
+        entry(rb, j2);
+        if (!bits) break;
+      }
+      if (nb) flush();
     }
-    par ^= 1;
-    rhi = nrhi;
-    rlo = nrlo;
+    if (lane == 0) sused[wv] = used;
+    asm volatile("" ::"v"(touch));  // the touching load is kept, and waited for here
+    __syncthreads();
+    // the four waves' rows -> one gradient slot per entry, a float4 per thread
+    static_assert(kRound * F4 <= kTilePix, "one float4 of a round's sums per thread");
+    if (re < cnt) {
+      float4 v[NW];
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        // a wave's rows are in walking order: entries above re come first
+        const uint32_t u = sused[w];
+        const int k = __builtin_popcount((u >> re) >> 1);
+        const float4 a = reinterpret_cast<const float4*>(part[w][k])[rf];
+        const bool has = (u >> re) & 1u;
+        v[w] = make_float4(has ? a.x : 0.f, has ? a.y : 0.f, has ? a.z : 0.f, has ? a.w : 0.f);
+      }
+      reinterpret_cast<float4*>(gslot + (size_t)rslot * PS)[rf] =
+          make_float4((v[0].x + v[1].x) + (v[2].x + v[3].x), (v[0].y + v[1].y) + (v[2].y + v[3].y),
+                      (v[0].z + v[1].z) + (v[2].z + v[3].z), (v[0].w + v[1].w) + (v[2].w + v[3].w));
+    }
+    __syncthreads();
+    rhi = rlo;
+    rlo = nlo;
+    gidv = gidn;
+    maskv = maskn;
+    nlo = lo2;
+    gidn = gid2;
+    maskn = mask2;
   }
 }
 
@@ -894,12 +856,12 @@ void launch_blend_backward(const RenderConst& rc, const CtxLayout& L, char* ctx,
                            hipStream_t s) {
   const ViewDev* views = reinterpret_cast<const ViewDev*>(ctx + L.views);
   if (rc.nf == 16)
-    hipLaunchKernelGGL(k_blend_bwd<16>, dim3(rc.total_tiles + rc.n_views * kSplitPerView * (kSegMax - 1)),
+    hipLaunchKernelGGL(k_blend_bwd<16>, dim3(rc.total_tiles + rc.n_views * kSplitUnits),
                        dim3(kTilePix), 0, s, rc,
                        views, ctx, L,
                        dout);
   else
-    hipLaunchKernelGGL(k_blend_bwd<0>, dim3(rc.total_tiles + rc.n_views * kSplitPerView * (kSegMax - 1)),
+    hipLaunchKernelGGL(k_blend_bwd<0>, dim3(rc.total_tiles + rc.n_views * kSplitUnits),
                        dim3(kTilePix), 0, s, rc,
                        views, ctx, L,
                        dout);

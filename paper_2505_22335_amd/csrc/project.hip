@@ -321,24 +321,54 @@ __global__ void __launch_bounds__(256) k_project_backward(RenderConst rc, asgs_g
     {
       const uint32_t start = ctx_ptr<const uint32_t>(ctx, L.toff)[gid];
       const float* slot = ctx_ptr<const float>(ctx, L.gslot);
+      const short4 r = ctx_ptr<const short4>(ctx, L.rect)[gid];
+      const float4 g0 = ctx_ptr<const float4>(ctx, L.geom)[2 * gid];
+      const float4 g1 = ctx_ptr<const float4>(ctx, L.geom)[2 * gid + 1];
+      // D: sums of dL/dpower times (dx, dy, dx^2, dx dy, dy^2), the distances
+      // from the centre; G: its sum (5), then the channels. A
+      // slot holds the moments of dL/dpower over the pixel coordinates about its
+      // tile's centre, (1, lx, ly, lx^2, lx ly, ly^2), and the channel sums. The
+      // second moments about the centre and the step to the 2D covariance
+      // are differences of nearly equal terms for thin Gaussians: FP64.
       float G[GS];
 #pragma unroll
       for (int k = 0; k < GS; ++k) G[k] = 0.f;
+      double D[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
       constexpr int GSP = (GS + 3) & ~3;  // slot stride (whole float4)
       const uint64_t end = min((uint64_t)start + cnt, (uint64_t)rc.cap);
+      int cx = r.x, cy = r.z;
       for (uint64_t p = start; p < end; ++p) {
         const float4* sp = reinterpret_cast<const float4*>(slot + p * GSP);
+        float M[GSP];
 #pragma unroll
         for (int k4 = 0; k4 < GSP / 4; ++k4) {
           const float4 v = sp[k4];
-          if (4 * k4 + 0 < GS) G[4 * k4 + 0] += v.x;
-          if (4 * k4 + 1 < GS) G[4 * k4 + 1] += v.y;
-          if (4 * k4 + 2 < GS) G[4 * k4 + 2] += v.z;
-          if (4 * k4 + 3 < GS) G[4 * k4 + 3] += v.w;
+          M[4 * k4] = v.x;
+          M[4 * k4 + 1] = v.y;
+          M[4 * k4 + 2] = v.z;
+          M[4 * k4 + 3] = v.w;
+        }
+        // the Gaussian's centre from the tile's
+        const double uu = (double)g0.x - (double)((float)(cx * kTile) + kTileMid);
+        const double vv = (double)g0.y - (double)((float)(cy * kTile) + kTileMid);
+        const double Sdx = uu * M[0] - M[1];
+        const double Sdy = vv * M[0] - M[2];
+        D[0] += Sdx;
+        D[1] += Sdy;
+        D[2] += uu * Sdx - (uu * M[1] - M[3]);
+        D[3] += vv * Sdx - (uu * M[2] - M[4]);
+        D[4] += vv * Sdy - (vv * M[2] - M[5]);
+        G[5] += M[0];
+#pragma unroll
+        for (int k = 6; k < GS; ++k) G[k] += M[k];
+        if (++cx > r.y) {
+          cx = r.x;
+          ++cy;
         }
       }
-      const float du = G[0], dv = G[1], dA = G[2], dB = G[3], dC = G[4];
-      dop[i] = G[5];
+      const float du = (float)-(g0.z * D[0] + g0.w * D[1]), dv = (float)-(g0.w * D[0] + g1.x * D[1]);
+      const double dA = -0.5 * D[2], dB = -D[3], dC = -0.5 * D[4];
+      dop[i] = G[5] / g1.y;
       drgb[i] = G[6];
       drgb[n + i] = G[7];
       drgb[2 * n + i] = G[8];
@@ -350,12 +380,15 @@ __global__ void __launch_bounds__(256) k_project_backward(RenderConst rc, asgs_g
       load_gauss(g, view, i, n, m, s, q, o);
       Proj P;
       proj_core(V, m, s, q, rc.dilation, rc.znear, P);
-      const float a = P.a, b = P.b, c = P.c, det = P.det;
       // conic (A,B,C) = (c, -b, a)/det  ->  2D covariance (a, b, c)
-      const float id2 = 1.f / (det * det);
-      const float da = (-c * c * dA + b * c * dB - b * b * dC) * id2;
-      const float db = (2.f * b * c * dA + (-det - 2.f * b * b) * dB + 2.f * a * b * dC) * id2;
-      const float dc = (-b * b * dA + a * b * dB - a * a * dC) * id2;
+      float da, db, dc;
+      {
+        const double a = P.a, b = P.b, c = P.c, det = a * c - b * b;
+        const double id2 = 1.0 / (det * det);
+        da = (float)((-c * c * dA + b * c * dB - b * b * dC) * id2);
+        db = (float)((2.0 * b * c * dA + (-det - 2.0 * b * b) * dB + 2.0 * a * b * dC) * id2);
+        dc = (float)((-b * b * dA + a * b * dB - a * a * dC) * id2);
+      }
       // covariance -> T = J W and Sigma
       float ST0[3], ST1[3];
       sym_mul(P.S, P.T0, ST0);

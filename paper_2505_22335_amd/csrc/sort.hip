@@ -23,15 +23,18 @@ namespace asgs {
 
 namespace {
 
-template <typename T>
-ASGS_DEV T wave_incl_scan(T v, int lane) {
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const T u = __shfl_up(v, o);
-    if (lane >= o) v += u;
-  }
-  return v;
+// Inclusive sum over the wave's lanes (mod 2^32): shifts inside the rows of 16
+// lanes, then the rows' last lanes broadcast to the rows above.
+ASGS_DEV uint32_t wave_incl_scan(uint32_t x) {
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, true);   // row_shr 1
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, true);   // row_shr 2
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, true);   // row_shr 4
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, true);   // row_shr 8
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);  // row_bcast 15 -> rows 1, 3
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);  // row_bcast 31 -> rows 2, 3
+  return x;
 }
+ASGS_DEV uint32_t last_lane(uint32_t x) { return (uint32_t)__builtin_amdgcn_readlane((int)x, 63); }
 
 // The block's (view, Gaussian) pair of this thread.
 struct ScanBlock {
@@ -66,140 +69,171 @@ ASGS_DEV int order_bin(uint32_t c) { return kOrderBins - 1 - (int)(c < kOrderBin
 
 __global__ void __launch_bounds__(kTileScanThreads) k_tile_scan(RenderConst rc, const ViewDev* __restrict__ views,
                                                                char* ctx, CtxLayout L) {
-  __shared__ uint32_t bins[kOrderBins];
-  __shared__ uint32_t scount[ASGS_MAX_VIEWS][kSplitThresholds];  // per view: lists per length band, then above each threshold
-  __shared__ uint32_t sused[ASGS_MAX_VIEWS];
-  __shared__ uint32_t vcnt[ASGS_MAX_VIEWS];
-  __shared__ unsigned long long wtot[kTileScanThreads / 64];
-  __shared__ uint32_t wbin[kTileScanThreads / 64];
-  __shared__ unsigned long long wvis[kTileScanThreads / 64];
-  __shared__ unsigned long long wpb[kTileScanThreads / 64], wpv[kTileScanThreads / 64];
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   constexpr int NW = kTileScanThreads / 64;
-  const int T = rc.total_tiles;
+  __shared__ uint32_t bins[kOrderBins];
+  __shared__ uint32_t scount[ASGS_MAX_VIEWS][kLenBins];  // per view: lists per length class
+  __shared__ uint32_t sused[ASGS_MAX_VIEWS], starget[ASGS_MAX_VIEWS];
+  __shared__ int32_t sbase[ASGS_MAX_VIEWS + 1];   // first tile of each view
+  __shared__ uint32_t svis[ASGS_MAX_VIEWS + 1];   // visible pairs before each view
+  __shared__ uint32_t sneed[ASGS_MAX_VIEWS][kSplitLadder];  // per view: records each segment length of the ladder takes
+  __shared__ unsigned long long wtot[NW];
+  __shared__ uint32_t wbin[NW], wpb[NW], wpv[NW];
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const uint32_t T = (uint32_t)rc.total_tiles;
   uint32_t* tcur = ctx_ptr<uint32_t>(ctx, L.tcur);
   uint2* ranges = ctx_ptr<uint2>(ctx, L.ranges);
   uint4* binfo = ctx_ptr<uint4>(ctx, L.binfo);
+  uint4* sinfo = ctx_ptr<uint4>(ctx, L.sinfo);
   CtxHeader* hdr = ctx_ptr<CtxHeader>(ctx, L.hdr);
-  // thread t owns the consecutive tiles [a0, a1)
-  const int per = (T + kTileScanThreads - 1) / kTileScanThreads;
-  const int a0 = min(T, t * per), a1 = min(T, a0 + per);
+  // Each wave owns consecutive 64-element chunks of the binning blocks and of
+  // the tiles, one element per lane, so that every access is coalesced.
+  const uint32_t nbx = (uint32_t)((rc.n + kScanThreads - 1) / kScanThreads);
+  const uint32_t nbk = nbx * (uint32_t)rc.n_views;
+  const uint32_t perb = ((nbk + 63) / 64 + NW - 1) / NW * 64, pert = ((T + 63) / 64 + NW - 1) / NW * 64;
+  const uint32_t b0 = min(nbk, wv * perb), b1 = min(nbk, b0 + perb);
+  const uint32_t a0 = min(T, wv * pert), a1 = min(T, a0 + pert);
+  // per block: tile-count sum and visible count
+  const uint32_t* bs = ctx_ptr<const uint32_t>(ctx, L.bsum);
+  const uint32_t* vs = ctx_ptr<const uint32_t>(ctx, L.vsum);
+  auto at = [&](const uint32_t* p, uint32_t i, uint32_t end) { return i < end ? p[i] : 0u; };
   bins[t] = 0u;
-  for (int q = t; q < ASGS_MAX_VIEWS * kSplitThresholds; q += kTileScanThreads) (&scount[0][0])[q] = 0u;
-  if (t < ASGS_MAX_VIEWS) {
-    sused[t] = 0u;
-    vcnt[t] = 0u;
+  for (int q = t; q < rc.n_views * kLenBins; q += kTileScanThreads) (&scount[0][0])[q] = 0u;
+  for (int q = t; q < rc.n_views * kSplitLadder; q += kTileScanThreads) (&sneed[0][0])[q] = 0u;
+  if (t < ASGS_MAX_VIEWS) sused[t] = 0u;
+  if (t <= ASGS_MAX_VIEWS) svis[t] = 0u;
+  if (t <= rc.n_views) sbase[t] = t < rc.n_views ? views[t].tile_base : (int32_t)T;
+  for (int q = t; q < rc.n_views * kSplitUnits; q += kTileScanThreads) sinfo[q] = make_uint4(~0u, 0u, 0u, 0u);
+  unsigned long long mine = 0;
+  uint32_t pb = 0u, pv = 0u;  // of this wave's blocks
+#pragma unroll 4
+  for (uint32_t b = b0; b < b1; b += 64) {
+    pb += at(bs, b + lane, b1);
+    pv += at(vs, b + lane, b1);
   }
   __syncthreads();
-  unsigned long long mine = 0;
-  for (int i = a0; i < a1; ++i) {
-    const uint32_t c = tcur[i];
-    mine += c;
-    atomicAdd(&bins[order_bin(c)], 1u);
-    if (c > (uint32_t)kSplitLen) {
-      // band j: kSplitLen + j kSplitStep < c <= kSplitLen + (j + 1) kSplitStep (the last open)
-      const uint32_t j = (c - kSplitLen - 1) / kSplitStep;
-      atomicAdd(&scount[find_view(views, rc.n_views, i)][j < kSplitThresholds ? j : kSplitThresholds - 1], 1u);
+  // view of tile i, from the view of an earlier tile
+  auto view_from = [&](int v, uint32_t i) {
+    while ((int32_t)i >= sbase[v + 1]) ++v;
+    return v;
+  };
+  int v = 0;
+  for (uint32_t i0 = a0; i0 < a1; i0 += 64) {
+    const uint32_t i = i0 + lane;
+    if (i < a1) {
+      const uint32_t c = tcur[i];
+      mine += c;
+      atomicAdd(&bins[order_bin(c)], 1u);
+      if (c > (uint32_t)split_target(0)) {
+        v = view_from(v, i);
+        atomicAdd(&scount[v][len_bin(c)], 1u);
+      }
     }
   }
-  unsigned long long vis = 0;
-  // per-block exclusive prefixes for the emission: of the tile-count sums and
-  // of the visible counts, over all blocks (a view's own visible prefix is the
-  // difference to its first block's); thread t takes consecutive blocks
+  for (int o = 32; o > 0; o >>= 1) {
+    mine += __shfl_xor(mine, o);
+    pb += __shfl_xor(pb, o);
+    pv += __shfl_xor(pv, o);
+  }
+  if (lane == 0) {
+    wtot[wv] = mine;
+    wpb[wv] = pb;
+    wpv[wv] = pv;
+  }
+  __syncthreads();
+  unsigned long long total = 0;
+  uint32_t before = 0u, pvt = 0u;
+  pb = pv = 0u;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    before += w < wv ? (uint32_t)wtot[w] : 0u;
+    total += wtot[w];
+    pb += w < wv ? wpb[w] : 0u;
+    pv += w < wv ? wpv[w] : 0u;
+    pvt += wpv[w];
+  }
+  // per-block exclusive prefixes for the emission, over all blocks
   {
-    const int64_t nbk = scan_blocks(rc.n, rc.n_views);
-    const int64_t perb = (nbk + kTileScanThreads - 1) / kTileScanThreads;
-    const int64_t b0 = min(nbk, (int64_t)t * perb), b1 = min(nbk, b0 + perb);
-    const uint32_t* bs = ctx_ptr<const uint32_t>(ctx, L.bsum);
-    const uint32_t* vs = ctx_ptr<const uint32_t>(ctx, L.vsum);
     uint32_t* bp = ctx_ptr<uint32_t>(ctx, L.bpre);
     uint32_t* vp = ctx_ptr<uint32_t>(ctx, L.vpre);
-    const int64_t nbx = (rc.n + kScanThreads - 1) / kScanThreads;
-    unsigned long long sb = 0, sv = 0;
-    for (int64_t b = b0; b < b1; ++b) {
-      sb += bs[b];
-      sv += vs[b];
-      atomicAdd(&vcnt[b / nbx], vs[b]);  // visible Gaussians per view
+    uint32_t x = at(bs, b0 + lane, b1), y = at(vs, b0 + lane, b1);
+    uint32_t w = nbk ? (b0 + nbx - 1) / nbx : 0u;  // the next view to start
+    for (uint32_t b = b0; b < b1; b += 64) {
+      const uint32_t xn = at(bs, b + 64 + lane, b1), yn = at(vs, b + 64 + lane, b1);
+      const uint32_t ix = wave_incl_scan(x), iy = wave_incl_scan(y);
+      if (b + lane < b1) {
+        bp[b + lane] = pb + ix - x;
+        vp[b + lane] = pv + iy - y;
+      }
+      for (; w * nbx < min(b1, b + 64); ++w)  // views that start in this chunk
+        if (b + lane == w * nbx) svis[w] = pv + iy - y;
+      pb += last_lane(ix);
+      pv += last_lane(iy);
+      x = xn;
+      y = yn;
     }
-    // visible pairs of the whole batch
-    vis = sv;
-    for (int o = 32; o > 0; o >>= 1) vis += __shfl_xor(vis, o);
-    const unsigned long long ib = wave_incl_scan(sb, lane), iv = wave_incl_scan(sv, lane);
-    if (lane == 63) {
-      wpb[wv] = ib;
-      wpv[wv] = iv;
-    }
-    __syncthreads();
-    unsigned long long eb = ib - sb, ev = iv - sv;
-    for (int w = 0; w < wv; ++w) {
-      eb += wpb[w];
-      ev += wpv[w];
-    }
-    for (int64_t b = b0; b < b1; ++b) {
-      bp[b] = (uint32_t)eb;
-      vp[b] = (uint32_t)ev;
-      eb += bs[b];
-      ev += vs[b];
+    if (t == 0) svis[rc.n_views] = pvt;
+  }
+  // per view, the records that cutting at each segment length of the ladder takes
+  {
+    constexpr int kB0 = len_bin(split_target(0)) + 1, kNB = kLenBins - kB0;
+    for (int q = t; q < rc.n_views * kSplitLadder * kNB; q += kTileScanThreads) {
+      const int w = q / (kSplitLadder * kNB), r = q - w * (kSplitLadder * kNB);
+      const int l = r / kNB, b = r - l * kNB + kB0;
+      const uint32_t k = scount[w][b];
+      if (k) atomicAdd(&sneed[w][l], k * (uint32_t)(bin_segments(b, split_target(l)) - 1));
     }
   }
-  const unsigned long long incl = wave_incl_scan(mine, lane);
-  if (lane == 63) wtot[wv] = incl;
-  if (lane == 0) wvis[wv] = vis;
-  __syncthreads();
-  // lists above each threshold: suffix sums of the bands, one view per thread
-  if (t < rc.n_views) {
-    uint32_t above = 0u;
-    for (int j = kSplitThresholds - 1; j >= 0; --j) {
-      above += scount[t][j];
-      scount[t][j] = above;
-    }
-  }
+  // places in the blend order: longest class first
   const uint32_t bv = bins[t];
-  const uint32_t bincl = wave_incl_scan(bv, lane);
-  if (lane == 63) wbin[wv] = bincl;
-  unsigned long long before = 0, total = 0, vtot = 0;
-  for (int w = 0; w < NW; ++w) {
-    before += w < wv ? wtot[w] : 0ull;
-    total += wtot[w];
-    vtot += wvis[w];
-  }
+  const uint32_t oincl = wave_incl_scan(bv);
+  if (lane == 63) wbin[wv] = oincl;
   __syncthreads();
-  uint32_t bbefore = 0;
-  for (int w = 0; w < wv; ++w) bbefore += wbin[w];
-  bins[t] = bbefore + bincl - bv;
+  uint32_t obefore = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) obefore += w < wv ? wbin[w] : 0u;
+  bins[t] = obefore + oincl - bv;
   const bool ovf = total > (unsigned long long)rc.cap;
   if (t == 0) {
     hdr->n_isect = total;
-    hdr->n_visible = vtot;
+    hdr->n_visible = pvt;
     hdr->overflow = ovf ? 1u : 0u;
   }
+  if (t < rc.n_views) {
+    ctx_ptr<uint32_t>(ctx, L.vcount)[t] = svis[t + 1] - svis[t];
+    // the smallest segment length the records allow
+    int l = 0;
+    while (l < kSplitLadder && sneed[t][l] > (uint32_t)kSplitUnits) ++l;
+    starget[t] = (uint32_t)l;
+  }
   __syncthreads();
-  if (t < rc.n_views) ctx_ptr<uint32_t>(ctx, L.vcount)[t] = vcnt[t];
-  uint4* sinfo = ctx_ptr<uint4>(ctx, L.sinfo);
-  for (int q = t; q < rc.n_views * kSplitPerView; q += kTileScanThreads) sinfo[q] = make_uint4(~0u, 0u, 0u, 0u);
-  __syncthreads();  // the slot table is cleared before any slot is taken
   uint32_t* bslot = ctx_ptr<uint32_t>(ctx, L.bslot);
-  unsigned long long run = before + incl - mine;
-  for (int i = a0; i < a1; ++i) {
-    const uint32_t c = tcur[i];
-    const uint2 r = ovf ? make_uint2(0u, 0u) : make_uint2((uint32_t)run, (uint32_t)(run + c));
-    ranges[i] = r;
-    tcur[i] = (uint32_t)run;
-    binfo[atomicAdd(&bins[order_bin(c)], 1u)] = make_uint4((uint32_t)i, r.x, r.y, 0u);
-    // split when longer than the view's threshold (the slot order is arbitrary)
-    uint32_t sl = 0u;
-    if (!ovf && c > (uint32_t)kSplitLen) {
-      const int v = find_view(views, rc.n_views, i);
-      int j = 0;
-      while (j < kSplitThresholds && scount[v][j] > (uint32_t)kSplitPerView) ++j;
-      if (j < kSplitThresholds && c > (uint32_t)(kSplitLen + j * kSplitStep)) {
-        const uint32_t slot = (uint32_t)v * kSplitPerView + atomicAdd(&sused[v], 1u);
-        sinfo[slot] = make_uint4((uint32_t)i, r.x, r.y, 0u);
-        sl = slot + 1u;
+  v = 0;
+  for (uint32_t i0 = a0; i0 < a1; i0 += 64) {
+    const uint32_t i = i0 + lane;
+    const uint32_t c = i < a1 ? tcur[i] : 0u;
+    const uint32_t incl = wave_incl_scan(c);
+    const uint32_t run = before + incl - c;
+    before += last_lane(incl);
+    if (i < a1) {
+      const uint2 r = ovf ? make_uint2(0u, 0u) : make_uint2(run, run + c);
+      ranges[i] = r;
+      tcur[i] = run;
+      binfo[atomicAdd(&bins[order_bin(c)], 1u)] = make_uint4(i, r.x, r.y, 0u);
+      // cut by the view's segment length (the order of the records is arbitrary)
+      uint32_t sl = 0u;
+      if (!ovf && c > (uint32_t)split_target(0)) {
+        v = view_from(v, i);
+        const int l = (int)starget[v];
+        const int n = l < kSplitLadder ? bin_segments(len_bin(c), split_target(l)) : 1;
+        if (n > 1) {
+          const uint32_t first = (uint32_t)v * kSplitUnits + atomicAdd(&sused[v], (uint32_t)(n - 1));
+          const uint32_t len = segment_length(c, (uint32_t)n);
+          for (uint32_t s = 0; (s + 1) * len < c; ++s) sinfo[first + s] = make_uint4(i, r.x, r.y, s);
+          sl = split_slot(first, (uint32_t)n);
+        }
       }
+      bslot[i] = sl;
     }
-    bslot[i] = sl;
-    run += c;
   }
 }
 
@@ -226,7 +260,7 @@ __global__ void __launch_bounds__(kScanThreads) k_dup_emit(RenderConst rc, const
   // first gradient slot: sum of the blocks before this one (the scan's
   // prefix) + the prefix in it
   const unsigned long long pre = ctx_ptr<const uint32_t>(ctx, L.bpre)[blockIdx.x];
-  const uint32_t incl = wave_incl_scan(cnt, lane);
+  const uint32_t incl = wave_incl_scan(cnt);
   if (lane == 0) wred[wv] = wv == 0 ? pre : 0ull;
   if (lane == 63) wsum[wv] = incl;
   // place in the view's visible list: visible Gaussians of the view's earlier
