@@ -39,55 +39,70 @@ ASGS_DEV void prioritise(uint32_t rank, int n_cu) {
   else if (band == 2u) __builtin_amdgcn_s_setprio(1);
 }
 
-// Which of the tile's four 8x8 quarters (bit w) hold a pixel centre that can
-// pass the alpha test power >= ln(alpha_min / o) of an entry: a conservative
-// test against the bounding box of the ellipse d^T Q d <= 2 L, Q = [[A, B],
-// [B, C]], L = -ln(alpha_min / o), whose half extents are sqrt(2 L C / det Q)
-// and sqrt(2 L A / det Q). The box is computed in FP64 from the stored FP32
-// conic and widened by a relative 1e-3 + 2e-6 cond(Q) (covering the FP32
-// rounding of the per-pixel power, whose error grows with the condition
-// number) plus 0.01 px; entries too ill-conditioned for that bound are kept
-// everywhere. Entries whose threshold no pixel can reach (o < alpha_min, or
-// a NaN threshold) are dropped everywhere.
-ASGS_DEV uint32_t quarter_mask(const float4& g0, const float4& g1, int x0, int y0) {
-  const float lnthr = g1.z;
-  if (!(lnthr <= 0.f)) return 0u;
-  const double a = g0.z, b = g0.w, c = g1.x;
-  const double det = a * c - b * b;
-  if (!(det > 0.0) || !(a > 0.0) || !(c > 0.0)) return 0xFu;
-  const double half_tr = 0.5 * (a + c);
-  const double disc = sqrt(0.25 * (a - c) * (a - c) + b * b);
-  const double lmax = half_tr + disc;
-  const double cond = lmax * lmax / det;  // lmax / lmin
-  const double rel = 1e-3 + 2e-6 * cond;
-  if (!(rel < 0.25)) return 0xFu;
-  const double L2 = -2.0 * (double)lnthr;
-  const double hx = sqrt(L2 * c / det) * (1.0 + rel) + 0.01;
-  const double hy = sqrt(L2 * a / det) * (1.0 + rel) + 0.01;
-  const double u = g0.x, v = g0.y;
-  uint32_t m = 0u;
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    const double sx = x0 + 8 * (w & 1), sy = y0 + 8 * (w >> 1);
-    if (u + hx >= sx && u - hx <= sx + 7.0 && v + hy >= sy && v - hy <= sy + 7.0) m |= 1u << w;
+ASGS_DEV bool any_lane(bool b) { return __builtin_amdgcn_ballot_w64(b) != 0; }
+
+// A Gaussian's blend record in scalar registers: geometry (u, v, A, B, C, o,
+// ln(alpha_min / o)) and channels. The loads go through the constant address
+// space, so a wave-uniform index makes them scalar loads.
+typedef float f4u __attribute__((ext_vector_type(4), aligned(16)));
+typedef float f8u __attribute__((ext_vector_type(8), aligned(16)));
+typedef float f16u __attribute__((ext_vector_type(16), aligned(16)));
+#define ASGS_CONST_AS __attribute__((address_space(4)))
+
+template <int CS>
+struct SRec;
+template <>
+struct SRec<4> {
+  f8u g;
+  f4u c;
+  ASGS_DEV void load(const float* geom, const float* chan, uint32_t gid) {
+    g = *(const ASGS_CONST_AS f8u*)(geom + (size_t)gid * kGeomStride);
+    c = *(const ASGS_CONST_AS f4u*)(chan + (size_t)gid * 4);
   }
-  return m;
-}
+  ASGS_DEV float ch(int k) const { return c[k]; }
+  // The unused last word stays allocated until the record is used: its
+  // register, reused earlier, would have to wait for the load in flight.
+  ASGS_DEV void keep() const { asm volatile("" ::"s"(g[7])); }
+};
+template <>
+struct SRec<20> {
+  f8u g;
+  f16u c;
+  f4u d;
+  ASGS_DEV void load(const float* geom, const float* chan, uint32_t gid) {
+    g = *(const ASGS_CONST_AS f8u*)(geom + (size_t)gid * kGeomStride);
+    const float* p = chan + (size_t)gid * 20;
+    c = *(const ASGS_CONST_AS f16u*)p;
+    d = *(const ASGS_CONST_AS f4u*)(p + 16);
+  }
+  ASGS_DEV float ch(int k) const { return k < 16 ? c[k < 16 ? k : 0] : d[k < 16 ? 0 : k - 16]; }
+  ASGS_DEV void keep() const { asm volatile("" ::"s"(g[7])); }
+};
 
-constexpr int kFwdThreads = 2 * kTilePix;  // two waves per 8x8 quarter: front and back half of its list
-constexpr int kSplitMin = 16;             // a round's quarter list shorter than this stays on the front wave
+constexpr int kFwdThreads = 128;  // two waves per 8x8 quarter: front and back half of its list
+constexpr int kFwdRound = 256;    // list entries per round
+constexpr int kSplitMin = 16;     // a round's quarter list shorter than this stays on the front wave
 
-// Forward compositing, one 512-thread workgroup per tile. Each 8x8 quarter
-// of the tile has two waves. Per round of staged list entries, the quarter's
-// entries that can reach one of its pixels are split in list order: the
+// Forward compositing, one workgroup of two waves per 8x8 quarter of a tile.
+// Per round of up to 256 list entries, the entries that can reach one of the
+// quarter's pixels (the sort's quarter masks) are split in list order: the
 // front wave composites the first half onto the running state (T, channels,
 // last contributor), the back wave the second half from T = 1 at the same
-// time; then the front wave appends the back half's result,
+// time, both with the records in scalar registers (requested one entry ahead,
+// their cache lines touched at the start of the round); then the front wave
+// appends the back half's result,
 //   C <- C + T C_back,  T <- T T_back,
 // which equals compositing the two halves in order as long as the
 // transmittance cannot have crossed T_min inside the back half
 // (T T_back >= T_min, T being monotone). Pixels where it could re-run the
 // back half on the front wave with the sequential rule.
+//
+// Bound by the vector ALU (about 42 instructions per used entry) and, on few
+// tiles, by the longest lists. One 512-thread workgroup per tile with the
+// records and an FP64 box test per entry staged through LDS waited at its
+// barriers two thirds of the time: one 640x480 view of 157k intersections
+// 48 us, now 32 us; 774k intersections 265 us, now 158; eight 320x240 views
+// with 986k 337 us, now 208; 80 tiles of 50k (no features) 70 us, now 50.
 //
 // With L1, the output stage also forms the weighted L1 residual of the maps
 // against the targets and its gradient (the terms of the L1 loss kernel, in
@@ -98,30 +113,32 @@ template <int NF, bool L1>
 __global__ void __launch_bounds__(kFwdThreads) k_blend_fwd(RenderConst rc, const ViewDev* __restrict__ views,
                                                            char* ctx, CtxLayout L, asgs_images out, BlendL1 l1) {
   constexpr int CS = 4 + NF;
-  constexpr int CS4 = CS / 4;
-  const uint4 bi = ctx_ptr<const uint4>(ctx, L.binfo)[blockIdx.x];  // longest lists first
+  // 32 consecutive workgroups are the four quarters of eight tiles, those of a
+  // tile eight apart, so that they share an XCD's L2 (workgroups go to the
+  // XCDs round-robin)
+  const uint32_t bpos = (blockIdx.x >> 5) * 8u + (blockIdx.x & 7u);
+  const int qd = (blockIdx.x >> 3) & 3;
+  if (bpos >= (uint32_t)rc.total_tiles) return;
+  const uint4 bi = ctx_ptr<const uint4>(ctx, L.binfo)[bpos];  // longest lists first
   const int tile = (int)bi.x;
   const int view = find_view(views, rc.n_views, tile);
   const ViewDev& V = views[view];
   const int lt = tile - V.tile_base;
   const int ty = lt / V.TX, tx = lt - ty * V.TX;
-  const int t = threadIdx.x;
-  const int lane = t & 63;
-  const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int qd = wv & 3;         // quarter
-  const bool back = wv >= 4;     // back half of the quarter's list
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool back = wv == 1;     // back half of the quarter's list
   const int tq = (qd << 6) | lane;
-  const int x0 = tx * kTile, y0 = ty * kTile;
-  const int px = x0 + tile_lx(tq);
-  const int py = y0 + tile_ly(tq);
+  const int px = tx * kTile + tile_lx(tq);
+  const int py = ty * kTile + tile_ly(tq);
   const bool inside = px < V.W && py < V.H;
   const float pxf = (float)px, pyf = (float)py;
   const uint2 rg = make_uint2(bi.y, bi.z);
-  prioritise(blockIdx.x, rc.n_cu);
+  prioritise(bpos, rc.n_cu);
   const uint32_t* pairgid = ctx_ptr<const uint32_t>(ctx, L.pairgid);
-  const float4* geom = ctx_ptr<const float4>(ctx, L.geom);
-  const float4* chan4 = ctx_ptr<const float4>(ctx, L.chan);
-  uint8_t* pmask = ctx_ptr<uint8_t>(ctx, L.pmask);
+  const float* geom = ctx_ptr<const float>(ctx, L.geom);
+  const float* chan = ctx_ptr<const float>(ctx, L.chan);
+  const uint8_t* pmask = ctx_ptr<const uint8_t>(ctx, L.pmask);
   // lists walked by several backward workgroups: rounds end at the segment
   // boundaries, and the pixel's state is recorded at the end of every segment
   // but the last
@@ -130,12 +147,9 @@ __global__ void __launch_bounds__(kFwdThreads) k_blend_fwd(RenderConst rc, const
   constexpr int SA = split_first(CS);
   float* sp = ctx_ptr<float>(ctx, L.split) + (size_t)(sl ? (sl & kSplitSlotMask) - 1u : 0u) * split_floats(CS);
 
-  __shared__ float4 sg[kTilePix * 2];
-  __shared__ float4 sc[kTilePix * CS4];
-  __shared__ uint8_t smask[kTilePix];
-  __shared__ uint16_t swl[kFwdThreads / 64][kTilePix];
-  __shared__ float xch[4][CS + 2][64];  // back-half state per quarter pixel: T, channels, last
-  __shared__ uint64_t qdone[4];         // front lanes already stopped, per quarter
+  __shared__ uint2 swl[2][kFwdRound];   // per wave: the quarter's entries of the round
+  __shared__ float xch[CS + 2][64];     // back-half state per pixel: T, channels, last
+  __shared__ uint64_t qdone;            // front lanes already stopped
 
   // L1 targets and weight of the pixel, requested now and used in the output stage
   float tv[CS + 1], tw = 1.f;
@@ -165,117 +179,135 @@ __global__ void __launch_bounds__(kFwdThreads) k_blend_fwd(RenderConst rc, const
   uint32_t last = 0;
   bool done = back || !inside;  // back lanes keep no running state
   const float amax = rc.alpha_max, tmin = rc.T_min;
-  // Composite list positions [i0, i1) of this wave's round list. real: the
-  // running state with the T_min stop; otherwise a local back-half state.
-  // The next entry's index and geometry are read from LDS while the current
-  // one is composited.
-  auto run = [&](int i0, int i1, uint32_t base, bool act, bool real) {
-    if (i0 >= i1) return;
-    int jn = __builtin_amdgcn_readfirstlane(swl[wv][i0]);
-    float4 g0n = sg[2 * jn], g1n = sg[2 * jn + 1];
-    for (int i = i0; i < i1; ++i) {
-      const int j = jn;
-      const float4 g0 = g0n, g1 = g1n;
-      if (i + 1 < i1) {
-        jn = __builtin_amdgcn_readfirstlane(swl[wv][i + 1]);
-        g0n = sg[2 * jn];
-        g1n = sg[2 * jn + 1];
-      }
+  // Composite the positions [i0, i1) of this wave's list of the round on the
+  // lanes with reach = 0 (others: -inf, below every power); a lane stops
+  // (reach = -inf) before T would fall below tstop (T_min, or -1 for a local
+  // back-half state).
+  constexpr float kNoReach = -__builtin_inff();
+  auto run = [&](int i0, int i1, float& reach, float tstop) {
+    const uint2* lst = swl[wv];
+    // one entry at list position pos; false when every lane has stopped
+    auto entry = [&](const SRec<CS>& rec, uint32_t pos) -> bool {
+      rec.keep();
       float dx, dy;
-      const float power = eval_power(g0.x, g0.y, g0.z, g0.w, g1.x, pxf, pyf, dx, dy);
+      const float power = eval_power(rec.g[0], rec.g[1], rec.g[2], rec.g[3], rec.g[4], pxf, pyf, dx, dy);
       // alpha >= alpha_min  <=>  power >= ln(alpha_min / o) (record slot 6)
-      const bool take = act && power <= 0.f && power >= g1.z;
-      if (!__ballot(take)) continue;
-      const float alpha = fminf(amax, g1.y * __expf(power));
+      const bool use = power <= reach && power >= rec.g[6];
+      if (!any_lane(use)) return true;
+      const float alpha = fminf(amax, rec.g[5] * __expf(power));
       const float Tn = T * (1.f - alpha);
-      const bool stop = real && take && Tn < tmin;
-      if (take && !stop) {
+      const bool stop = use && Tn < tstop;
+      if (use && !stop) {
         const float w = alpha * T;
 #pragma unroll
-        for (int c4 = 0; c4 < CS4; ++c4) {
-          const float4 v = sc[j * CS4 + c4];
-          acc[4 * c4 + 0] = fmaf(w, v.x, acc[4 * c4 + 0]);
-          acc[4 * c4 + 1] = fmaf(w, v.y, acc[4 * c4 + 1]);
-          acc[4 * c4 + 2] = fmaf(w, v.z, acc[4 * c4 + 2]);
-          acc[4 * c4 + 3] = fmaf(w, v.w, acc[4 * c4 + 3]);
-        }
+        for (int k = 0; k < CS; ++k) acc[k] = fmaf(w, rec.ch(k), acc[k]);
         T = Tn;
-        last = base - rg.x + (uint32_t)j + 1u;
+        last = pos;
       }
-      if (real && __ballot(stop)) {
-        done = done || stop;
-        act = act && !stop;
-        if (__ballot(act) == 0) break;
+      if (any_lane(stop)) {
+        reach = stop ? kNoReach : reach;
+        return any_lane(reach == 0.f);
       }
+      return true;
+    };
+    SRec<CS> ra, rb;
+    uint2 ea = lst[i0], eb = lst[min(i0 + 1, i1 - 1)];
+    ra.load(geom, chan, (uint32_t)__builtin_amdgcn_readfirstlane((int)ea.x));
+    for (int i = i0;;) {
+      rb.load(geom, chan, (uint32_t)__builtin_amdgcn_readfirstlane((int)eb.x));
+      const uint32_t pa = ea.y;
+      ea = lst[min(i + 2, i1 - 1)];
+      if (!entry(ra, pa) || ++i >= i1) break;
+      ra.load(geom, chan, (uint32_t)__builtin_amdgcn_readfirstlane((int)ea.x));
+      const uint32_t pb = eb.y;
+      eb = lst[min(i + 2, i1 - 1)];
+      if (!entry(rb, pb) || ++i >= i1) break;
     }
   };
-  // the Gaussian ids of the next round are read while this round is staged
-  uint32_t gid_next = t < kTilePix && rg.x + t < rg.y ? pairgid[rg.x + t] : 0u;
   uint32_t seg = 0u, segend = rg.x + seglen;  // current segment and its end
   uint32_t rstep = 0u;                        // entries of the round
-  for (uint32_t base = rg.x; base < rg.y; base += rstep) {
-    if (__syncthreads_count(!done) == 0) break;
-    const uint32_t p = base + t;
-    rstep = min((uint32_t)kTilePix, min(segend, rg.y) - base);
-    if (t < rstep) {
-      const uint32_t gid = gid_next;
-      const float4 g0 = geom[2 * (size_t)gid];
-      const float4 g1 = geom[2 * (size_t)gid + 1];
-      sg[2 * t] = g0;
-      sg[2 * t + 1] = g1;
+  // the round's Gaussian ids and quarter masks, lane l entry 64 k + l
+  uint32_t gid[kFwdRound / 64], msk[kFwdRound / 64];
+  auto fetch = [&](uint32_t base, uint32_t end) {
 #pragma unroll
-      for (int c = 0; c < CS4; ++c) sc[t * CS4 + c] = chan4[(size_t)gid * CS4 + c];
-      const uint8_t m = (uint8_t)quarter_mask(g0, g1, x0, y0);
-      smask[t] = m;
-      pmask[p] = m;  // reused by the backward
+    for (int k = 0; k < kFwdRound / 64; ++k) {
+      const uint32_t p = base + 64 * k + lane;
+      gid[k] = p < end ? pairgid[p] : 0u;
+      msk[k] = p < end ? pmask[p] : 0u;
     }
-    if (t < kTilePix && p + rstep < rg.y) gid_next = pairgid[p + rstep];
+  };
+  fetch(rg.x, min(rg.y, min(segend, rg.x + kFwdRound)));
+  for (uint32_t base = rg.x; base < rg.y; base += rstep) {
     {
       const uint64_t dm = __ballot(done);
-      if (!back && lane == 0) qdone[qd] = dm;
+      if (!back && lane == 0) qdone = dm;
     }
     __syncthreads();
-    const int cnt = (int)rstep;
+    const uint64_t dm = qdone;
+    if (!~dm) break;
+    rstep = min((uint32_t)kFwdRound, min(segend, rg.y) - base);
     // the quarter's entries of the round (those that can reach one of its
-    // pixels), in list order, compacted into swl (the same list on both waves)
+    // pixels), in list order, compacted into swl (the same list on both waves):
+    // the Gaussian and the position in the tile's list plus one
     int n = 0;
-    for (int c64 = 0; c64 < cnt; c64 += 64) {
-      const bool mine = c64 + lane < cnt && ((smask[c64 + lane] >> qd) & 1u);
+#pragma unroll
+    for (int k = 0; k < kFwdRound / 64; ++k) {
+      const bool mine = (msk[k] >> qd) & 1u;
       const uint64_t bits = __ballot(mine);
-      if (mine) swl[wv][n + __builtin_amdgcn_mbcnt_hi((uint32_t)(bits >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bits, 0u))] = (uint16_t)(c64 + lane);
+      if (mine)
+        swl[wv][n + __builtin_amdgcn_mbcnt_hi((uint32_t)(bits >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bits, 0u))] =
+            make_uint2(gid[k], base - rg.x + 64 * k + lane + 1u);
       n += __builtin_popcountll(bits);
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     const int nf = n < kSplitMin ? n : (n + 1) / 2;
+    // touch the records of this wave's half, and request the next round's ids
+    float touch = 0.f;
+    for (int i = (back ? nf : 0) + lane; i < (back ? n : nf); i += 64) {
+      const size_t g = swl[wv][i].x;
+      touch += geom[g * kGeomStride] + chan[g * CS] + chan[g * CS + CS - 1];
+    }
+    {
+      const uint32_t nb = base + rstep, nend = nb == segend ? segend + seglen : segend;
+      fetch(nb, min(rg.y, min(nend, nb + kFwdRound)));
+    }
     if (back) {
       T = 1.f;
 #pragma unroll
       for (int c = 0; c < CS; ++c) acc[c] = 0.f;
       last = 0u;
-      const bool skip = !inside || ((qdone[qd] >> lane) & 1u);
-      run(nf, n, base, !skip, false);
-      xch[qd][0][lane] = T;
+      const bool skip = !inside || ((dm >> lane) & 1u);
+      float reach = skip ? kNoReach : 0.f;
+      if (nf < n) run(nf, n, reach, -1.f);
+      xch[0][lane] = T;
 #pragma unroll
-      for (int c = 0; c < CS; ++c) xch[qd][1 + c][lane] = acc[c];
-      xch[qd][CS + 1][lane] = __uint_as_float(last);
-    } else if (__ballot(!done)) {
-      run(0, nf, base, !done, true);
+      for (int c = 0; c < CS; ++c) xch[1 + c][lane] = acc[c];
+      xch[CS + 1][lane] = __uint_as_float(last);
+    } else if (n > 0) {
+      float reach = done ? kNoReach : 0.f;
+      run(0, nf, reach, tmin);
+      done = reach != 0.f;
     }
+    asm volatile("" ::"v"(touch));  // the touching loads are kept, and waited for here
     __syncthreads();
     if (!back && nf != n) {
       // append the back half
-      const float Tb = xch[qd][0][lane];
-      const uint32_t lastb = __float_as_uint(xch[qd][CS + 1][lane]);
+      const float Tb = xch[0][lane];
+      const uint32_t lastb = __float_as_uint(xch[CS + 1][lane]);
       const bool fix = !done && T * Tb < tmin;
       if (!done && !fix) {
 #pragma unroll
-        for (int c = 0; c < CS; ++c) acc[c] = fmaf(T, xch[qd][1 + c][lane], acc[c]);
+        for (int c = 0; c < CS; ++c) acc[c] = fmaf(T, xch[1 + c][lane], acc[c]);
         T *= Tb;
         if (lastb) last = lastb;
       }
-      if (__ballot(fix)) run(nf, n, base, fix, true);
+      if (any_lane(fix)) {
+        float reach = fix ? 0.f : kNoReach;
+        run(nf, n, reach, tmin);
+        done = done || (fix && reach != 0.f);
+      }
     }
     const bool ends = base + rstep == segend;
     if (ends && !back && segend < rg.y) {
@@ -416,40 +448,6 @@ ASGS_DEV void bf_split(float v, uint16_t& hi, uint16_t& lo) {
   hi = bf_rne(v);
   lo = bf_rne(v - __uint_as_float((uint32_t)hi << 16));
 }
-
-// A Gaussian's blend record in scalar registers: geometry (u, v, A, B, C, o,
-// ln(alpha_min / o)) and channels. The loads go through the constant address
-// space, so a wave-uniform index makes them scalar loads.
-typedef float f4u __attribute__((ext_vector_type(4), aligned(16)));
-typedef float f8u __attribute__((ext_vector_type(8), aligned(16)));
-typedef float f16u __attribute__((ext_vector_type(16), aligned(16)));
-#define ASGS_CONST_AS __attribute__((address_space(4)))
-
-template <int CS>
-struct SRec;
-template <>
-struct SRec<4> {
-  f8u g;
-  f4u c;
-  ASGS_DEV void load(const float* geom, const float* chan, uint32_t gid) {
-    g = *(const ASGS_CONST_AS f8u*)(geom + (size_t)gid * kGeomStride);
-    c = *(const ASGS_CONST_AS f4u*)(chan + (size_t)gid * 4);
-  }
-  ASGS_DEV float ch(int k) const { return c[k]; }
-};
-template <>
-struct SRec<20> {
-  f8u g;
-  f16u c;
-  f4u d;
-  ASGS_DEV void load(const float* geom, const float* chan, uint32_t gid) {
-    g = *(const ASGS_CONST_AS f8u*)(geom + (size_t)gid * kGeomStride);
-    const float* p = chan + (size_t)gid * 20;
-    c = *(const ASGS_CONST_AS f16u*)p;
-    d = *(const ASGS_CONST_AS f4u*)(p + 16);
-  }
-  ASGS_DEV float ch(int k) const { return k < 16 ? c[k < 16 ? k : 0] : d[k < 16 ? 0 : k - 16]; }
-};
 
 // Backward compositing, one workgroup per tile (or per segment of a split
 // list), one pixel per thread.
@@ -724,7 +722,7 @@ __global__ void __launch_bounds__(kTilePix) __attribute__((amdgpu_waves_per_eu(5
     const float power = eval_power(rec.g[0], rec.g[1], rec.g[2], rec.g[3], rec.g[4], pxf, pyf, dx, dy);
     // same alpha threshold as the forward
     const bool use = (uint32_t)(rlo + j) < last && power <= 0.f && power >= rec.g[6];
-    if (!__ballot(use)) return;
+    if (!any_lane(use)) return;
     used |= 1u << j;
     const float raw = rec.g[5] * __expf(power);
     const float alpha = fminf(amax, raw);
@@ -836,7 +834,7 @@ void launch_blend_forward(const RenderConst& rc, const CtxLayout& L, char* ctx, 
                           const BlendL1* l1, hipStream_t s) {
   const ViewDev* views = reinterpret_cast<const ViewDev*>(ctx + L.views);
   const BlendL1 a = l1 ? *l1 : BlendL1{};
-  const dim3 grid(rc.total_tiles), block(kFwdThreads);
+  const dim3 grid((unsigned)((rc.total_tiles + 7) / 8 * 32)), block(kFwdThreads);
   if (rc.nf == 16) {
     if (l1) hipLaunchKernelGGL((k_blend_fwd<16, true>), grid, block, 0, s, rc, views, ctx, L, out, a);
     else hipLaunchKernelGGL((k_blend_fwd<16, false>), grid, block, 0, s, rc, views, ctx, L, out, a);

@@ -142,6 +142,27 @@ ASGS_DEV bool proj_core(const ViewDev& V, const float m[3], const float s[3], co
   return true;
 }
 
+// Half extents (two half-precision values, x low) of the box around the
+// ellipse power >= lnthr, outside which no pixel passes the alpha test:
+// sqrt(-2 lnthr Sigma'_xx) and sqrt(-2 lnthr Sigma'_yy), widened by a relative
+// 1e-3 + 4e-6 cond(Sigma') (the FP32 rounding of the conic and of the
+// per-pixel power grows with the condition number), 0.01 px, and the
+// conversion's rounding; infinite when too ill-conditioned for that bound,
+// minus infinity when no pixel can pass (o < alpha_min, a NaN threshold).
+ASGS_DEV uint32_t reach_box(const Proj& P, float lnthr) {
+  if (!(lnthr <= 0.f)) return 0xFC00FC00u;
+  const float half_tr = 0.5f * (P.a + P.c);
+  const float disc = sqrtf(0.25f * (P.a - P.c) * (P.a - P.c) + P.b * P.b);
+  const float lmax = half_tr + disc;
+  const float rel = 1e-3f + 4e-6f * (lmax * lmax / P.det);
+  if (!(rel < 0.25f)) return 0x7C007C00u;
+  const float grow = (1.f + rel) * (1.f + 1.f / 512.f);
+  const float hx = (sqrtf(-2.f * lnthr * P.a) + 0.01f) * grow, hy = (sqrtf(-2.f * lnthr * P.c) + 0.01f) * grow;
+  const uint32_t bx = hx < 60000.f ? __builtin_bit_cast(uint16_t, (_Float16)hx) : 0x7C00u;
+  const uint32_t by = hy < 60000.f ? __builtin_bit_cast(uint16_t, (_Float16)hy) : 0x7C00u;
+  return bx | by << 16;
+}
+
 template <int NF>
 __global__ void __launch_bounds__(256) k_project(RenderConst rc, asgs_gaussians g,
                                                  const ViewDev* __restrict__ views, char* ctx,
@@ -204,7 +225,9 @@ __global__ void __launch_bounds__(256) k_project(RenderConst rc, asgs_gaussians 
     geom[2 * gid] = make_float4(u, v, A, B);
     // slot 6: the power at which o exp(power) reaches alpha_min, so that the
     // blend kernels test alpha >= alpha_min without an exponential
-    geom[2 * gid + 1] = make_float4(C, o, logf(rc.alpha_min / o), 0.f);
+    // slot 7: half extents of the box of that ellipse, for the quarter masks
+    const float lnthr = logf(rc.alpha_min / o);
+    geom[2 * gid + 1] = make_float4(C, o, lnthr, __uint_as_float(reach_box(P, lnthr)));
   }
   if (!vis) {
     if (valid) {

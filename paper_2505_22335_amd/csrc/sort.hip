@@ -342,7 +342,20 @@ ASGS_DEV void bitonic_lds(unsigned long long* sk, int P, int t) {
     }
 }
 
+// Which of the tile's four 8x8 quarters (bit w) hold a pixel centre inside the
+// box the projection wrote around a Gaussian's alpha >= alpha_min ellipse:
+// the blend kernels' waves, one quarter each, skip the others.
+ASGS_DEV uint32_t quarter_mask(float u, float v, uint32_t box, float x0, float y0) {
+  const float hx = (float)__builtin_bit_cast(_Float16, (uint16_t)box);
+  const float hy = (float)__builtin_bit_cast(_Float16, (uint16_t)(box >> 16));
+  const bool xl = u + hx >= x0 && u - hx <= x0 + 7.f, xr = u + hx >= x0 + 8.f && u - hx <= x0 + 15.f;
+  const bool yt = v + hy >= y0 && v - hy <= y0 + 7.f, yb = v + hy >= y0 + 8.f && v - hy <= y0 + 15.f;
+  return (xl && yt ? 1u : 0u) | (xr && yt ? 2u : 0u) | (xl && yb ? 4u : 0u) | (xr && yb ? 8u : 0u);
+}
+
 struct ListOut {
+  const float* geom;
+  uint8_t* pmask;
   const short4* rect;
   const uint32_t* toff;
   uint32_t* pairgid;
@@ -351,11 +364,14 @@ struct ListOut {
   uint32_t tile;
   int tx, ty;
 
-  // Gaussian, gradient slot and tile of list position pos.
+  // Gaussian, gradient slot, tile and quarter mask of list position pos.
   ASGS_DEV void put(uint64_t pos, unsigned long long key) const {
     const uint32_t gid = (uint32_t)key;
     const short4 r = rect[gid];
+    const float2 c = *reinterpret_cast<const float2*>(geom + (size_t)gid * kGeomStride);
+    const uint32_t box = __float_as_uint(geom[(size_t)gid * kGeomStride + 7]);
     pairgid[pos] = gid;
+    pmask[pos] = (uint8_t)quarter_mask(c.x, c.y, box, (float)(tx * kTile), (float)(ty * kTile));
     pslot[pos] = toff[gid] + (uint32_t)((ty - r.z) * (r.y - r.x + 1) + (tx - r.x));
     ptile[pos] = tile;
   }
@@ -377,6 +393,8 @@ __global__ void __launch_bounds__(kListThreads) k_list_sort(RenderConst rc, cons
     out.ty = lt / V.TX;
     out.tx = lt - out.ty * V.TX;
   }
+  out.geom = ctx_ptr<const float>(ctx, L.geom);
+  out.pmask = ctx_ptr<uint8_t>(ctx, L.pmask);
   out.rect = ctx_ptr<const short4>(ctx, L.rect);
   out.toff = ctx_ptr<const uint32_t>(ctx, L.toff);
   out.pairgid = ctx_ptr<uint32_t>(ctx, L.pairgid);
