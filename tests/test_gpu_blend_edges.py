@@ -1,0 +1,112 @@
+"""The blend kernels at the edges of their rounds, list cuts and quarter
+masks, against the FP64 oracle (tolerances and guard band of the render
+parity tests: images 1e-4, gradients 1e-3)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+from tests.gpu_util import GRAD_TOL, IMG_TOL, guard_report, log, oracle_opts, rel_err, to_np, upstream
+
+pytestmark = pytest.mark.gpu
+
+if torch.cuda.is_available():
+    import paper_2505_22335_amd as P
+    from paper_2505_22335_amd import _lib as L
+
+
+def _check(sc, cam, nf, label, max_frac):
+    ref = oracle.render_scene(sc, cam, oracle_opts(nf), with_margins=True)
+    keep, rep = guard_report(ref["margins"], tie_ulps=0)
+    log("case", label, rep)
+    assert rep["frac"] <= max_frac, rep
+    G = upstream(5, cam.height, cam.width, nf)
+    G = {k: v * keep for k, v in G.items()}
+    _, gr = oracle.render_scene(sc, cam, oracle_opts(nf), grad_out=G, pose_grad=True)
+    g = P.gaussians_to_device(sc.arrays())
+    rc = P.RenderContext([cam], sc.n, n_feat=nf)
+    rc.fit(g)
+    out = rc.forward(g)
+    dg, dpose = rc.backward(g, {k: torch.as_tensor(v[None].astype(np.float32)).cuda() for k, v in G.items()})
+    torch.cuda.synchronize()
+    for k in ("rgb", "depth", "alpha") + (("feat",) if nf else ()):
+        e = rel_err(to_np(out[k][0]), ref[k], keep)
+        assert e <= IMG_TOL, (label, k, e)
+    for k in ("mean", "scale", "rot", "opacity", "rgb") + (("feat",) if nf else ()):
+        e = rel_err(to_np(dg[k][0]), gr["gauss"][k])
+        assert e <= GRAD_TOL, (label, k, e)
+    e = rel_err(to_np(dpose[0]), gr["pose"])
+    assert e <= GRAD_TOL, (label, "pose", e)
+
+
+@pytest.mark.parametrize("nf", [0, 16])
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 31, 32, 33, 128, 129, 255, 256, 257, 513, 1100])
+def test_one_tile_list_lengths(n, nf):
+    """n wide faint Gaussians over one 16x16 tile: batches of 8, rounds of 32
+    and 256 entries, and lists cut from 129 entries on."""
+    rng = np.random.default_rng(n)
+    z = rng.uniform(2.0, 4.0, n)
+    q = rng.normal(size=(4, n))
+    sc = synth.PlainScene(
+        mean=np.stack([rng.uniform(-0.2, 0.2, n), rng.uniform(-0.2, 0.2, n), z]).astype(np.float32),
+        scale=rng.uniform(1.5, 4.0, (3, n)).astype(np.float32), rot=(q / np.linalg.norm(q, axis=0)).astype(np.float32),
+        opacity=rng.uniform(0.006, 0.02, n).astype(np.float32), rgb=rng.uniform(0, 1, (3, n)).astype(np.float32),
+        feat=rng.normal(size=(nf, n)).astype(np.float32) if nf else None)
+    cam = synth.Camera(16, 16, 20.0, 20.0, 7.5, 7.5, np.eye(3, 4, dtype=np.float32))
+    _check(sc, cam, nf, "one tile n=%d nf=%d" % (n, nf), 0.15)
+
+
+def _box_and_power(geom, W, H):
+    """Half extents of each Gaussian's reach box (slot 7, two half floats) and
+    the kernels' float32 power at every pixel, (n, H, W): products and sums in
+    the kernels' order, fused steps rounded once."""
+    f = np.float32
+    box = geom[:, 7].copy().view(np.uint32)
+    hx = (box & 0xFFFF).astype(np.uint16).view(np.float16).astype(f)
+    hy = (box >> 16).astype(np.uint16).view(np.float16).astype(f)
+    u, v, A, B, C = (geom[:, i][:, None, None] for i in range(5))
+    dx = (u - np.arange(W, dtype=f)[None, None, :]).astype(f)
+    dy = (v - np.arange(H, dtype=f)[None, :, None]).astype(f)
+    fma = lambda a, b, c: (a.astype(np.float64) * b + c).astype(f)  # noqa: E731
+    with np.errstate(over="ignore", invalid="ignore"):
+        q = fma((C * dy).astype(f), dy, ((A * dx).astype(f) * dx).astype(f))
+        return hx, hy, dx, dy, fma(np.float32(-0.5) * np.ones_like(q), q, -((B * dx).astype(f) * dy).astype(f))
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("seed", [0, 1])
+def test_reach_box_holds_every_used_pixel(seed, mode):
+    """Needles of axis ratio up to 1e4, blobs wider than the image by orders
+    of magnitude, specks below a pixel and opacities at both ends: every pixel
+    that passes the kernels' alpha test lies inside the box the quarter masks
+    are formed from (the masks leave no used pixel out)."""
+    rng = np.random.default_rng(40 + seed)
+    n = 120
+    z = rng.uniform(1.5, 4.0, n)
+    scale = np.exp(rng.uniform(np.log(1e-3), np.log(0.3), (3, n)))
+    scale[0, :30] = rng.uniform(0.5, 10.0, 30)   # needles
+    scale[1:, :30] = 10.0 ** rng.uniform(-3.0, -1.5, (2, 30))
+    scale[:, 30:36] = 10.0 ** rng.uniform(1.0, 3.0, (3, 6))  # blobs
+    o = rng.uniform(0.02, 0.9, n)
+    o[30:36] = 0.01
+    o[100:110] = 0.0045
+    q = rng.normal(size=(4, n))
+    sc = synth.PlainScene(
+        mean=np.stack([rng.uniform(-0.8, 0.8, n) * z / 2, rng.uniform(-0.8, 0.8, n) * z / 2, z]).astype(np.float32),
+        scale=scale.astype(np.float32), rot=q.astype(np.float32), opacity=o.astype(np.float32),
+        rgb=rng.uniform(0, 1, (3, n)).astype(np.float32))
+    W, H = 75, 53
+    cam = synth.Camera(W, H, 60.0, 60.0, 37.0, 26.0, np.eye(3, 4, dtype=np.float32))
+    g = P.gaussians_to_device(sc.arrays())
+    rc = P.RenderContext([cam], n, n_feat=0, extent_mode=mode)
+    rc.fit(g)
+    rc.forward(g)
+    seen = rc.array(L.CTX_NTILES, torch.int32).cpu().numpy() > 0
+    geom = rc.array(L.CTX_GEOM, torch.float32, width=8).cpu().numpy()[seen]
+    hx, hy, dx, dy, power = _box_and_power(geom, W, H)
+    used = (power <= 0) & (power >= geom[:, 6][:, None, None])
+    outside = (np.abs(dx) > hx[:, None, None]) | (np.abs(dy) > hy[:, None, None])
+    log("case reach box", seed, mode, "used", int(used.sum()), "outside", int((used & outside).sum()))
+    assert used.sum() > 1000
+    assert not np.any(used & outside)
