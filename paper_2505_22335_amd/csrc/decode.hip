@@ -203,8 +203,7 @@ void launch_decode_backward(const DecodeConst& dc, const float* xyz, const float
   w.part = reinterpret_cast<float*>(wb + z.part);
   w.dcpart = reinterpret_cast<float*>(wb + z.dcpart);
   w.nblk_w = (int32_t)z.nblk_w;
-  for (int view = 0; view < dc.n_views; ++view)
-    launch_dec_bwd(dc, ht, dv, xyz, feat, params, dg, view, w, d_xyz, d_feat, d_params != nullptr, s);
+  launch_dec_bwd(dc, ht, dv, xyz, feat, params, dg, w, d_xyz, d_feat, d_params != nullptr, s);
   const unsigned nrb = d_params ? (unsigned)((dc.n_params + 63) / 64) + 1 : 1u;
   const unsigned nmean = d_xyz ? (unsigned)((dc.A * 3 + 255) / 256) : 0u;
   hipLaunchKernelGGL(k_decode_reduce, dim3(nrb + nmean), dim3(256), 0, s, dc, dv, w, d_params, d_pose, (int)nrb, dg,

@@ -1,8 +1,9 @@
-// Decoder backward on the matrix cores (VJP of UP-SLAM Eq. 8 and Eq. 9), per
-// view. One workgroup of eight waves takes 16-anchor tiles in turn: waves
-// 0..3 each own one of the opacity, colour, scale and rotation heads, waves
-// 4..7 share the feature head's output rows. Per tile and head, with X the
-// tile's inputs (one row per anchor):
+// Decoder backward on the matrix cores (VJP of UP-SLAM Eq. 8 and Eq. 9), all
+// views in one launch. One workgroup of eight waves takes (16-anchor tile,
+// view) items in turn, a tile's views one after another: waves 0..3 each own
+// one of the opacity, colour, scale and rotation heads, waves 4..7 share the
+// feature head's output rows. Per item and head, with X the item's inputs (one
+// row per anchor):
 //   Z = X W1^T + b1, H = act(Z)                 (ReLU; SoftPlus for features)
 //   Y = H W2^T + b2, dY = dL/d(decoded) * act'(Y)
 //   dW2 += dY^T H, db2 += sum_a dY, dH = dY W2, dZ = dH * act'(Z)
@@ -13,6 +14,19 @@
 // share of the camera-centre gradient. Each workgroup writes one partial of
 // every parameter gradient, reduced afterwards in a fixed order
 // (deterministic, no atomics).
+//
+// The workgroup meets at one barrier per item. What crosses waves is taken up
+// one item later: the feature waves' dH partials (then the feature head's dX
+// and dW1), the rotation head's dZ (its dW1 is wave 4's), and, after the
+// barrier, the sum of the heads' dX. Every feature wave forms the feature
+// head's hidden layer itself. So the two waves of a SIMD drift apart and one's
+// matrix products run under the other's activations and LDS traffic; each
+// SIMD's pair has about 204 products (32 cycles each) per item at k = 10, 6.5k
+// of the roughly 11k cycles an item takes (16k with three barriers per item
+// and the head's activation chosen per element). One launch per view, each
+// with its own prologue and parameter partials, took 116 us a view for 50k
+// anchors (eight views 928 us, now 540); one view of 100k anchors 177 us, now
+// 150; of 20k 49 us, now 43.
 //
 // Operand layouts. v_mfma_f32_16x16x4f32 (wave64): lane l = 16 g + f supplies
 // A[f][g] and B[g][f] and receives D[4 g + r][f], r = 0..3. A 16x16 block
@@ -28,6 +42,8 @@
 // gradients, which are loaded a tile ahead as coalesced runs.
 #include <math.h>
 
+#include <type_traits>
+
 #include "decode_shared.h"
 
 namespace asgs {
@@ -42,26 +58,32 @@ constexpr int kMaxWG = 256;    // one workgroup per compute unit
 constexpr int kW1L = 36;       // LDS row of a first-layer weight row: 35 inputs + the distance column
 constexpr int kW2L = 36;       // LDS row of a second-layer weight row in the prologue (32 units + pad)
 constexpr int kXL = 52;        // LDS row of an anchor's inputs: 35 + distance column, |x - c| at 36
-constexpr int kHB = 36;        // per-wave transpose rows of H and dZ (32 units + pad)
-constexpr int kYB = 20;        // per-wave transpose rows of dY (16 rows + pad)
+constexpr int kHB = 36;        // per-wave transpose rows of H, dZ (32 units + pad) and two row tiles of dY
 constexpr int kDXL = 36;       // dX row of an anchor in a head's slot
-constexpr int kSlots = 5;      // dX slots: heads 0..3 and the feature head
 
-// LDS carve (floats)
-constexpr int kOffW1 = 0;
-constexpr int kOffX = kOffW1 + kHeads * kHid * kW1L;
-constexpr int kOffHB = kOffX + 2 * 16 * kXL;
-constexpr int kOffYB = kOffHB + kBW * 16 * kHB;
-constexpr int kOffHF = kOffYB + kBW * 16 * kYB;  // the feature head's H, shared by its waves
-constexpr int kOffDH = kOffHF + 16 * kHB;
-constexpr int kOffDX = kOffDH + 4 * 64 * 8;
-constexpr int kOffG = kOffDX + 2 * kSlots * 16 * kDXL;
 constexpr int kPlanes = 27;    // (head, component) planes of the upstream gradients: 1 + 3 + 3 + 4 + 16
-constexpr int kGB = kPlanes * (16 * ASGS_MAX_K + 1);  // one buffer: each plane's run of 16 k values + pad
-constexpr int kLdsFloats = kOffG + 2 * kGB;
-// the second-layer weights (at most 27 k = 432 rows of kW2L), b2 and b1 are
-// copied once into the region from kOffHB on
-static_assert(kLdsFloats - kOffHB >= 27 * ASGS_MAX_K * (kW2L + 1) + 3 + kHeads * kHid, "weight copy does not fit");
+
+// LDS carve (floats); kR: second-layer row tiles per wave
+template <int kR>
+struct Lds {
+  static constexpr int kMaxK = kR == 3 ? 12 : ASGS_MAX_K;                 // largest k of this instantiation
+  static constexpr int kW1 = 0;                                           // [5 heads][32][kW1L]
+  static constexpr int kX = kW1 + kHeads * kHid * kW1L;                   // three items' inputs
+  static constexpr int kTW = kX + 3 * 16 * kXL;                           // temporal weights [2][5 heads][32]
+  static constexpr int kDC = kTW + 2 * kHeads * kHid;                     // camera-centre sums [views][3]
+  static constexpr int kHBo = kDC + 3 * ASGS_MAX_VIEWS;                   // per wave: transpose rows (H, dY, dZ)
+  static constexpr int kHR = kHBo + kBW * 16 * kHB;                       // the rotation head's dZ, two items
+  static constexpr int kDH = kHR + 2 * 16 * kHB;                          // feature dH partials, two items
+  static constexpr int kDX = kDH + 2 * 4 * 64 * 8;                        // dX of heads 0..3, three items
+  static constexpr int kDXF = kDX + 3 * 4 * 16 * kDXL;                    // dX of the feature head, two items
+  static constexpr int kG = kDXF + 2 * 16 * kDXL;
+  static constexpr int kGB = kPlanes * (16 * kMaxK + 1);  // upstream gradients, two items: each plane's run of 16 k values + pad
+  static constexpr int kFloats = kG + 2 * kGB;
+  // the second-layer weights (at most 27 k rows of kW2L), b2 and b1 are copied
+  // once into the region from kHBo on
+  static_assert(kFloats - kHBo >= 27 * kMaxK * (kW2L + 1) + 3 + kHeads * kHid, "weight copy does not fit");
+  static_assert(kFloats * 4 <= 160 * 1024, "LDS");
+};
 
 ASGS_DEV f4v mfma(float a, float b, f4v c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
@@ -83,29 +105,39 @@ ASGS_DEV T pick5(const T (&a)[kHeads], int i) {
   return v;
 }
 
+// The upstream gradient planes of the heads' components: plane p of view v is
+// n values from base[p] + v stride[p] (an absent plane: a stand-in, never used).
+struct PlaneTable {
+  const float* base[32];
+  int64_t stride[32];
+};
+
 template <int kR>
 __global__ void __launch_bounds__(kBT, 1) k_dec_bwd(DecodeConst dc, HeadTable ht, DecodeViews dv,
                                                     const float* __restrict__ xyz, const float* __restrict__ feat,
-                                                    const float* __restrict__ params, asgs_gaussians dg, int view,
+                                                    const float* __restrict__ params, PlaneTable pt,
                                                     DecWork w, float* d_xyz, float* d_feat, int want_params) {
+  using C = Lds<kR>;
   extern __shared__ __attribute__((aligned(16))) float smem[];
   const int t = threadIdx.x;
   const int lane = t & 63;
   const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
   const int fl = lane & 15, fg = lane >> 4;
-  float* const W1L = smem + kOffW1;
-  float (*const XB)[16][kXL] = reinterpret_cast<float (*)[16][kXL]>(smem + kOffX);
-  float (*const HBw)[kHB] = reinterpret_cast<float (*)[kHB]>(smem + kOffHB + wv * 16 * kHB);
-  float (*const YBw)[kYB] = reinterpret_cast<float (*)[kYB]>(smem + kOffYB + wv * 16 * kYB);
-  float (*const HF)[kHB] = reinterpret_cast<float (*)[kHB]>(smem + kOffHF);
-  float* const DH = smem + kOffDH;
-  float (*const DX)[kSlots][16][kDXL] = reinterpret_cast<float (*)[kSlots][16][kDXL]>(smem + kOffDX);
-  float* const GB = smem + kOffG;
+  float* const W1L = smem + C::kW1;
+  float (*const XB)[16][kXL] = reinterpret_cast<float (*)[16][kXL]>(smem + C::kX);
+  float* const TW = smem + C::kTW;
+  float* const DC = smem + C::kDC;
+  float (*const HBw)[kHB] = reinterpret_cast<float (*)[kHB]>(smem + C::kHBo + wv * 16 * kHB);
+  float (*const HR)[16][kHB] = reinterpret_cast<float (*)[16][kHB]>(smem + C::kHR);
+  float* const DH = smem + C::kDH;
+  float (*const DX)[4][16][kDXL] = reinterpret_cast<float (*)[4][16][kDXL]>(smem + C::kDX);
+  float (*const DXF)[16][kDXL] = reinterpret_cast<float (*)[16][kDXL]>(smem + C::kDXF);
+  float* const GB = smem + C::kG;
   const int A = (int)dc.A;
   const int k = dc.k;
   const int n = A * k;
   const int nx = ht.nx;
-  const float lt0 = dv.lt[view][0], lt1 = dv.lt[view][1];
+  const int V = dc.n_views;
   const bool has_feat = ht.m[4] > 0;
   // ---- this wave's head, output rows and duties ----
   const int hd = wv < 4 ? wv : 4;
@@ -128,10 +160,10 @@ __global__ void __launch_bounds__(kBT, 1) k_dec_bwd(DecodeConst dc, HeadTable ht
   // the tile's upstream gradients are staged per (head, component) plane as
   // runs of 16 k values (stride run + 1, odd, against bank conflicts)
   const int run = 16 * k, gstride = run + 1;
-  // ---- per-tile inputs: features, positions and upstream gradients, fetched a
-  // tile ahead into registers and staged through LDS ----
-  // (loads are unconditional, from clamped indices, and masked when staged:
-  // a load under a branch would be waited for at the branch's end)
+  // ---- per-item inputs: features, positions and upstream gradients, fetched an
+  // item ahead into registers and staged through LDS ----
+  // (loads into registers are unconditional, from clamped indices, and masked
+  // when staged: a load under a branch would be waited for at the branch's end)
   float xv = 0.f, pv[3] = {0.f, 0.f, 0.f};
   auto fetch_x = [&](int tile) {
     const int a0 = tile * 16, a = t >> 5, c = t & 31;
@@ -140,83 +172,75 @@ __global__ void __launch_bounds__(kBT, 1) k_dec_bwd(DecodeConst dc, HeadTable ht
 #pragma unroll
     for (int cc = 0; cc < 3; ++cc) pv[cc] = xyz[(int64_t)cc * A + ap];
   };
-  auto put_x = [&](int buf, int tile) {
+  auto put_x = [&](int buf, int tile, int view) {
     const int a0 = tile * 16;
     XB[buf][t >> 5][t & 31] = a0 + (t >> 5) < A ? xv : 0.f;
-    if (t < 16) {
-      float D[3] = {0.f, 0.f, 0.f}, dist = 1.f;
-      if (a0 + t < A) {
-        for (int c = 0; c < 3; ++c) D[c] = pv[c] - dv.c[view][c];
-        dist = sqrtf(D[0] * D[0] + D[1] * D[1] + D[2] * D[2]);
-        for (int c = 0; c < 3; ++c) D[c] /= dist;
+    if (wv == 0) {
+      // lane 16 c + a: component c of anchor a's direction; lanes 48 + a: its distance
+      const bool ok = a0 + fl < A;
+      float D[3];
+      for (int c = 0; c < 3; ++c) D[c] = pv[c] - dv.c[view][c];
+      const float dist = ok ? sqrtf(D[0] * D[0] + D[1] * D[1] + D[2] * D[2]) : 1.f;
+      const float dc_ = fg == 0 ? D[0] : fg == 1 ? D[1] : D[2];
+      const float del = ok ? dc_ / dist : 0.f;
+      if (fg < 3) {
+        XB[buf][fl][32 + fg] = del;
+      } else {
+        XB[buf][fl][35] = nx > 0 && ok ? dist : 0.f;  // distance input (weight column 35)
+        XB[buf][fl][36] = dist;                       // |x - c| for the anchor gradients
       }
-      for (int c = 0; c < 3; ++c) XB[buf][t][32 + c] = D[c];
-      XB[buf][t][35] = nx > 0 && a0 + t < A ? dist : 0.f;  // distance input (weight column 35)
-      XB[buf][t][36] = dist;                                // |x - c| for the anchor gradients
     }
   };
-  // wave w loads planes w, w + 8, w + 16, w + 24 (those present), each as
-  // kR coalesced chunks of 64 values (16 k <= 64 kR)
+  // wave w loads planes w, w + 8, w + 16, w + 24, each as kR coalesced chunks of
+  // 64 values (16 k <= 64 kR) at 32-bit offsets from the plane; values past the
+  // last anchor repeat the plane's last one and are masked where they are used
   const int nplanes = has_feat ? kPlanes : 11;
-  // the plane, or for an absent plane the first parameter as a stand-in
-  // that is only ever read at index 0
-  const float* pbase[4];
-  int plim[4];  // indices below plim are read from the plane, others at 0
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int p = wv + 8 * i;
-    const int ph = p < 1 ? 0 : p < 4 ? 1 : p < 7 ? 2 : p < 11 ? 3 : 4;
-    const int pc = p - (ph == 0 ? 0 : ph == 1 ? 1 : ph == 2 ? 4 : ph == 3 ? 7 : 11);
-    const bool present = p < nplanes;
-    pbase[i] = present ? out_plane(dg, view, ph, pc, n) : params;
-    plim[i] = present ? n : 0;
-  }
   float gpre[4][kR];
-  auto fetch_g = [&](int tile) {
-    const int g0 = tile * run;
+  auto fetch_g = [&](int tile, int view) {
+    uint32_t off[kR];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int c = 0; c < kR; ++c) off[c] = 4u * (uint32_t)min(tile * run + lane + 64 * c, n - 1);
 #pragma unroll
-      for (int c = 0; c < kR; ++c) {
-        const int gi = g0 + lane + 64 * c;
-        gpre[i][c] = pbase[i][gi < plim[i] ? gi : 0];
-      }
+    for (int i = 0; i < 4; ++i) {
+      const int p = wv + 8 * i < nplanes ? wv + 8 * i : 0;
+      const char* src = reinterpret_cast<const char*>(pt.base[p] + view * pt.stride[p]);
+#pragma unroll
+      for (int c = 0; c < kR; ++c) gpre[i][c] = *reinterpret_cast<const float*>(src + off[c]);
+    }
   };
-  auto put_g = [&](int buf, int tile) {
-    const int g0 = tile * run;
+  auto put_g = [&](int buf) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       if (wv + 8 * i >= nplanes) break;
+      float* dst = GB + buf * C::kGB + (wv + 8 * i) * gstride + lane;
 #pragma unroll
-      for (int c = 0; c < kR; ++c) {
-        const int idx = lane + 64 * c;
-        if (idx < run) GB[buf * kGB + (wv + 8 * i) * gstride + idx] = g0 + idx < n ? gpre[i][c] : 0.f;
-      }
+      for (int c = 0; c < kR; ++c)
+        if (lane + 64 * c < run) dst[64 * c] = gpre[i][c];
     }
   };
   const int ngrid = (A + 15) / 16;
   if ((int)blockIdx.x < ngrid) {
     fetch_x(blockIdx.x);
-    fetch_g(blockIdx.x);
+    fetch_g(blockIdx.x, 0);
   }
   // ---- the weights into LDS (coalesced): the first-layer rows of every head
   // (kept for the whole kernel); the second-layer rows (36 floats: b128 reads
   // of four units and b32 reads across rows without bank conflicts), b2 and
-  // b1 (with the view's temporal term), in the region past the input tiles,
-  // which is free until the first tile is staged ----
-  float* const W2L = smem + kOffHB;                         // [all rows][kW2L]
+  // b1, in the region past the input tiles, which is free until the first item
+  // is staged ----
+  float* const W2L = smem + C::kHBo;                         // [all rows][kW2L]
   const int nrows = ht.nrows;
   float* const B2L = W2L + nrows * kW2L;                    // [all rows]
   float* const B1L = B2L + ((nrows + 3) & ~3);             // [5 heads][32] (16-byte aligned)
   {
     // head by head, each a contiguous block of the packed parameters: every
     // load of the thread is issued before its first store
-    constexpr int kK = kR == 3 ? 12 : ASGS_MAX_K;  // largest k of this instantiation
+    constexpr int kK = C::kMaxK;
     constexpr int kMs[kHeads] = {1, 3, 3, 4, 16};
     constexpr int kE1 = (kHid * kIn + kBT - 1) / kBT;
     constexpr int kE2m = (16 * kK * kHid + kBT - 1) / kBT;
     const int nh = has_feat ? kHeads : 4;
-    float v1[kHeads][kE1], v2[kHeads][kE2m], vd[kHeads], vb1[kHeads], vb2[kHeads];
+    float v1[kHeads][kE1], v2[kHeads][kE2m], vd[kHeads], vb1[kHeads], vb2[kHeads], vt0[kHeads], vt1[kHeads];
 #pragma unroll
     for (int h = 0; h < kHeads; ++h) {
       if (h >= nh) break;
@@ -236,7 +260,8 @@ __global__ void __launch_bounds__(kBT, 1) k_dec_bwd(DecodeConst dc, HeadTable ht
       }
       vd[h] = nx > 0 ? params[ox + (t & 31) * nx] : 0.f;
       vb1[h] = params[o1 + kHid * kIn + (t & 31)];
-      if (nx == 3) vb1[h] += params[ox + (t & 31) * 3 + 1] * lt0 + params[ox + (t & 31) * 3 + 2] * lt1;
+      vt0[h] = nx == 3 ? params[ox + (t & 31) * 3 + 1] : 0.f;
+      vt1[h] = nx == 3 ? params[ox + (t & 31) * 3 + 2] : 0.f;
       vb2[h] = params[w2 + rw * kHid + (t < rw ? t : 0)];
     }
 #pragma unroll
@@ -259,14 +284,17 @@ __global__ void __launch_bounds__(kBT, 1) k_dec_bwd(DecodeConst dc, HeadTable ht
       if (t < kHid) {
         W1L[(h * kHid + t) * kW1L + kIn] = vd[h];  // the distance weight (zero without that input)
         B1L[h * kHid + t] = vb1[h];
+        TW[h * kHid + t] = vt0[h];
+        TW[(kHeads + h) * kHid + t] = vt1[h];
       }
       if (t < rw) B2L[r0 + t] = vb2[h];
     }
     // input columns past 36 only meet discarded outputs of dW1; keep them finite
-    for (int e = t; e < 2 * 16 * (kXL - 37); e += kBT) {
+    for (int e = t; e < 3 * 16 * (kXL - 37); e += kBT) {
       const int row = e / (kXL - 37);
       XB[row >> 4][row & 15][37 + e - row * (kXL - 37)] = 0.f;
     }
+    if (t < 3 * ASGS_MAX_VIEWS) DC[t] = 0.f;
   }
   __syncthreads();
   // ---- second-layer weights and biases in registers ----
@@ -308,8 +336,8 @@ __global__ void __launch_bounds__(kBT, 1) k_dec_bwd(DecodeConst dc, HeadTable ht
   }
   __syncthreads();  // the second-layer copy is no longer read
   if ((int)blockIdx.x < ngrid) {
-    put_x(0, blockIdx.x);
-    put_g(0, blockIdx.x);
+    put_x(0, blockIdx.x, 0);
+    put_g(0);
   }
   __syncthreads();
   // ---- accumulators ----
@@ -323,49 +351,55 @@ __global__ void __launch_bounds__(kBT, 1) k_dec_bwd(DecodeConst dc, HeadTable ht
   f4v dw1[2][3];
 #pragma unroll
   for (int b = 0; b < 2; ++b) dw1[b][0] = dw1[b][1] = dw1[b][2] = f4v{0.f, 0.f, 0.f, 0.f};
-  float db1[2] = {0.f, 0.f};
-  float dcl[3] = {0.f, 0.f, 0.f};
+  float db1[2] = {0.f, 0.f}, dt0[2] = {0.f, 0.f}, dt1[2] = {0.f, 0.f};  // bias and temporal weights
   const float* w1l = W1L + hd * kHid * kW1L;
 
   // dZ from dH and H (registers, units x anchors), then the head's dX^T into
-  // its slot; with publish, dZ also into the wave's transpose rows
-  auto tail = [&](const f4v (&h)[2], const f4v (&dh)[2], int buf, bool dx_now, bool publish) {
+  // its slot dxs and dZ into transpose rows pub (either may be NULL)
+  auto tail = [&](const f4v (&h)[2], const f4v (&dh)[2], float (*dxs)[kDXL], float (*pub)[kHB]) {
     f4v dz[2];
+    if (hd == 4) {
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+      for (int e = 0; e < 8; ++e) dz[e >> 2][e & 3] = dh[e >> 2][e & 3] * (1.f - fexp(-h[e >> 2][e & 3]));
+    } else {
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        dz[b][r] = hd == 4 ? dh[b][r] * (1.f - fexp(-h[b][r])) : (h[b][r] > 0.f ? dh[b][r] : 0.f);
-    if (dx_now) {
+      for (int e = 0; e < 8; ++e) dz[e >> 2][e & 3] = h[e >> 2][e & 3] > 0.f ? dh[e >> 2][e & 3] : 0.f;
+    }
+    if (pub) {
+#pragma unroll
+      for (int b = 0; b < 2; ++b) *reinterpret_cast<f4v*>(&pub[fl][16 * b + 4 * fg]) = dz[b];
+    }
+    if (dxs) {
       // dX^T (inputs x anchors) = W1^T dZ^T, K = units
       f4v dx[3];
 #pragma unroll
       for (int ct = 0; ct < 3; ++ct) dx[ct] = f4v{0.f, 0.f, 0.f, 0.f};
+      // columns past 36 (lanes of the third block) give rows of dX^T that are not kept
+      const int c2 = 32 + (fl & 3);
 #pragma unroll
-      for (int b = 0; b < 2; ++b)
+      for (int b = 0; b < 2; ++b) {
+        float wr[4][3];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const float* wr = w1l + (16 * b + 4 * fg + r) * kW1L;
-#pragma unroll
-          for (int ct = 0; ct < 3; ++ct) {
-            const int i = 16 * ct + fl;
-            const float wv1 = wr[i < kW1L ? i : 0];
-            dx[ct] = mfma(i < kW1L ? wv1 : 0.f, dz[b][r], dx[ct]);
-          }
+          const float* row = w1l + (16 * b + 4 * fg + r) * kW1L;
+          wr[r][0] = row[fl];
+          wr[r][1] = row[16 + fl];
+          wr[r][2] = row[c2];
         }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int ct = 0; ct < 3; ++ct) dx[ct] = mfma(wr[r][ct], dz[b][r], dx[ct]);
+      }
       // lane (f, g) holds dX[anchor f][inputs 16 ct + 4 g + r]
 #pragma unroll
       for (int ct = 0; ct < 3; ++ct)
-        if (16 * ct + 4 * fg < kDXL) *reinterpret_cast<f4v*>(&DX[buf][wv < 4 ? wv : 4][fl][16 * ct + 4 * fg]) = dx[ct];
-    }
-    if (publish) {
-#pragma unroll
-      for (int b = 0; b < 2; ++b) *reinterpret_cast<f4v*>(&HBw[fl][16 * b + 4 * fg]) = dz[b];
+        if (16 * ct + 4 * fg < kDXL) *reinterpret_cast<f4v*>(&dxs[fl][16 * ct + 4 * fg]) = dx[ct];
     }
   };
   // dW1 += dZ^T X, db1 += sum_a dZ, with dZ read by rows of anchors from the
-  // transpose rows src of the wave that formed it
-  auto acc_dw1 = [&](const float (*src)[kHB], int buf) {
+  // transpose rows src of the wave that formed it; view: the item's
+  auto acc_dw1 = [&](const float (*src)[kHB], const float (*xb)[kXL], int view) {
     float dzt[2][4];
 #pragma unroll
     for (int b = 0; b < 2; ++b)
@@ -375,195 +409,255 @@ __global__ void __launch_bounds__(kBT, 1) k_dec_bwd(DecodeConst dc, HeadTable ht
 #pragma unroll
     for (int ct = 0; ct < 3; ++ct)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) xa[ct][r] = XB[buf][4 * fg + r][16 * ct + fl];
+      for (int r = 0; r < 4; ++r) xa[ct][r] = xb[4 * fg + r][16 * ct + fl];
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
-      db1[b] += (dzt[b][0] + dzt[b][1]) + (dzt[b][2] + dzt[b][3]);
+      const float c = (dzt[b][0] + dzt[b][1]) + (dzt[b][2] + dzt[b][3]);
+      db1[b] += c;
+      if (nx == 3) {
+        dt0[b] = fmaf(dv.lt[view][0], c, dt0[b]);
+        dt1[b] = fmaf(dv.lt[view][1], c, dt1[b]);
+      }
 #pragma unroll
       for (int r = 0; r < 4; ++r)
 #pragma unroll
         for (int ct = 0; ct < 3; ++ct) dw1[b][ct] = mfma(dzt[b][r], xa[ct][r], dw1[b][ct]);
     }
   };
-  float (*const HB3)[kHB] = reinterpret_cast<float (*)[kHB]>(smem + kOffHB + 3 * 16 * kHB);
 
-  int j = 0;
-  for (int tile = blockIdx.x; tile < ngrid; tile += gridDim.x, ++j) {
-    const int a0 = tile * 16;
-    const int buf = j & 1;
-    const bool more = tile + (int)gridDim.x < ngrid;
-    const float* gb = GB + buf * kGB;
-    if (more) {
-      fetch_x(tile + gridDim.x);
-      fetch_g(tile + gridDim.x);
+  f4v hp[2];  // the feature waves' H of the previous item
+  hp[0] = hp[1] = f4v{0.f, 0.f, 0.f, 0.f};
+  float gfeat = 0.f, gxyz = 0.f;  // anchor gradients of the tile, over its views
+  int tile = blockIdx.x, view = 0, ptile = 0, pview = 0;  // this item's and the previous one's
+  int xcur = 0, xprev = 2;                                // their input buffers
+  bool have = tile < ngrid;
+  // item by item, and one more round for what the last item left
+  for (int par = 0, prev = 0; have || prev; par ^= 1) {
+    int ntile = tile, nview = view + 1;
+    if (nview == V) {
+      nview = 0;
+      ntile += (int)gridDim.x;
     }
-    f4v h[2], dh[2];
-    dh[0] = dh[1] = f4v{0.f, 0.f, 0.f, 0.f};
-    float ht_[2][4];
-    if (wv < 4) {
+    const bool more = have && ntile < ngrid;
+    const int xnext = xcur == 2 ? 0 : xcur + 1;
+    if (more) {
+      if (ntile != tile) fetch_x(ntile);
+      fetch_g(ntile, nview);
+    }
+    f4v h[2];
+    h[0] = h[1] = f4v{0.f, 0.f, 0.f, 0.f};
+    if (have && active) {
+      const float (*xb)[kXL] = XB[xcur];
+      const float* gb = GB + par * C::kGB;
+      const int nanch = A - tile * 16;  // anchors of the tile (or more)
+      f4v dh[2];
+      dh[0] = dh[1] = f4v{0.f, 0.f, 0.f, 0.f};
       // Z^T (units x anchors) = W1 X^T, K = inputs
-      f4v z0 = {0.f, 0.f, 0.f, 0.f}, z1 = z0;
+      f4v z[2];
+      z[0] = z[1] = f4v{0.f, 0.f, 0.f, 0.f};
+      {
+        // every operand requested before the first product
+        float x[9], wa[9], wb[9];
 #pragma unroll
-      for (int s = 0; s < 9; ++s) {
-        const float xb = XB[buf][fl][4 * s + fg];
-        z0 = mfma(w1l[fl * kW1L + 4 * s + fg], xb, z0);
-        z1 = mfma(w1l[(16 + fl) * kW1L + 4 * s + fg], xb, z1);
+        for (int s = 0; s < 9; ++s) {
+          x[s] = xb[fl][4 * s + fg];
+          wa[s] = w1l[fl * kW1L + 4 * s + fg];
+          wb[s] = w1l[(16 + fl) * kW1L + 4 * s + fg];
+        }
+#pragma unroll
+        for (int s = 0; s < 9; ++s) {
+          z[0] = mfma(wa[s], x[s], z[0]);
+          z[1] = mfma(wb[s], x[s], z[1]);
+        }
       }
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        h[0][r] = fmaxf(z0[r] + b1r[0][r], 0.f);
-        h[1][r] = fmaxf(z1[r] + b1r[1][r], 0.f);
+      for (int b = 0; b < 2; ++b) {
+        f4v b1 = {b1r[b][0], b1r[b][1], b1r[b][2], b1r[b][3]};
+        if (nx == 3) {
+          // the view's temporal term
+          const f4v s0 = *reinterpret_cast<const f4v*>(&TW[hd * kHid + 16 * b + 4 * fg]);
+          const f4v s1 = *reinterpret_cast<const f4v*>(&TW[(kHeads + hd) * kHid + 16 * b + 4 * fg]);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) b1[r] += s0[r] * dv.lt[view][0] + s1[r] * dv.lt[view][1];
+        }
+        z[b] += b1;
+      }
+      if (hd == 4) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) h[e >> 2][e & 3] = fsoftplus(z[e >> 2][e & 3]);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) h[e >> 2][e & 3] = fmaxf(z[e >> 2][e & 3], 0.f);
       }
       // H by rows of anchors (B operand of dW2)
 #pragma unroll
       for (int b = 0; b < 2; ++b) *reinterpret_cast<f4v*>(&HBw[fl][16 * b + 4 * fg]) = h[b];
       wave_sync();
+      float ht_[2][4];
 #pragma unroll
       for (int b = 0; b < 2; ++b)
 #pragma unroll
         for (int r = 0; r < 4; ++r) ht_[b][r] = HBw[4 * fg + r][16 * b + fl];
-    } else if (has_feat && q < 2) {
-      // the feature head's hidden layer once: unit block q on feature wave q
-      f4v z = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int s = 0; s < 9; ++s) z = mfma(w1l[(16 * q + fl) * kW1L + 4 * s + fg], XB[buf][fl][4 * s + fg], z);
-      f4v hq;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) hq[r] = fsoftplus(z[r] + (q ? b1r[1][r] : b1r[0][r]));
-      *reinterpret_cast<f4v*>(&HF[fl][16 * q + 4 * fg]) = hq;
-    }
-    __syncthreads();  // the feature head's H is complete
-    if (wv >= 4 && has_feat) {
-#pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        h[b] = *reinterpret_cast<const f4v*>(&HF[fl][16 * b + 4 * fg]);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) ht_[b][r] = HF[4 * fg + r][16 * b + fl];
-      }
-    }
-    if (active) {
-#pragma unroll
-      for (int i = 0; i < kR; ++i) {
-        if (i >= nt) break;
+      wave_sync();
+      // row tiles i0 .. i0 + cnt - 1 together, so that their product chains interleave
+      auto row_tiles = [&](auto cnt, auto first) {
+        constexpr int N = decltype(cnt)::value, i0 = decltype(first)::value;
         // Y (anchors x rows) = H W2^T, K = units
-        f4v y = {0.f, 0.f, 0.f, 0.f};
+        f4v y[N], dy[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+          y[i] = f4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int r = 0; r < 4; ++r) dy[i][r] = gb[goff[i0 + i] + (4 * fg + r) * k];  // a valid location for every lane
+        }
 #pragma unroll
         for (int b = 0; b < 2; ++b)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) y = mfma(h[b][r], w2y[i][b][r], y);
-        f4v dy;
+          for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const float gv = gb[goff[i] + (4 * fg + r) * k];  // a valid location for every lane
-          dy[r] = (rok[i] ? gv : 0.f) * fact_grad(hd, y[r] + b2r[i], dc.l_s);
+            for (int i = 0; i < N; ++i) y[i] = mfma(h[b][r], w2y[i0 + i][b][r], y[i]);
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) dy[i][r] = rok[i0 + i] && 4 * fg + r < nanch ? dy[i][r] : 0.f;
+        if (hd < 3) {
+          // sigmoid outputs (scaled by l_s for the scale head); rotation and feature are raw
+#pragma unroll
+          for (int i = 0; i < N; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const float s = fsigm(y[i][r] + b2r[i0 + i]);
+              dy[i][r] *= hd == 2 ? dc.l_s * s * (1.f - s) : s * (1.f - s);
+            }
         }
-        db2[i] += (dy[0] + dy[1]) + (dy[2] + dy[3]);
+        // dY transposed through LDS
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) HBw[4 * fg + r][16 * i + fl] = dy[i][r];
+        wave_sync();
+        f4v dyt[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) dyt[i] = *reinterpret_cast<const f4v*>(&HBw[fl][16 * i + 4 * fg]);
+        wave_sync();
         // dW2 (rows x units) += dY^T H, K = anchors
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int r = 0; r < 4; ++r)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) dw2[i][b] = mfma(dy[r], ht_[b][r], dw2[i][b]);
-        // dH^T (units x anchors) += W2^T dY^T, K = rows (dY transposed through LDS)
+          for (int i = 0; i < N; ++i)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) YBw[4 * fg + r][fl] = dy[r];
-        wave_sync();
-        const f4v dyt = *reinterpret_cast<const f4v*>(&YBw[fl][4 * fg]);
-        wave_sync();
+            for (int b = 0; b < 2; ++b) dw2[i0 + i][b] = mfma(dy[i][r], ht_[b][r], dw2[i0 + i][b]);
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int i = 0; i < N; ++i) db2[i0 + i] += (dy[i][0] + dy[i][1]) + (dy[i][2] + dy[i][3]);
+        // dH^T (units x anchors) += W2^T dY^T, K = rows
 #pragma unroll
-          for (int r = 0; r < 4; ++r) dh[b] = mfma(w2h[i][b][r], dyt[r], dh[b]);
+        for (int i = 0; i < N; ++i)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) dh[b] = mfma(w2h[i0 + i][b][r], dyt[i][r], dh[b]);
+      };
+      using I0 = std::integral_constant<int, 0>;
+      using I1 = std::integral_constant<int, 1>;
+      using I2 = std::integral_constant<int, 2>;
+      if (nt >= 2) row_tiles(I2{}, I0{});
+      else if (nt == 1) row_tiles(I1{}, I0{});
+      if (nt == 3) row_tiles(I1{}, I2{});
+      if constexpr (kR > 3)
+        if (nt == 4) row_tiles(I2{}, I2{});
+      if (wv < 4) {
+        tail(h, dh, DX[xcur][wv], wv == 3 ? HR[par] : HBw);
+        if (wv < 3) {
+          wave_sync();
+          acc_dw1(HBw, xb, view);
+        }
+      } else {
+        // the feature waves' dH partials, summed below in a fixed order
+#pragma unroll
+        for (int b = 0; b < 2; ++b) *reinterpret_cast<f4v*>(&DH[((par * 4 + q) * 64 + lane) * 8 + 4 * b]) = dh[b];
       }
     }
-    if (wv < 4) {
-      tail(h, dh, buf, true, true);
-      if (hw1 >= 0) {
-        wave_sync();
-        acc_dw1(HBw, buf);
-      }
-    } else if (active) {
-      // the feature waves' dH partials, summed below in a fixed order
+    // ---- what the previous item left to other waves ----
+    if (prev) {
+      if (wv == 4) acc_dw1(HR[par ^ 1], XB[xprev], pview);  // the rotation head's dW1
+      if (wv >= 6 && has_feat) {
+        f4v dh[2];
+        const float* D = DH + (par ^ 1) * 4 * 64 * 8;
 #pragma unroll
-      for (int b = 0; b < 2; ++b) *reinterpret_cast<f4v*>(&DH[(q * 64 + lane) * 8 + 4 * b]) = dh[b];
-    }
-    __syncthreads();  // feature dH partials and the rotation head's dZ written; every thread is past the last tile's anchor step
-    if (wv == 4) acc_dw1(HB3, buf);  // the rotation head's dW1
-    if (wv >= 4 && active && (q == 2 || q == 3)) {
-#pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        const f4v p0 = *reinterpret_cast<const f4v*>(&DH[(0 * 64 + lane) * 8 + 4 * b]);
-        const f4v p1 = *reinterpret_cast<const f4v*>(&DH[(1 * 64 + lane) * 8 + 4 * b]);
-        const f4v p2 = *reinterpret_cast<const f4v*>(&DH[(2 * 64 + lane) * 8 + 4 * b]);
-        const f4v p3 = *reinterpret_cast<const f4v*>(&DH[(3 * 64 + lane) * 8 + 4 * b]);
-        dh[b] = (p0 + p1) + (p2 + p3);
-      }
-      tail(h, dh, buf, q == 2, q == 3);
-      if (q == 3) {
-        wave_sync();
-        acc_dw1(HBw, buf);
+        for (int b = 0; b < 2; ++b) {
+          const f4v p0 = *reinterpret_cast<const f4v*>(&D[(0 * 64 + lane) * 8 + 4 * b]);
+          const f4v p1 = *reinterpret_cast<const f4v*>(&D[(1 * 64 + lane) * 8 + 4 * b]);
+          const f4v p2 = *reinterpret_cast<const f4v*>(&D[(2 * 64 + lane) * 8 + 4 * b]);
+          const f4v p3 = *reinterpret_cast<const f4v*>(&D[(3 * 64 + lane) * 8 + 4 * b]);
+          dh[b] = (p0 + p1) + (p2 + p3);
+        }
+        // wave 6: dX; wave 7: dW1
+        tail(hp, dh, wv == 6 ? DXF[par ^ 1] : nullptr, wv == 7 ? HBw : nullptr);
+        if (wv == 7) {
+          wave_sync();
+          acc_dw1(HBw, XB[xprev], pview);
+        }
       }
     }
+    hp[0] = h[0];
+    hp[1] = h[1];
     if (more) {
-      put_x(buf ^ 1, tile + gridDim.x);
-      put_g(buf ^ 1, tile + gridDim.x);
+      put_x(xnext, ntile, nview);
+      put_g(par ^ 1);
     }
-    __syncthreads();  // every head's dX of the tile is in its slot; the next tile's inputs staged
-    // ---- anchor gradients of the tile ----
-    {
-      const int a = t >> 5, c = t & 31;
-      if (d_feat && a0 + a < A) {
-        float v = (DX[buf][0][a][c] + DX[buf][1][a][c]) + (DX[buf][2][a][c] + DX[buf][3][a][c]);
-        if (has_feat) v += DX[buf][4][a][c];
-        float* p = d_feat + (int64_t)(a0 + a) * 32 + c;
-        *p = (view == 0 ? 0.f : *p) + v;
+    __syncthreads();  // the previous item's dX is complete; the next item's inputs are staged
+    // ---- anchor gradients of the previous item ----
+    if (prev) {
+      const int a0 = ptile * 16, a = t >> 5, c = t & 31;
+      const float (*D0)[16][kDXL] = DX[xprev];
+      const float (*D4)[kDXL] = DXF[par ^ 1];
+      const bool first = pview == 0, last = pview == V - 1;
+      {
+        float v = (D0[0][a][c] + D0[1][a][c]) + (D0[2][a][c] + D0[3][a][c]);
+        if (has_feat) v += D4[a][c];
+        gfeat = first ? v : gfeat + v;
+        if (last && d_feat && a0 + a < A) d_feat[(int64_t)(a0 + a) * 32 + c] = gfeat;
       }
-      if (t < 16 && a0 + t < A) {
-        float gd[3], del[3];
-        for (int cc = 0; cc < 3; ++cc) {
-          gd[cc] = (DX[buf][0][t][32 + cc] + DX[buf][1][t][32 + cc]) + (DX[buf][2][t][32 + cc] + DX[buf][3][t][32 + cc]);
-          if (has_feat) gd[cc] += DX[buf][4][t][32 + cc];
-          del[cc] = XB[buf][t][32 + cc];
-        }
-        float gdist = 0.f;
-        if (nx > 0) {
-          gdist = (DX[buf][0][t][35] + DX[buf][1][t][35]) + (DX[buf][2][t][35] + DX[buf][3][t][35]);
-          if (has_feat) gdist += DX[buf][4][t][35];
-        }
-        const float dist = XB[buf][t][36];
-        const float pr = del[0] * gd[0] + del[1] * gd[1] + del[2] * gd[2];
-        for (int cc = 0; cc < 3; ++cc) {
-          // through delta = D / |D| (projected, scaled by 1/|D|) and |D| (along delta)
-          const float dD = (gd[cc] - del[cc] * pr) / dist + gdist * del[cc];
-          if (d_xyz) {
-            float* p = &d_xyz[(int64_t)cc * A + a0 + t];
-            *p = (view == 0 ? 0.f : *p) + dD;
-          }
-          dcl[cc] -= dD;
-        }
+      if (wv == 0) {
+        // lane 16 c + a: component c of anchor a; lanes 48 + a: its distance
+        const int col = 32 + fg;
+        float g = (D0[0][fl][col] + D0[1][fl][col]) + (D0[2][fl][col] + D0[3][fl][col]);
+        if (has_feat) g += D4[fl][col];
+        const float del = XB[xprev][fl][col], dist = XB[xprev][fl][36];
+        const float pd = fg < 3 ? del * g : 0.f;
+        const float p1 = pd + __shfl_xor(pd, 16);
+        const float pr = p1 + __shfl_xor(p1, 32);
+        const float gdist = nx > 0 ? __shfl(g, 48 + fl) : 0.f;
+        // through delta = D / |D| (projected, scaled by 1/|D|) and |D| (along delta)
+        const float dD = a0 + fl < A && fg < 3 ? (g - del * pr) / dist + gdist * del : 0.f;
+        gxyz = first ? dD : gxyz + dD;
+        if (last && d_xyz && a0 + fl < A && fg < 3) d_xyz[(int64_t)fg * A + a0 + fl] = gxyz;
+        // the camera-centre sum over the anchors
+        float x = dD;
+        x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x128, 0xF, 0xF, true));  // row_ror 8
+        x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x124, 0xF, 0xF, true));  // row_ror 4
+        x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x122, 0xF, 0xF, true));  // row_ror 2
+        x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x121, 0xF, 0xF, true));  // row_ror 1
+        if (fl == 0 && fg < 3) DC[3 * pview + fg] -= x;
       }
     }
+    prev = have;
+    ptile = tile;
+    pview = view;
+    xprev = xcur;
+    xcur = xnext;
+    tile = ntile;
+    view = nview;
+    have = more;
   }
-  // ---- the workgroup's camera-centre partial (lanes 0..15 of wave 0) ----
-  if (wv == 0) {
-#pragma unroll
-    for (int cc = 0; cc < 3; ++cc) {
-      float x = dcl[cc];
-      x += __shfl_xor(x, 8);
-      x += __shfl_xor(x, 4);
-      x += __shfl_xor(x, 2);
-      x += __shfl_xor(x, 1);
-      if (lane == 0) w.dcpart[((int64_t)blockIdx.x * dc.n_views + view) * 3 + cc] = x;
-    }
-  }
+  // ---- the workgroup's camera-centre partials ----
+  __syncthreads();
+  if (t < 3 * V) w.dcpart[(int64_t)blockIdx.x * 3 * V + t] = DC[t];
   if (!want_params) return;
   // ---- this workgroup's parameter partials ----
   float* P = w.part;
   const int64_t bk = blockIdx.x, nbk = w.nblk_w;
-  const bool add = view > 0;
-  auto put = [&](int64_t pi, float v) {
-    float* dst = P + part_index(pi, bk, nbk);
-    *dst = (add ? *dst : 0.f) + v;
-  };
+  auto put = [&](int64_t pi, float v) { P[part_index(pi, bk, nbk)] = v; };
 #pragma unroll
   for (int i = 0; i < kR; ++i) {
     if (!active || i >= nt) break;
@@ -584,8 +678,8 @@ __global__ void __launch_bounds__(kBT, 1) k_dec_bwd(DecodeConst dc, HeadTable ht
   if (hw1 < 0) return;
   const int o1w = (int)ht.off[hw1], oxw = (int)ht.xoff[hw1];  // the head of this wave's dW1
   // extra input columns: the distance weight's gradient is column 35 of the
-  // products with X; the temporal weights' gradients are the bias gradient
-  // times the view's embedding (accumulated over views by put)
+  // products with X; the temporal weights' gradients are the items' bias
+  // gradients times their view's embedding
 #pragma unroll
   for (int b = 0; b < 2; ++b) {
 #pragma unroll
@@ -596,15 +690,19 @@ __global__ void __launch_bounds__(kBT, 1) k_dec_bwd(DecodeConst dc, HeadTable ht
       if (fl < 3) put(o1w + u * kIn + 32 + fl, dw1[b][2][r]);
       if (fl == 3 && nx > 0) put(oxw + u * nx, dw1[b][2][r]);
     }
-    float sb = db1[b];
+    float sb = db1[b], s0 = dt0[b], s1 = dt1[b];
     sb += __shfl_xor(sb, 16);
+    s0 += __shfl_xor(s0, 16);
+    s1 += __shfl_xor(s1, 16);
     sb += __shfl_xor(sb, 32);
+    s0 += __shfl_xor(s0, 32);
+    s1 += __shfl_xor(s1, 32);
     if (fg == 0) {
       const int u = 16 * b + fl;
       put(o1w + kHid * kIn + u, sb);
       if (nx == 3) {
-        put(oxw + u * 3 + 1, sb * lt0);
-        put(oxw + u * 3 + 2, sb * lt1);
+        put(oxw + u * 3 + 1, s0);
+        put(oxw + u * 3 + 2, s1);
       }
     }
   }
@@ -612,16 +710,17 @@ __global__ void __launch_bounds__(kBT, 1) k_dec_bwd(DecodeConst dc, HeadTable ht
 
 template <int kR>
 void launch_k(const DecodeConst& dc, const HeadTable& ht, const DecodeViews& dv, const float* xyz, const float* feat,
-              const float* params, const asgs_gaussians& dg, int view, const DecWork& w, float* d_xyz,
+              const float* params, const PlaneTable& pt, const DecWork& w, float* d_xyz,
               float* d_feat, bool want_params, hipStream_t s) {
+  constexpr int kBytes = Lds<kR>::kFloats * (int)sizeof(float);
   static bool attr_set = false;  // more than 64 KiB of dynamic LDS
   if (!attr_set) {
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_dec_bwd<kR>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, kLdsFloats * (int)sizeof(float));
+                              hipFuncAttributeMaxDynamicSharedMemorySize, kBytes);
     attr_set = true;
   }
-  hipLaunchKernelGGL(k_dec_bwd<kR>, dim3((unsigned)w.nblk_w), dim3(kBT), kLdsFloats * sizeof(float), s, dc, ht, dv,
-                     xyz, feat, params, dg, view, w, d_xyz, d_feat, want_params ? 1 : 0);
+  hipLaunchKernelGGL(k_dec_bwd<kR>, dim3((unsigned)w.nblk_w), dim3(kBT), kBytes, s, dc, ht, dv,
+                     xyz, feat, params, pt, w, d_xyz, d_feat, want_params ? 1 : 0);
 }
 
 }  // namespace
@@ -632,14 +731,29 @@ int64_t dec_bwd_blocks(int64_t n_anchors) {
 }
 
 void launch_dec_bwd(const DecodeConst& dc, const HeadTable& ht, const DecodeViews& dv, const float* xyz,
-                    const float* feat, const float* params, const asgs_gaussians& dg, int view, const DecWork& w,
+                    const float* feat, const float* params, const asgs_gaussians& dg, const DecWork& w,
                     float* d_xyz, float* d_feat, bool want_params, hipStream_t s) {
+  PlaneTable pt;
+  const int64_t n = dc.A * dc.k;
+  const float* field[kHeads] = {dg.opacity, dg.rgb, dg.scale, dg.rot, dg.feat};
+  const int64_t vstride[kHeads] = {dg.view_stride[3], dg.view_stride[4], dg.view_stride[1], dg.view_stride[2],
+                                   dg.view_stride[5]};
+  int p = 0;
+  for (int h = 0; h < kHeads; ++h)
+    for (int c = 0; c < ht.m[h]; ++c, ++p) {
+      pt.base[p] = field[h] + c * n;
+      pt.stride[p] = vstride[h];
+    }
+  for (; p < 32; ++p) {
+    pt.base[p] = params;
+    pt.stride[p] = 0;
+  }
   // second-layer row tiles per wave: the rotation head has ceil(4 k / 16),
   // each feature wave ceil(k / 4)
   if (dc.k <= 12)
-    launch_k<3>(dc, ht, dv, xyz, feat, params, dg, view, w, d_xyz, d_feat, want_params, s);
+    launch_k<3>(dc, ht, dv, xyz, feat, params, pt, w, d_xyz, d_feat, want_params, s);
   else
-    launch_k<4>(dc, ht, dv, xyz, feat, params, dg, view, w, d_xyz, d_feat, want_params, s);
+    launch_k<4>(dc, ht, dv, xyz, feat, params, pt, w, d_xyz, d_feat, want_params, s);
 }
 
 }  // namespace asgs

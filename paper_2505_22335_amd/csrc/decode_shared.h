@@ -112,7 +112,7 @@ void launch_dec_fwd(const DecodeConst& dc, const HeadTable& ht, const DecodeView
                     const float* feat, const float* off, const float* params, const asgs_gaussians& out,
                     hipStream_t s);
 void launch_dec_bwd(const DecodeConst& dc, const HeadTable& ht, const DecodeViews& dv, const float* xyz,
-                    const float* feat, const float* params, const asgs_gaussians& dg, int view, const DecWork& w,
+                    const float* feat, const float* params, const asgs_gaussians& dg, const DecWork& w,
                     float* d_xyz, float* d_feat, bool want_params, hipStream_t s);
 
 
