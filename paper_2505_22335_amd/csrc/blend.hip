@@ -663,8 +663,10 @@ __global__ void __launch_bounds__(kTilePix) __attribute__((amdgpu_waves_per_eu(5
   }
   float T = Tf;
   float sacc = 0.f;  // sum over later Gaussians of w_l (G . c_l)
-  if (front && inside && ehi == eend) {
-    // the record of a boundary the forward passed
+  if (front && inside && whi == eend) {
+    // the record of a boundary that the forward of this quarter passed: where
+    // it stopped before, in a longer segment's earlier round, it wrote none,
+    // and no pixel uses a later entry
     const float* rb = ctx_ptr<const float>(ctx, L.split) + (size_t)blockIdx.x * split_floats(CS) + (size_t)t * split_first(CS);
     T = rb[0];
 #pragma unroll

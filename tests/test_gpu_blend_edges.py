@@ -16,7 +16,7 @@ if torch.cuda.is_available():
     from paper_2505_22335_amd import _lib as L
 
 
-def _check(sc, cam, nf, label, max_frac):
+def _check(sc, cam, nf, label, max_frac, grads=("mean", "scale", "rot", "opacity", "rgb")):
     ref = oracle.render_scene(sc, cam, oracle_opts(nf), with_margins=True)
     keep, rep = guard_report(ref["margins"], tie_ulps=0)
     log("case", label, rep)
@@ -33,7 +33,7 @@ def _check(sc, cam, nf, label, max_frac):
     for k in ("rgb", "depth", "alpha") + (("feat",) if nf else ()):
         e = rel_err(to_np(out[k][0]), ref[k], keep)
         assert e <= IMG_TOL, (label, k, e)
-    for k in ("mean", "scale", "rot", "opacity", "rgb") + (("feat",) if nf else ()):
+    for k in grads + (("feat",) if nf else ()):
         e = rel_err(to_np(dg[k][0]), gr["gauss"][k])
         assert e <= GRAD_TOL, (label, k, e)
     e = rel_err(to_np(dpose[0]), gr["pose"])
@@ -110,3 +110,37 @@ def test_reach_box_holds_every_used_pixel(seed, mode):
     log("case reach box", seed, mode, "used", int(used.sum()), "outside", int((used & outside).sum()))
     assert used.sum() > 1000
     assert not np.any(used & outside)
+
+
+def _quarter_stops_scene(n, nf):
+    """n specks over one 16x16 tile; the upper left quarter is closed by opaque
+    ones 40 entries into the sixth of sixteen equal list segments."""
+    rng = np.random.default_rng(n + nf)
+    z = np.linspace(2.0, 4.0, n)
+    u, v = rng.uniform(-0.5, 15.5, n), rng.uniform(-0.5, 15.5, n)
+    sig, o = rng.uniform(1.0, 2.0, n), rng.uniform(0.006, 0.03, n)
+    seg = -(-(-(-n // 16)) // 32) * 32
+    a = 5 * seg + 40
+    k = np.arange(100)
+    u[a:a + 100], v[a:a + 100] = 2.0 + 3.0 * (k & 1), 2.0 + 3.0 * ((k >> 1) & 1)
+    sig[a:a + 100], o[a:a + 100] = 2.0, 0.9
+    f = 20.0
+    sc = synth.PlainScene(
+        mean=np.stack([(u - 7.5) * z / f, (v - 7.5) * z / f, z]).astype(np.float32),
+        scale=np.broadcast_to(sig * z / f, (3, n)).astype(np.float32),
+        rot=np.broadcast_to(np.array([1.0, 0.0, 0.0, 0.0])[:, None], (4, n)).astype(np.float32),
+        opacity=o.astype(np.float32), rgb=rng.uniform(0, 1, (3, n)).astype(np.float32),
+        feat=rng.normal(size=(nf, n)).astype(np.float32) if nf else None)
+    return sc, synth.Camera(16, 16, f, f, 7.5, 7.5, np.eye(3, 4, dtype=np.float32))
+
+
+@pytest.mark.parametrize("nf", [0, 16])
+@pytest.mark.parametrize("n", [4300, 6000, 8100])
+def test_quarter_stops_inside_a_long_segment(n, nf):
+    """List segments of more than one round of 256 entries (288, 384, 512), one
+    quarter of the tile closed in a segment's first round while the others go on
+    past its end: that quarter recorded no state at the segment's end, and the
+    walk of the segment starts from its pixels' final state there."""
+    sc, cam = _quarter_stops_scene(n, nf)
+    # the specks are round: no gradient reaches their rotation
+    _check(sc, cam, nf, "quarter stops n=%d nf=%d" % (n, nf), 0.15, ("mean", "scale", "opacity", "rgb"))
