@@ -105,13 +105,6 @@ ASGS_DEV T pick5(const T (&a)[kHeads], int i) {
   return v;
 }
 
-// The upstream gradient planes of the heads' components: plane p of view v is
-// n values from base[p] + v stride[p] (an absent plane: a stand-in, never used).
-struct PlaneTable {
-  const float* base[32];
-  int64_t stride[32];
-};
-
 template <int kR>
 __global__ void __launch_bounds__(kBT, 1) k_dec_bwd(DecodeConst dc, HeadTable ht, DecodeViews dv,
                                                     const float* __restrict__ xyz, const float* __restrict__ feat,
@@ -733,21 +726,7 @@ int64_t dec_bwd_blocks(int64_t n_anchors) {
 void launch_dec_bwd(const DecodeConst& dc, const HeadTable& ht, const DecodeViews& dv, const float* xyz,
                     const float* feat, const float* params, const asgs_gaussians& dg, const DecWork& w,
                     float* d_xyz, float* d_feat, bool want_params, hipStream_t s) {
-  PlaneTable pt;
-  const int64_t n = dc.A * dc.k;
-  const float* field[kHeads] = {dg.opacity, dg.rgb, dg.scale, dg.rot, dg.feat};
-  const int64_t vstride[kHeads] = {dg.view_stride[3], dg.view_stride[4], dg.view_stride[1], dg.view_stride[2],
-                                   dg.view_stride[5]};
-  int p = 0;
-  for (int h = 0; h < kHeads; ++h)
-    for (int c = 0; c < ht.m[h]; ++c, ++p) {
-      pt.base[p] = field[h] + c * n;
-      pt.stride[p] = vstride[h];
-    }
-  for (; p < 32; ++p) {
-    pt.base[p] = params;
-    pt.stride[p] = 0;
-  }
+  const PlaneTable pt = plane_table(dc, ht, dg);
   // second-layer row tiles per wave: the rotation head has ceil(4 k / 16),
   // each feature wave ceil(k / 4)
   if (dc.k <= 12)

@@ -25,7 +25,6 @@ typedef float f4v __attribute__((ext_vector_type(4)));
 constexpr int kBW = 8;         // waves per workgroup
 constexpr int kBT = 64 * kBW;  // threads per workgroup
 constexpr int kXL = 52;        // LDS row of an anchor's inputs (35 + distance column, pad)
-constexpr int kHB = 36;        // rows of the feature head's shared H (32 units + pad)
 constexpr int kWL = 36;        // LDS rows of the weights in the prologue (35 or 32 + pad)
 constexpr int kPlanes = 27;    // (head, component) planes: 1 + 3 + 3 + 4 + 16
 
@@ -33,8 +32,7 @@ constexpr int kPlanes = 27;    // (head, component) planes: 1 + 3 + 3 + 4 + 16
 // row tiles per wave, else 16). The prologue's weight copy (first-layer rows
 // of every head, second-layer rows, b1, b2) uses the output buffers' region.
 constexpr int kOffX = 0;
-constexpr int kOffHF = kOffX + 2 * 16 * kXL;
-constexpr int kOffTW = kOffHF + 16 * kHB;  // temporal weights of every unit: [5 * 32][2]
+constexpr int kOffTW = kOffX + 2 * 16 * kXL;  // temporal weights of every unit: [5 * 32][2]
 constexpr int kOffOB = kOffTW + kHeads * kHid * 2;
 template <int kR>
 struct FwdLds {
@@ -48,20 +46,14 @@ static_assert(FwdLds<3>::kFloats * 4 <= 80 * 1024, "two workgroups per compute u
 ASGS_DEV f4v mfma(float a, float b, f4v c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
 typedef __bf16 bf8v __attribute__((ext_vector_type(8)));
-typedef unsigned int u4v __attribute__((ext_vector_type(4)));
 
-// bfloat16 bits of a finite float, rounded to nearest even
-ASGS_DEV unsigned f2bf(float f) {
-  unsigned u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return u >> 16;
-}
-// eight floats as the bfloat16 operand of v_mfma_f32_16x16x32_bf16 (element j = K index 8 g + j)
+// eight floats as the bfloat16 operand of v_mfma_f32_16x16x32_bf16 (element j =
+// K index 8 g + j), rounded to nearest even
 ASGS_DEV bf8v pack_bf8(const float (&v)[8]) {
-  u4v p;
+  bf8v p;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) p[i] = f2bf(v[2 * i]) | (f2bf(v[2 * i + 1]) << 16);
-  return __builtin_bit_cast(bf8v, p);
+  for (int i = 0; i < 8; ++i) p[i] = (__bf16)v[i];
+  return p;
 }
 
 // kBf: the BF16 decoder (operands of the feature columns of the first layer
@@ -71,14 +63,13 @@ template <int kR, bool kBf>
 __global__ void __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(4, 4))) k_dec_fwd(DecodeConst dc, HeadTable ht, DecodeViews dv,
                                                     const float* __restrict__ xyz, const float* __restrict__ feat,
                                                     const float* __restrict__ off, const float* __restrict__ params,
-                                                    asgs_gaussians out) {
+                                                    PlaneTable pt, float* __restrict__ mean) {
   extern __shared__ __attribute__((aligned(16))) float smem[];
   const int t = threadIdx.x;
   const int lane = t & 63;
   const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
   const int fl = lane & 15, fg = lane >> 4;
   float (*const XB)[16][kXL] = reinterpret_cast<float (*)[16][kXL]>(smem + kOffX);
-  float (*const HF)[kHB] = reinterpret_cast<float (*)[kHB]>(smem + kOffHF);
   float* const OB = smem + kOffOB;
   float* const TW = smem + kOffTW;
   // BF16: the feature columns 8 g .. 8 g + 7 of anchor f as the B operand of Z^T
@@ -172,15 +163,9 @@ __global__ void __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(4, 4))
       }
       if (t < rw) B2L[r0 + t] = vb2[h];
     }
-    // input columns past 35 are never read by the first layer; keep them finite
-    for (int e = t; e < 2 * 16 * (kXL - 37); e += kBT) {
-      const int row = e / (kXL - 37);
-      XB[row >> 4][row & 15][37 + e - row * (kXL - 37)] = 0.f;
-    }
   }
   __syncthreads();
-  // first layer as the A operand of Z^T (unit 16 b + f, input 4 s + g); the
-  // feature waves 0 and 1 form one unit block each
+  // first layer as the A operand of Z^T (unit 16 b + f, input 4 s + g)
   float w1a[2][9], b1r[2][4];
   float w2y[kR][2][4], b2r[kR];
   // BF16: the feature columns as bfloat16 A operands (unit 16 b + f, inputs
@@ -195,10 +180,9 @@ __global__ void __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(4, 4))
   int ooff[kR];  // LDS output offset of the lane's row of row tile i (plus a k)
   bool rok[kR];
   {
-    const int ub = wv < 4 ? 0 : (q & 1) * 16;  // unit offset of block 0
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
-      const float* wrow = &W1L[(hd * kHid + ub + 16 * b + fl) * kWL];
+      const float* wrow = &W1L[(hd * kHid + 16 * b + fl) * kWL];
       if constexpr (kBf) {
         float v8[8];
 #pragma unroll
@@ -209,12 +193,12 @@ __global__ void __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(4, 4))
 #pragma unroll
         for (int s = 0; s < 9; ++s) w1a[b][s] = wrow[4 * s + fg];
       }
-      const f4v v = *reinterpret_cast<const f4v*>(&B1L[hd * kHid + (ub + 16 * b + 4 * fg) % kHid]);
+      const f4v v = *reinterpret_cast<const f4v*>(&B1L[hd * kHid + 16 * b + 4 * fg]);
 #pragma unroll
       for (int r = 0; r < 4; ++r) b1r[b][r] = v[r];
     }
   }
-  const int tw0 = (hd * kHid + (wv < 4 ? 0 : (q & 1) * 16) + 4 * fg) * 2;  // the lane's first temporal pair
+  const int tw0 = (hd * kHid + 4 * fg) * 2;  // the lane's first temporal pair
 #pragma unroll
   for (int i = 0; i < kR; ++i) {
     const int o = 16 * (t0 + i) + fl;
@@ -243,7 +227,16 @@ __global__ void __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(4, 4))
   // LDS; the means of the tile's Gaussians fetched with the first view ----
   const int ngrid = (A + 15) / 16;
   float xv = 0.f, pv[3] = {0.f, 0.f, 0.f}, mx[2] = {0.f, 0.f}, mo[2] = {0.f, 0.f};
-  // item j of this workgroup: tile blockIdx.x + (j / V) gridDim.x, view j % V
+  // elements t and t + 512 of the tile's 3 x 16 k means (component-major):
+  // component, Gaussian and anchor of the tile
+  int mcm[2], mgl[2], man[2];
+#pragma unroll
+  for (int c2 = 0; c2 < 2; ++c2) {
+    const int e = t + c2 * kBT;
+    mcm[c2] = e >= 3 * run ? 3 : e >= 2 * run ? 2 : e >= run ? 1 : 0;
+    mgl[c2] = e - mcm[c2] * run;
+    man[c2] = mgl[c2] / k;
+  }
   auto fetch = [&](int tile, int view) {
     const int a0 = tile * 16, a = t >> 5, c = t & 31;
     const int ax = a0 + a < A ? a0 + a : 0, ap = a0 + (t & 15) < A ? a0 + (t & 15) : 0;
@@ -251,31 +244,27 @@ __global__ void __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(4, 4))
 #pragma unroll
     for (int cc = 0; cc < 3; ++cc) pv[cc] = xyz[(int64_t)cc * A + ap];
     if (view == 0) {
-      // means: elements t and t + 512 of the tile's 3 x 16 k values (component-major)
 #pragma unroll
       for (int c2 = 0; c2 < 2; ++c2) {
-        const int e = t + c2 * kBT;
-        const int cm = e / run, gl = e - cm * run;
-        const int g = a0 * k + gl;
-        const bool okm = cm < 3 && g < n;
-        mo[c2] = off[okm ? (int64_t)cm * n + g : 0];
-        mx[c2] = xyz[okm ? (int64_t)cm * A + g / k : 0];
+        const int g = a0 * k + mgl[c2];
+        const bool okm = mcm[c2] < 3 && g < n;
+        mo[c2] = off[okm ? (int64_t)mcm[c2] * n + g : 0];
+        mx[c2] = xyz[okm ? (int64_t)mcm[c2] * A + a0 + man[c2] : 0];
       }
     }
   };
   auto put_x = [&](int buf, int tile, int view) {
     const int a0 = tile * 16;
     XB[buf][t >> 5][t & 31] = a0 + (t >> 5) < A ? xv : 0.f;
-    if (t < 16) {
-      float D[3] = {0.f, 0.f, 0.f}, dist = 1.f;
-      if (a0 + t < A) {
-        for (int c = 0; c < 3; ++c) D[c] = pv[c] - dv.c[view][c];
-        dist = sqrtf(D[0] * D[0] + D[1] * D[1] + D[2] * D[2]);
-        for (int c = 0; c < 3; ++c) D[c] /= dist;
-      }
-      for (int c = 0; c < 3; ++c) XB[buf][t][32 + c] = D[c];
-      XB[buf][t][35] = nx > 0 && a0 + t < A ? dist : 0.f;  // distance input (weight column 35)
-      XB[buf][t][36] = 0.f;
+    if (wv == 0) {
+      // lane 16 c + a: component c of anchor a's direction; lanes 48 + a: its distance
+      const bool ok = a0 + fl < A;
+      float D[3];
+      for (int c = 0; c < 3; ++c) D[c] = pv[c] - dv.c[view][c];
+      const float dist = ok ? sqrtf(D[0] * D[0] + D[1] * D[1] + D[2] * D[2]) : 1.f;
+      const float dc_ = fg == 0 ? D[0] : fg == 1 ? D[1] : D[2];
+      const float del = ok ? dc_ / dist : 0.f;
+      XB[buf][fl][32 + fg] = fg < 3 ? del : nx > 0 && ok ? dist : 0.f;  // column 35: the distance input
     }
   };
   const int ntile_wg = (int)blockIdx.x < ngrid ? (ngrid - 1 - (int)blockIdx.x) / (int)gridDim.x + 1 : 0;
@@ -285,12 +274,13 @@ __global__ void __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(4, 4))
     put_x(0, blockIdx.x, 0);
   }
   __syncthreads();
+  // item j: tile blockIdx.x + (j / V) gridDim.x, view j % V
+  int tile = blockIdx.x, view = 0;
   for (int j = 0; j < nitems; ++j) {
-    const int tile = blockIdx.x + (j / V) * gridDim.x, view = j % V;
     const int a0 = tile * 16;
     const int buf = j & 1;
     const bool more = j + 1 < nitems;
-    const int tile_n = blockIdx.x + ((j + 1) / V) * gridDim.x, view_n = (j + 1) % V;
+    const int view_n = view + 1 < V ? view + 1 : 0, tile_n = view_n ? tile : tile + (int)gridDim.x;
     // the means of this tile (first view), held until the outputs are written
     const float mx0 = mx[0], mo0 = mo[0], mx1 = mx[1], mo1 = mo[1];
     if (more) fetch(tile_n, view_n);
@@ -303,12 +293,12 @@ __global__ void __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(4, 4))
       for (int r = 0; r < 4; ++r) {
         bv[b][r] = b1r[b][r];
         if (nx == 3) {
-          const int e = (tw0 + (16 * b + r) * 2) % (kHeads * kHid * 2);
+          const int e = tw0 + (16 * b + r) * 2;
           bv[b][r] += TW[e] * lt0 + TW[e + 1] * lt1;
         }
       }
     f4v h[2];
-    if (wv < 4) {
+    {
       // Z^T (units x anchors) = W1 X^T, K = inputs
       f4v z0 = {0.f, 0.f, 0.f, 0.f}, z1 = z0;
       if constexpr (kBf) {
@@ -324,29 +314,19 @@ __global__ void __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(4, 4))
           z1 = mfma(w1a[1][s], xb, z1);
         }
       }
+      if (hd == 4) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        h[0][r] = fmaxf(z0[r] + bv[0][r], 0.f);
-        h[1][r] = fmaxf(z1[r] + bv[1][r], 0.f);
-      }
-    } else if (has_feat && q < 2) {
-      // the feature head's hidden layer once: unit block q on feature wave q
-      f4v z = {0.f, 0.f, 0.f, 0.f};
-      if constexpr (kBf) {
-        z = mfma(w1x[0], XB[buf][fl][32 + fg], __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1b[0], xbf(buf), z, 0, 0, 0));
+        for (int r = 0; r < 4; ++r) {
+          h[0][r] = fsoftplus(z0[r] + bv[0][r]);
+          h[1][r] = fsoftplus(z1[r] + bv[1][r]);
+        }
       } else {
 #pragma unroll
-        for (int s = 0; s < 9; ++s) z = mfma(w1a[0][s], XB[buf][fl][4 * s + fg], z);
+        for (int r = 0; r < 4; ++r) {
+          h[0][r] = fmaxf(z0[r] + bv[0][r], 0.f);
+          h[1][r] = fmaxf(z1[r] + bv[1][r], 0.f);
+        }
       }
-      f4v hq;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) hq[r] = fsoftplus(z[r] + bv[0][r]);
-      *reinterpret_cast<f4v*>(&HF[fl][16 * q + 4 * fg]) = hq;
-    }
-    __syncthreads();  // the feature head's H is complete; the last item's outputs are written
-    if (wv >= 4 && has_feat) {
-#pragma unroll
-      for (int b = 0; b < 2; ++b) h[b] = *reinterpret_cast<const f4v*>(&HF[fl][16 * b + 4 * fg]);
     }
     float* const ob = OB + buf * kOB;
     bf8v hb;  // BF16: H as the A operand of the second layer
@@ -370,9 +350,21 @@ __global__ void __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(4, 4))
 #pragma unroll
             for (int r = 0; r < 4; ++r) y = mfma(h[b][r], w2y[i][b][r], y);
         }
+        float o4[4];
+        if (hd < 3) {
+          // sigmoid (scaled by l_s for the scale head); rotation and feature are raw
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const float s = fsigm(y[r] + b2r[i]);
+            o4[r] = hd == 2 ? dc.l_s * s : s;
+          }
+        } else {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) o4[r] = y[r] + b2r[i];
+        }
         if (rok[i]) {
 #pragma unroll
-          for (int r = 0; r < 4; ++r) ob[ooff[i] + (4 * fg + r) * k] = fout_act(hd, y[r] + b2r[i], dc.l_s);
+          for (int r = 0; r < 4; ++r) ob[ooff[i] + (4 * fg + r) * k] = o4[r];
         }
       }
     }
@@ -381,27 +373,27 @@ __global__ void __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(4, 4))
     // ---- the tile's contiguous runs of every plane: wave w takes planes
     // w, w + 8, w + 16, w + 24 ----
     const int g0 = a0 * k;
+    const int left = n - g0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int p = wv + 8 * i;
       if (p >= nplanes) break;
-      const int ph = p < 1 ? 0 : p < 4 ? 1 : p < 7 ? 2 : p < 11 ? 3 : 4;
-      const int pc = p - (ph == 0 ? 0 : ph == 1 ? 1 : ph == 2 ? 4 : ph == 3 ? 7 : 11);
-      float* const dst = out_plane(out, view, ph, pc, n) + g0;
+      char* const dst = reinterpret_cast<char*>(pt.base[p] + view * pt.stride[p] + g0);
 #pragma unroll
       for (int c = 0; c < kR; ++c) {
         const int idx = lane + 64 * c;
-        if (idx < run && g0 + idx < n) dst[idx] = ob[p * gstride + idx];
+        if (idx < min(run, left)) *reinterpret_cast<float*>(dst + 4u * (uint32_t)idx) = ob[p * gstride + idx];
       }
     }
     if (view == 0) {
 #pragma unroll
       for (int c2 = 0; c2 < 2; ++c2) {
-        const int e = t + c2 * kBT;
-        const int cm = e / run, gl = e - cm * run;
-        if (cm < 3 && g0 + gl < n) out.mean[(int64_t)cm * n + g0 + gl] = c2 ? mx1 + dc.l_o * mo1 : mx0 + dc.l_o * mo0;
+        if (mcm[c2] < 3 && g0 + mgl[c2] < n)
+          mean[(int64_t)mcm[c2] * n + g0 + mgl[c2]] = c2 ? mx1 + dc.l_o * mo1 : mx0 + dc.l_o * mo0;
       }
     }
+    tile = tile_n;
+    view = view_n;
   }
 }
 
@@ -418,7 +410,7 @@ void launch_k(const DecodeConst& dc, const HeadTable& ht, const DecodeViews& dv,
   const int64_t tiles = (dc.A + 15) / 16;
   const unsigned nblk = (unsigned)(tiles < 512 ? tiles : 512);
   hipLaunchKernelGGL((k_dec_fwd<kR, kBf>), dim3(nblk), dim3(kBT), FwdLds<kR>::kFloats * sizeof(float), s, dc, ht, dv, xyz,
-                     feat, off, params, out);
+                     feat, off, params, plane_table(dc, ht, out), out.mean);
 }
 
 }  // namespace

@@ -102,6 +102,27 @@ struct DecWork {
 };
 
 
+// The planes of the heads' components, in head order (opacity, rgb, scale,
+// rot, feat): plane p of view v is n values from base[p] + v stride[p].
+struct PlaneTable {
+  float* base[32];
+  int64_t stride[32];
+};
+inline PlaneTable plane_table(const DecodeConst& dc, const HeadTable& ht, const asgs_gaussians& g) {
+  PlaneTable pt = {};
+  const int64_t n = dc.A * dc.k;
+  float* const field[kHeads] = {g.opacity, g.rgb, g.scale, g.rot, g.feat};
+  const int64_t vstride[kHeads] = {g.view_stride[3], g.view_stride[4], g.view_stride[1], g.view_stride[2],
+                                   g.view_stride[5]};
+  int p = 0;
+  for (int h = 0; h < kHeads; ++h)
+    for (int c = 0; c < ht.m[h]; ++c, ++p) {
+      pt.base[p] = field[h] + c * n;
+      pt.stride[p] = vstride[h];
+    }
+  return pt;
+}
+
 // Workgroup partials of the parameter gradients are stored chunk-major: for
 // every run of 64 parameters, the 64-float segments of all workgroups are
 // contiguous, so the reduction of one run reads one contiguous region.
