@@ -26,25 +26,32 @@ namespace asgs {
 
 namespace {
 
-// Mean gradients summed over views: d_off = l_o dmu, d_xyz += sum_i dmu
-// (element e of the 3 A anchor coordinates).
-ASGS_DEV void dec_bwd_mean(const DecodeConst& dc, const asgs_gaussians& dg, float* d_xyz, float* d_off,
-                           int64_t e) {
-  const int64_t A = dc.A;
-  const int k = dc.k;
-  const int64_t n = A * k;
-  if (e >= A * 3) return;
-  const int c = (int)(e / A);
-  const int64_t a = e - c * A;
-  float sx = 0.f;
-  for (int i = 0; i < k; ++i) {
-    const int64_t gn = a * k + i;
-    float s = 0.f;
-    for (int view = 0; view < dc.n_views; ++view) s += dg.mean[view * dg.view_stride[0] + c * n + gn];
+// Mean gradients summed over views: d_off = l_o dmu, d_xyz += sum_i dmu. One
+// workgroup per component and 256 / k whole anchors, a Gaussian per thread (so
+// that the planes are read and written as runs); the anchors' sums over their
+// k Gaussians, in order, through LDS.
+ASGS_DEV void dec_bwd_mean(const DecodeConst& dc, const asgs_gaussians& dg, float* d_xyz, float* d_off, int blk,
+                           float* sh) {
+  const int64_t A = dc.A, n = A * dc.k;
+  const int k = dc.k, t = threadIdx.x, per = 256 / k;
+  const int nb = (int)((A + per - 1) / per);
+  const int c = blk / nb;
+  const int64_t a0 = (int64_t)(blk - c * nb) * per;
+  const int64_t gn = a0 * k + t;
+  float s = 0.f;
+  if (t < per * k && gn < n) {
+    const float* src = dg.mean + c * n + gn;
+#pragma unroll 8
+    for (int view = 0; view < dc.n_views; ++view) s += src[view * dg.view_stride[0]];
     d_off[c * n + gn] = dc.l_o * s;
-    sx += s;
   }
-  d_xyz[c * A + a] += sx;
+  sh[t] = s;
+  __syncthreads();
+  if (t < per && a0 + t < A) {
+    float sx = 0.f;
+    for (int i = 0; i < k; ++i) sx += sh[t * k + i];
+    d_xyz[c * A + a0 + t] += sx;
+  }
 }
 
 // Fixed-order reduction of the workgroup partials: 64 parameters per
@@ -55,12 +62,12 @@ ASGS_DEV void dec_bwd_mean(const DecodeConst& dc, const asgs_gaussians& dg, floa
 __global__ void __launch_bounds__(256) k_decode_reduce(DecodeConst dc, DecodeViews dv, DecWork w, float* d_params,
                                                        float* d_pose, int mean_first, asgs_gaussians dg,
                                                        float* d_xyz, float* d_off) {
-  if ((int)blockIdx.x >= mean_first) {
-    dec_bwd_mean(dc, dg, d_xyz, d_off, (int64_t)(blockIdx.x - mean_first) * blockDim.x + threadIdx.x);
-    return;
-  }
   // without d_params only the camera-centre term is reduced (one block)
   __shared__ float red[4][64];
+  if ((int)blockIdx.x >= mean_first) {
+    dec_bwd_mean(dc, dg, d_xyz, d_off, (int)blockIdx.x - mean_first, &red[0][0]);
+    return;
+  }
   const int t = threadIdx.x;
   const int pl = t & 63, q = t >> 6;
   const int64_t p = (int64_t)blockIdx.x * 64 + pl;
@@ -205,7 +212,8 @@ void launch_decode_backward(const DecodeConst& dc, const float* xyz, const float
   w.nblk_w = (int32_t)z.nblk_w;
   launch_dec_bwd(dc, ht, dv, xyz, feat, params, dg, w, d_xyz, d_feat, d_params != nullptr, s);
   const unsigned nrb = d_params ? (unsigned)((dc.n_params + 63) / 64) + 1 : 1u;
-  const unsigned nmean = d_xyz ? (unsigned)((dc.A * 3 + 255) / 256) : 0u;
+  const int per = 256 / dc.k;  // anchors of a mean workgroup
+  const unsigned nmean = d_xyz ? 3u * (unsigned)((dc.A + per - 1) / per) : 0u;
   hipLaunchKernelGGL(k_decode_reduce, dim3(nrb + nmean), dim3(256), 0, s, dc, dv, w, d_params, d_pose, (int)nrb, dg,
                      d_xyz, d_off);
 }
