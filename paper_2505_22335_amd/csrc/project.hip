@@ -306,9 +306,24 @@ __global__ void __launch_bounds__(256) k_project(RenderConst rc, asgs_gaussians 
 // world mean, plus the pose partials dL/drho = dL/dt, dL/dphi = t x dL/dt +
 // the rotation term of W = R_cw.
 // ---------------------------------------------------------------------------
+// D += the sums of a slot's dL/dpower times (dx, dy, dx^2, dx dy, dy^2), the
+// pixels' distances from the centre (u, v), from its moments M about the centre
+// of tile (tx, ty).
+ASGS_DEV void moments_about(float u, float v, int tx, int ty, const float* M, double (&D)[5]) {
+  const double uu = (double)u - (double)((float)(tx * kTile) + kTileMid);
+  const double vv = (double)v - (double)((float)(ty * kTile) + kTileMid);
+  const double Sdx = uu * M[0] - M[1];
+  const double Sdy = vv * M[0] - M[2];
+  D[0] += Sdx;
+  D[1] += Sdy;
+  D[2] += uu * Sdx - (uu * M[1] - M[3]);
+  D[3] += vv * Sdx - (uu * M[2] - M[4]);
+  D[4] += vv * Sdy - (vv * M[2] - M[5]);
+}
+
 template <int NF>
 __global__ void __launch_bounds__(256) k_project_backward(RenderConst rc, asgs_gaussians g,
-                                                          asgs_gaussians dg, float* d_pose,
+                                                          asgs_gaussians dg,
                                                           const ViewDev* __restrict__ views,
                                                           char* ctx, CtxLayout L) {
   constexpr int CS = 4 + NF;
@@ -332,36 +347,66 @@ __global__ void __launch_bounds__(256) k_project_backward(RenderConst rc, asgs_g
     dop[e] = 0.f;
     for (int k = 0; k < NF; ++k) dft[k * n + e] = 0.f;
   }
-  // and the e-th visible Gaussian of the view (index order) the full chain,
-  // so that the waves on this path carry no invisible lanes
+  // and the visible Gaussians of the view (index order) the full chain, so that
+  // the waves on this path carry no invisible lanes. A workgroup takes eight
+  // runs of 32 of them, a run of every other workgroup between two of its own:
+  // neighbours in index are neighbours in space, and those close to the camera
+  // cover many tiles each.
   const int64_t nvis = ovf ? 0 : (int64_t)ctx_ptr<const uint32_t>(ctx, L.vcount)[view];
-  if (e < nvis) {
-    const ViewDev& V = views[view];
-    const int64_t gid = (int64_t)ctx_ptr<const uint32_t>(ctx, L.vlist)[(int64_t)view * n + e];
-    const int64_t i = gid - (int64_t)view * n;
-    // visible pairs own ntiles consecutive gradient slots from toff
-    const uint32_t cnt = ctx_ptr<const uint32_t>(ctx, L.ntiles)[gid];
-    {
-      const uint32_t start = ctx_ptr<const uint32_t>(ctx, L.toff)[gid];
-      const float* slot = ctx_ptr<const float>(ctx, L.gslot);
-      const short4 r = ctx_ptr<const short4>(ctx, L.rect)[gid];
-      const float4 g0 = ctx_ptr<const float4>(ctx, L.geom)[2 * gid];
-      const float4 g1 = ctx_ptr<const float4>(ctx, L.geom)[2 * gid + 1];
-      // D: sums of dL/dpower times (dx, dy, dx^2, dx dy, dy^2), the distances
-      // from the centre; G: its sum (5), then the channels. A
-      // slot holds the moments of dL/dpower over the pixel coordinates about its
-      // tile's centre, (1, lx, ly, lx^2, lx ly, ly^2), and the channel sums. The
-      // second moments about the centre and the step to the 2D covariance
-      // are differences of nearly equal terms for thin Gaussians: FP64.
-      float G[GS];
+  const int t = threadIdx.x;
+  const int64_t nblk = (nvis + 255) >> 8;
+  const int64_t ev = (int64_t)blockIdx.x < nblk ? ((int64_t)(t >> 5) * nblk + blockIdx.x) * 32 + (t & 31) : nvis;
+  // Sums over the Gaussian's slots. D: dL/dpower times (dx, dy, dx^2, dx dy,
+  // dy^2), the distances from its centre; G: dL/dpower (5), then the channels.
+  // A slot holds the moments of dL/dpower over the pixel coordinates about its
+  // tile's centre, (1, lx, ly, lx^2, lx ly, ly^2), and the channel sums. The
+  // second moments about the centre and the step to the 2D covariance are
+  // differences of nearly equal terms for thin Gaussians: FP64.
+  constexpr int GSP = (GS + 3) & ~3;  // slot stride (whole float4)
+  double D[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+  float G[GS];
 #pragma unroll
-      for (int k = 0; k < GS; ++k) G[k] = 0.f;
-      double D[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-      constexpr int GSP = (GS + 3) & ~3;  // slot stride (whole float4)
-      const uint64_t end = min((uint64_t)start + cnt, (uint64_t)rc.cap);
+  for (int k = 0; k < GS; ++k) G[k] = 0.f;
+  const float* slot = ctx_ptr<const float>(ctx, L.gslot);
+  // A Gaussian over up to kFewSlots tiles is summed by its thread; one over
+  // more by a whole wave, four lanes per slot and sixteen slots at a time, so
+  // that no thread walks a long list alone. A room's volume (up to 130 tiles a
+  // Gaussian): 68 us with each Gaussian its thread's and 256 neighbours to a
+  // workgroup, 52 with whole waves from 33 slots on, 43 with the runs of 32
+  // spread as well, 39 from 17 on, 40 from 9 on (where 50k slots of 9.5k
+  // Gaussians go from 16 to 30 us).
+  constexpr uint32_t kFewSlots = 16;
+  __shared__ double SD[5][256];
+  __shared__ float SG[GS - 5][256];
+  struct Queued {
+    uint32_t start, num;
+    short4 rect;
+    float u, v;
+    int thread;
+  };
+  __shared__ Queued queue[256];
+  __shared__ int nqueue;
+  if (t == 0) nqueue = 0;
+  __syncthreads();
+  int64_t gid = 0;
+  uint32_t num = 0u;
+  float4 g0 = make_float4(0.f, 0.f, 0.f, 0.f), g1 = g0;
+  if (ev < nvis) {
+    gid = (int64_t)ctx_ptr<const uint32_t>(ctx, L.vlist)[(int64_t)view * n + ev];
+    // a visible Gaussian owns ntiles consecutive slots from toff
+    const uint32_t start = ctx_ptr<const uint32_t>(ctx, L.toff)[gid];
+    const uint32_t cnt = ctx_ptr<const uint32_t>(ctx, L.ntiles)[gid];
+    num = (uint32_t)(min((uint64_t)start + cnt, (uint64_t)rc.cap) - min((uint64_t)start, (uint64_t)rc.cap));
+    const short4 r = ctx_ptr<const short4>(ctx, L.rect)[gid];
+    g0 = ctx_ptr<const float4>(ctx, L.geom)[2 * gid];
+    g1 = ctx_ptr<const float4>(ctx, L.geom)[2 * gid + 1];
+    if (num > kFewSlots) {
+      // in any order: every entry is summed on its own
+      queue[atomicAdd(&nqueue, 1)] = Queued{start, num, r, g0.x, g0.y, t};
+    } else {
       int cx = r.x, cy = r.z;
-      for (uint64_t p = start; p < end; ++p) {
-        const float4* sp = reinterpret_cast<const float4*>(slot + p * GSP);
+      const float4* sp = reinterpret_cast<const float4*>(slot + (size_t)start * GSP);
+      for (uint32_t q = 0; q < num; ++q, sp += GSP / 4) {
         float M[GSP];
 #pragma unroll
         for (int k4 = 0; k4 < GSP / 4; ++k4) {
@@ -371,16 +416,7 @@ __global__ void __launch_bounds__(256) k_project_backward(RenderConst rc, asgs_g
           M[4 * k4 + 2] = v.z;
           M[4 * k4 + 3] = v.w;
         }
-        // the Gaussian's centre from the tile's
-        const double uu = (double)g0.x - (double)((float)(cx * kTile) + kTileMid);
-        const double vv = (double)g0.y - (double)((float)(cy * kTile) + kTileMid);
-        const double Sdx = uu * M[0] - M[1];
-        const double Sdy = vv * M[0] - M[2];
-        D[0] += Sdx;
-        D[1] += Sdy;
-        D[2] += uu * Sdx - (uu * M[1] - M[3]);
-        D[3] += vv * Sdx - (uu * M[2] - M[4]);
-        D[4] += vv * Sdy - (vv * M[2] - M[5]);
+        moments_about(g0.x, g0.y, cx, cy, M, D);
         G[5] += M[0];
 #pragma unroll
         for (int k = 6; k < GS; ++k) G[k] += M[k];
@@ -389,6 +425,59 @@ __global__ void __launch_bounds__(256) k_project_backward(RenderConst rc, asgs_g
           ++cy;
         }
       }
+    }
+  }
+  __syncthreads();
+  for (int qi = t >> 6; qi < nqueue; qi += 256 / 64) {
+    const Queued qe = queue[qi];
+    const uint32_t nq = qe.num;
+    const short4 r = qe.rect;
+    const int tt = qe.thread;
+    const uint32_t w = (uint32_t)(r.y - r.x + 1);
+    const int f = t & 3;  // floats 8 f .. 8 f + 7 of a slot
+    double Dq[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    float S[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) S[k] = 0.f;
+    for (uint32_t q = (t & 63) >> 2; q < nq; q += 16) {
+      const float* p = slot + (size_t)(qe.start + q) * GSP + 8 * f;
+      const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+      const float4 a = 8 * f < GSP ? *reinterpret_cast<const float4*>(p) : z;
+      const float4 b = 8 * f + 4 < GSP ? *reinterpret_cast<const float4*>(p + 4) : z;
+      const float M[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+      if (f == 0) moments_about(qe.u, qe.v, r.x + (int)(q % w), r.z + (int)(q / w), M, Dq);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) S[k] += M[k];
+    }
+#pragma unroll
+    for (int o = 4; o < 64; o <<= 1) {
+#pragma unroll
+      for (int k = 0; k < 5; ++k) Dq[k] += __shfl_xor(Dq[k], o);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) S[k] += __shfl_xor(S[k], o);
+    }
+    if ((t & 63) < 4) {
+      if (f == 0) {
+#pragma unroll
+        for (int k = 0; k < 5; ++k) SD[k][tt] = Dq[k];
+        SG[0][tt] = S[0];
+      }
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        if (8 * f + k >= 6 && 8 * f + k < GS) SG[8 * f + k - 5][tt] = S[k];
+    }
+  }
+  __syncthreads();
+  if (ev < nvis) {
+    const ViewDev& V = views[view];
+    const int64_t i = gid - (int64_t)view * n;
+    if (num > kFewSlots) {
+#pragma unroll
+      for (int k = 0; k < 5; ++k) D[k] = SD[k][t];
+#pragma unroll
+      for (int k = 5; k < GS; ++k) G[k] = SG[k - 5][t];
+    }
+    {
       const float du = (float)-(g0.z * D[0] + g0.w * D[1]), dv = (float)-(g0.w * D[0] + g1.x * D[1]);
       const double dA = -0.5 * D[2], dB = -D[3], dC = -0.5 * D[4];
       dop[i] = G[5] / g1.y;
@@ -519,30 +608,29 @@ __global__ void __launch_bounds__(256) k_project_backward(RenderConst rc, asgs_g
   }
 }
 
-// Fixed-order sum of the per-block pose partials of each view: every thread
+// Fixed-order sum of the per-block pose partials, a workgroup per view: every thread
 // adds the six partials of its blocks, then six wave and workgroup sums.
-__global__ void __launch_bounds__(256) k_pose_reduce(int n_views, int nbx, const float* __restrict__ part,
+__global__ void __launch_bounds__(256) k_pose_reduce(int nbx, const float* __restrict__ part,
                                                      float* d_pose) {
   __shared__ float fin[6][256 / 64];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  for (int vv = 0; vv < n_views; ++vv) {
-    float acc[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int bx = threadIdx.x; bx < nbx; bx += blockDim.x) {
-      const float* p = part + ((int64_t)vv * nbx + bx) * 6;
+  const int vv = blockIdx.x;
+  float acc[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+  for (int bx = threadIdx.x; bx < nbx; bx += blockDim.x) {
+    const float* p = part + ((int64_t)vv * nbx + bx) * 6;
 #pragma unroll
-      for (int k = 0; k < 6; ++k) acc[k] += p[k];
-    }
+    for (int k = 0; k < 6; ++k) acc[k] += p[k];
+  }
 #pragma unroll
-    for (int k = 0; k < 6; ++k) {
-      for (int off = 32; off > 0; off >>= 1) acc[k] += __shfl_xor(acc[k], off);
-      if (lane == 0) fin[k][wv] = acc[k];
-    }
-    __syncthreads();
-    if (threadIdx.x < 6) {
-      const int k = threadIdx.x;
-      d_pose[vv * 6 + k] = (fin[k][0] + fin[k][1]) + (fin[k][2] + fin[k][3]);
-    }
-    __syncthreads();
+  for (int k = 0; k < 6; ++k) {
+    for (int off = 32; off > 0; off >>= 1) acc[k] += __shfl_xor(acc[k], off);
+    if (lane == 0) fin[k][wv] = acc[k];
+  }
+  __syncthreads();
+  if (threadIdx.x < 6) {
+    const int k = threadIdx.x;
+    d_pose[vv * 6 + k] = (fin[k][0] + fin[k][1]) + (fin[k][2] + fin[k][3]);
   }
 }
 
@@ -577,11 +665,11 @@ void launch_project_backward(const RenderConst& rc, const asgs_gaussians& g, con
   dim3 grid((unsigned)((rc.n + 255) / 256), (unsigned)rc.n_views);
   const ViewDev* views = reinterpret_cast<const ViewDev*>(ctx + L.views);
   if (rc.nf == 16)
-    hipLaunchKernelGGL(k_project_backward<16>, grid, dim3(256), 0, s, rc, g, dg, d_pose, views, ctx, L);
+    hipLaunchKernelGGL(k_project_backward<16>, grid, dim3(256), 0, s, rc, g, dg, views, ctx, L);
   else
-    hipLaunchKernelGGL(k_project_backward<0>, grid, dim3(256), 0, s, rc, g, dg, d_pose, views, ctx, L);
+    hipLaunchKernelGGL(k_project_backward<0>, grid, dim3(256), 0, s, rc, g, dg, views, ctx, L);
   if (d_pose)
-    hipLaunchKernelGGL(k_pose_reduce, dim3(1), dim3(256), 0, s, rc.n_views, (int)grid.x,
+    hipLaunchKernelGGL(k_pose_reduce, dim3((unsigned)rc.n_views), dim3(256), 0, s, (int)grid.x,
                        reinterpret_cast<const float*>(ctx + L.posepart), d_pose);
 }
 

@@ -144,3 +144,32 @@ def test_quarter_stops_inside_a_long_segment(n, nf):
     sc, cam = _quarter_stops_scene(n, nf)
     # the specks are round: no gradient reaches their rotation
     _check(sc, cam, nf, "quarter stops n=%d nf=%d" % (n, nf), 0.15, ("mean", "scale", "opacity", "rgb"))
+
+
+@pytest.mark.parametrize("nf", [0, 16])
+@pytest.mark.parametrize("n", [3, 33, 300])
+def test_gradients_over_many_tiles(n, nf):
+    """Strips over up to 18 x 2 tiles of a 288x24 image, between specks: the
+    projection's backward sums up to 16 tiles in the Gaussian's thread and more
+    in a wave."""
+    rng = np.random.default_rng(n + nf)
+    z = rng.uniform(2.0, 4.0, n)
+    f = 100.0
+    u, v = rng.uniform(110.0, 178.0, n), rng.uniform(2.0, 22.0, n)
+    wide = np.arange(n) % 3 != 2
+    sx, sy = np.where(wide, rng.uniform(35.0, 60.0, n), 1.5), rng.uniform(0.8, 2.5, n)
+    q = np.stack([np.ones(n), 0.01 * rng.normal(size=n), 0.01 * rng.normal(size=n), 0.01 * rng.normal(size=n)])
+    sc = synth.PlainScene(
+        mean=np.stack([(u - 143.5) * z / f, (v - 11.5) * z / f, z]).astype(np.float32),
+        scale=np.stack([sx * z / f, sy * z / f, sy * z / f]).astype(np.float32), rot=q.astype(np.float32),
+        opacity=rng.uniform(0.05, 0.6, n).astype(np.float32), rgb=rng.uniform(0, 1, (3, n)).astype(np.float32),
+        feat=rng.normal(size=(nf, n)).astype(np.float32) if nf else None)
+    cam = synth.Camera(288, 24, f, f, 143.5, 11.5, np.eye(3, 4, dtype=np.float32))
+    rc = P.RenderContext([cam], n, n_feat=nf)
+    g = P.gaussians_to_device(sc.arrays())
+    rc.fit(g)
+    rc.forward(g)
+    tiles = rc.array(L.CTX_NTILES, torch.int32).cpu().numpy()
+    log("case many tiles", n, nf, "largest", int(tiles.max()), "16:", int((tiles == 16).sum()), "17:", int((tiles == 17).sum()))
+    assert tiles.max() > 16 and (n < 300 or ((tiles == 16).any() and (tiles == 17).any()))
+    _check(sc, cam, nf, "many tiles n=%d nf=%d" % (n, nf), 0.15)
