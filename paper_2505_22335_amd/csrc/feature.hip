@@ -56,11 +56,21 @@ ASGS_DEV void bf_split(float v, uint16_t& hi, uint16_t& lo) {
   hi = bf_rne(v);
   lo = bf_rne(v - bf_val(hi));
 }
-ASGS_DEV bf8v as_bf8(const uint16_t* u) {
-  bf8v r;
+// eight values as high and low bfloat16 operands
+ASGS_DEV void split8(const float (&v)[8], bf8v& hi, bf8v& lo) {
+  typedef float f2v __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf2v __attribute__((ext_vector_type(2)));
 #pragma unroll
-  for (int i = 0; i < 8; ++i) r[i] = __builtin_bit_cast(__bf16, u[i]);
-  return r;
+  for (int j = 0; j < 8; j += 2) {
+    const bf2v h = __builtin_convertvector((f2v{v[j], v[j + 1]}), bf2v);
+    const uint32_t u = __builtin_bit_cast(uint32_t, h);
+    const bf2v l = __builtin_convertvector(
+        (f2v{v[j] - __uint_as_float(u << 16), v[j + 1] - __uint_as_float(u & 0xffff0000u)}), bf2v);
+    hi[j] = h[0];
+    hi[j + 1] = h[1];
+    lo[j] = l[0];
+    lo[j + 1] = l[1];
+  }
 }
 // sum over the four lanes of one pixel column (lanes l, l^16, l^32, l^48);
 // every lane of the column gets the same bits
@@ -113,17 +123,6 @@ ASGS_DEV TileCells tile_cells(const FeatArgs& a, int tx, int ty) {
   return t;
 }
 
-// Everything one lane knows about its pixel after the forward.
-struct LanePix {
-  bool valid;
-  int64_t p;           // pixel index in the view
-  float h[32];         // hidden units 32 g + u of the lane's group g
-  float cw[4];         // corner weights
-  int cs[4];           // corner slots in the tile's patch table
-  float q, a, nF, den, cos;
-  bool floored;
-};
-
 // Staged per workgroup: M fragments, first-layer weights, m, the tile's patches.
 struct FeatShared {
   uint16_t frag[kFrag];
@@ -132,7 +131,7 @@ struct FeatShared {
   float w1[8 * 64 * 4];
   float b1[kFHid];         // at hpos(k)
   float m[kFHid];          // at hpos(k)
-  float cell[kSlots][kCell];
+  __attribute__((aligned(16))) float cell[kSlots][kCell];
 };
 
 ASGS_DEV void stage_weights(const FeatArgs& a, FeatShared& S) {
@@ -150,15 +149,28 @@ ASGS_DEV void stage_weights(const FeatArgs& a, FeatShared& S) {
   }
 }
 
-ASGS_DEV void stage_cells(const FeatArgs& a, FeatShared& S, int view, const TileCells& tc) {
-  const int n = tc.ncy * tc.ncx;
-  const float* base = a.cells + (int64_t)view * a.Hp * a.Wp * kCell;
-  for (int q = threadIdx.x; q < n * kCell; q += blockDim.x) {
-    const int sl = q / kCell, e = q - sl * kCell;
-    const int cy = tc.cy0 + sl / tc.ncx, cx = tc.cx0 + sl % tc.ncx;
-    S.cell[sl][e] = base[((int64_t)cy * a.Wp + cx) * kCell + e];
+// A tile's patches on their way to LDS through the registers of NW waves, a
+// patch per wave and step: requested, then put.
+template <int NW>
+struct CellStage {
+  static constexpr int kN = kSlots / NW;
+  static_assert(kCell % 4 == 0 && kCell / 4 <= 64, "a float4 per lane");
+  float4 v[kN];
+  ASGS_DEV void request(const FeatArgs& a, int view, const TileCells& tc, int wv) {
+    const float4* base = reinterpret_cast<const float4*>(a.cells) + (int64_t)view * a.Hp * a.Wp * (kCell / 4);
+    const int lane = min((int)(threadIdx.x & 63), kCell / 4 - 1);
+#pragma unroll
+    for (int i = 0; i < kN; ++i) {
+      const int sl = min(wv + i * NW, tc.ncy * tc.ncx - 1), y = sl / tc.ncx;
+      v[i] = base[((int64_t)(tc.cy0 + y) * a.Wp + tc.cx0 + sl - y * tc.ncx) * (kCell / 4) + lane];
+    }
   }
-}
+  ASGS_DEV void put(FeatShared& S, int wv) const {
+#pragma unroll
+    for (int i = 0; i < kN; ++i)
+      if ((threadIdx.x & 63) < kCell / 4) reinterpret_cast<float4*>(S.cell[wv + i * NW])[threadIdx.x & 63] = v[i];
+  }
+};
 
 // G_c . G_c' of two patches of the tile (at most one row and one column
 // apart): the record of the upper-left patch of the pair holds it (self,
@@ -177,57 +189,90 @@ ASGS_DEV float patch_dot(const FeatShared& S, const TileCells& tc, int ya, int x
 // of the pixel. h[4 b + r] = relu(z) holds unit 32 g + 4 b + r.
 ASGS_DEV void first_layer(const float* w1, const float* b1g, const float (&xq)[4], int lane, float (&h)[32]) {
   const f4v* wl = reinterpret_cast<const f4v*>(w1) + lane;
-  f4v z[8];
+  f4v w[8], z[8];
 #pragma unroll
-  for (int b = 0; b < 8; ++b)
+  for (int b = 0; b < 8; ++b) {
+    w[b] = wl[64 * b];
 #pragma unroll
     for (int r = 0; r < 4; ++r) z[b][r] = b1g[4 * (4 * b + r)];
+  }
 #pragma unroll
   for (int st = 0; st < 4; ++st)
 #pragma unroll
-    for (int b = 0; b < 8; ++b) z[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(wl[64 * b][st], xq[st], z[b], 0, 0, 0);
+    for (int b = 0; b < 8; ++b) z[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[b][st], xq[st], z[b], 0, 0, 0);
 #pragma unroll
   for (int b = 0; b < 8; ++b)
 #pragma unroll
     for (int r = 0; r < 4; ++r) h[4 * b + r] = fmaxf(z[b][r], 0.f);
 }
 
-// Forward of one pixel per lane (column n = lane & 15, group g = lane >> 4):
-// first layer and M h on the matrix cores, the scalars of the cosine summed
-// over the four lanes of the pixel.
-ASGS_DEV void lane_forward(const FeatArgs& a, const FeatShared& S, const TileCells& tc, int view, int px, int py,
-                           LanePix& L) {
-  const int lane = threadIdx.x & 63, g = lane >> 4;
-  L.valid = px < a.W && py < a.H;
-  const int cpx = min(px, a.W - 1), cpy = min(py, a.H - 1);
-  const int64_t HW = (int64_t)a.W * a.H;
-  L.p = (int64_t)cpy * a.W + cpx;
-  const float* fx = a.feat + (int64_t)view * kFIn * HW + (int64_t)g * HW + L.p;
-  float xq[4];
+// Bilinear corners of a pixel (clamped into the image): patch coordinates,
+// weights, and slots in the tile's patch table.
+struct Corners {
+  int ys[4], xs[4], slot[4];
+  float wx, wy, w[4];
+};
+ASGS_DEV Corners corners(const FeatArgs& a, const TileCells& tc, int px, int py) {
+  int y0, y1, x0, x1;
+  Corners c;
+  bilin(py, a.Hp, a.sy, y0, y1, c.wy);
+  bilin(px, a.Wp, a.sx, x0, x1, c.wx);
+  const float wx = c.wx, wy = c.wy;
+  c.ys[0] = c.ys[1] = y0;
+  c.ys[2] = c.ys[3] = y1;
+  c.xs[0] = c.xs[2] = x0;
+  c.xs[1] = c.xs[3] = x1;
+  c.w[0] = (1.f - wy) * (1.f - wx);
+  c.w[1] = (1.f - wy) * wx;
+  c.w[2] = wy * (1.f - wx);
+  c.w[3] = wy * wx;
 #pragma unroll
-  for (int st = 0; st < 4; ++st) xq[st] = L.valid ? fx[4 * st * HW] : 0.f;
+  for (int k = 0; k < 4; ++k) c.slot[k] = (c.ys[k] - tc.cy0) * tc.ncx + (c.xs[k] - tc.cx0);
+  return c;
+}
+
+// beta of the pixel and |F|^2
+ASGS_DEV void pixel_scalars(const FeatShared& S, const TileCells& tc, const Corners& c, float& beta, float& nF) {
+  beta = nF = 0.f;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    beta = fmaf(c.w[k], S.cell[c.slot[k]][128], beta);
+    nF = fmaf(c.w[k] * c.w[k], patch_dot(S, tc, c.ys[k], c.xs[k], c.ys[k], c.xs[k]), nF);
+#pragma unroll
+    for (int e = k + 1; e < 4; ++e)
+      nF = fmaf(2.f * c.w[k] * c.w[e], patch_dot(S, tc, c.ys[k], c.xs[k], c.ys[e], c.xs[e]), nF);
+  }
+}
+
+// The sum v is formed here: neither are the reads of the steps before left
+// waiting for their use, nor those of the steps after started.
+ASGS_DEV void step_end(float& v) { asm volatile("" : "+v"(v)::"memory"); }
+
+// A row of 16 pixels per wave (column n = lane & 15; group g = lane >> 4 holds
+// units 32 g .. 32 g + 31): h = relu(W1 x + b1) of the lane's units, split into
+// the B operands of M h (units 32 g + 8 kb .. + 7 to put(kb, high, low)); mh =
+// M h + m there if kMh; returns the lane's part of h^T (M h + 2 m).
+template <bool kMh, class Put>
+ASGS_DEV float hidden(const FeatShared& S, const float (&xq)[4], float (&h)[32], float (&mh)[32], Put put) {
+  const int lane = threadIdx.x & 63, g = lane >> 4;
   // unit 32 g + u sits at hpos = 4 u + g: per-lane bases with constant offsets
-  const float* const b1g = S.b1 + g;
-  const float* const mg = S.m + g;
-  first_layer(S.w1, b1g, xq, lane, L.h);
-  // hidden units 32 g + u, u = 8 kb + i: B operands of M h (K = hidden)
+  first_layer(S.w1, S.b1 + g, xq, lane, h);
   bf8v bh[4], bl[4];
 #pragma unroll
   for (int kb = 0; kb < 4; ++kb) {
-    uint16_t hi[8], lo[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) bf_split(L.h[8 * kb + i], hi[i], lo[i]);
-    bh[kb] = as_bf8(hi);
-    bl[kb] = as_bf8(lo);
+    split8(reinterpret_cast<const float (&)[8]>(h[8 * kb]), bh[kb], bl[kb]);
+    put(kb, bh[kb], bl[kb]);
   }
-  __builtin_amdgcn_sched_barrier(0);
-  // M h: row block mb holds units 32 g' + 4 mb + j for lane group g', used
-  // at once for h^T (M h + 2 m)
+  // row block mb holds units 32 g' + 4 mb + j for lane group g'
   const uint16_t* fr = S.frag + lane * 8;
-  float qp = 0.f, ap = 0.f;
+  const float* const mg = S.m + g;
+  float qp = 0.f;
 #pragma unroll
   for (int mb = 0; mb < 8; ++mb) {
-    f4v d = {0.f, 0.f, 0.f, 0.f};
+    f4v m4;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) m4[j] = mg[4 * (4 * mb + j)];
+    f4v d = m4;
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb) {
       const bf8v ah = *reinterpret_cast<const bf8v*>(fr + ((mb * 4 + kb) * 2 + 0) * 512);
@@ -239,53 +284,33 @@ ASGS_DEV void lane_forward(const FeatArgs& a, const FeatShared& S, const TileCel
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int u = 4 * mb + j;
-      qp = fmaf(L.h[u], d[j] + 2.f * mg[4 * u], qp);
+      if (kMh) mh[u] = d[j];
+      qp = fmaf(h[u], d[j] + m4[j], qp);
     }
-    // keep the fragment loads of one row block together (hoisting all 64 of
-    // them would take every register)
-    __builtin_amdgcn_sched_barrier(0);
+    step_end(qp);  // one row block's fragments at a time (all 64 would take every register)
   }
-  // bilinear corners of the pixel in the tile's patch table
-  int y0, y1, x0, x1;
-  float wy, wx;
-  bilin(cpy, a.Hp, a.sy, y0, y1, wy);
-  bilin(cpx, a.Wp, a.sx, x0, x1, wx);
-  const int ys[4] = {y0, y0, y1, y1}, xs[4] = {x0, x1, x0, x1};
-  L.cw[0] = (1.f - wy) * (1.f - wx);
-  L.cw[1] = (1.f - wy) * wx;
-  L.cw[2] = wy * (1.f - wx);
-  L.cw[3] = wy * wx;
+  return qp;
+}
+
+// sum_c w_c Q_c at the lane's units (kept if kCs); returns the lane's part of its
+// product with h.
+template <bool kCs>
+ASGS_DEV float patch_product(const FeatShared& S, const Corners& c, const float (&h)[32], float (&cs)[32]) {
+  const int g = (threadIdx.x & 63) >> 4;
+  const float* cb[4];
 #pragma unroll
-  for (int c = 0; c < 4; ++c) L.cs[c] = (ys[c] - tc.cy0) * tc.ncx + (xs[c] - tc.cx0);
-  {
-    const float* cb[4];
+  for (int k = 0; k < 4; ++k) cb[k] = &S.cell[c.slot[k]][32 * g];
+  float ap = 0.f;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) cb[c] = &S.cell[L.cs[c]][32 * g];
+  for (int u = 0; u < 32; ++u) {
+    float v = 0.f;
 #pragma unroll
-    for (int u = 0; u < 32; ++u) {
-      float cs = 0.f;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) cs = fmaf(L.cw[c], cb[c][u], cs);
-      ap = fmaf(cs, L.h[u], ap);
-      if ((u & 3) == 3) __builtin_amdgcn_sched_barrier(0);  // four units' corner reads at a time
-    }
+    for (int k = 0; k < 4; ++k) v = fmaf(c.w[k], cb[k][u], v);
+    if (kCs) cs[u] = v;
+    ap = fmaf(v, h[u], ap);
+    if ((u & 3) == 3) step_end(ap);  // four units' corner reads at a time
   }
-  L.q = fmaxf(col_sum(qp) + a.mvec[kFHid], 0.f);
-  float beta = 0.f, nF = 0.f;
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    beta = fmaf(L.cw[c], S.cell[L.cs[c]][128], beta);
-    nF = fmaf(L.cw[c] * L.cw[c], patch_dot(S, tc, ys[c], xs[c], ys[c], xs[c]), nF);
-#pragma unroll
-    for (int e = c + 1; e < 4; ++e)
-      nF = fmaf(2.f * L.cw[c] * L.cw[e], patch_dot(S, tc, ys[c], xs[c], ys[e], xs[e]), nF);
-  }
-  L.a = col_sum(ap) + beta;
-  L.nF = fmaxf(nF, 0.f);
-  const float den = sqrtf(L.nF) * sqrtf(L.q);
-  L.floored = !(den >= 1e-12f);
-  L.den = L.floored ? 1e-12f : den;
-  L.cos = L.a / L.den;
+  return ap;
 }
 
 // ---------------------------------------------------------------------------
@@ -440,32 +465,61 @@ __global__ void __launch_bounds__(512) k_feat_cells(FeatArgs a, float* cells) {
 }
 
 // ---------------------------------------------------------------------------
-// Forward: persistent workgroups of kFwdWaves waves over 16x16 pixel tiles;
-// each wave takes one row of 16 pixels per round.
+// Forward: persistent workgroups of sixteen waves over 16x16 pixel tiles, a row
+// of 16 pixels per wave, one workgroup per CU (the LDS copy of M).
+//
+// The vector instructions (56 % of the time) and the matrix products (42 %) of a
+// SIMD follow one another here, also with half of its waves half a row ahead
+// (60.3 us against 60.8). 640x480, 384 channels: 60.8 us; with eight waves of
+// two rows in turn (232 registers, two waves per SIMD) 69.8; with eight waves
+// that take two rows at once and read M half as often 66 to 72.
 // ---------------------------------------------------------------------------
-constexpr int kFwdWaves = 8;
+constexpr int kFwdWaves = kFT;
 
 __global__ void __launch_bounds__(64 * kFwdWaves) k_feat_fwd(FeatArgs a) {
   __shared__ __attribute__((aligned(16))) FeatShared S;
   __shared__ float tl[kFwdWaves];
   stage_weights(a, S);
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, g = lane >> 4, n = lane & 15;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 4, n = lane & 15;
   const int total = a.tiles * a.V;
+  const int64_t HW = (int64_t)a.W * a.H;
+  // the row's features 4 s + g, requested a tile ahead (clamped into the image;
+  // what lies outside is not used)
+  float xn[4];
+  auto fetch = [&](int t) {
+    const int view = t / a.tiles, lt = t - view * a.tiles;
+    const int ty = lt / a.tiles_x, tx = lt - ty * a.tiles_x;
+    const int y = min(ty * kFT + wv, a.H - 1);
+    const float* fx = a.feat + (int64_t)view * kFIn * HW + (int64_t)y * a.W + g * HW + min(tx * kFT + n, a.W - 1);
+#pragma unroll
+    for (int st = 0; st < 4; ++st) xn[st] = fx[4 * st * HW];
+  };
+  fetch(blockIdx.x);
   for (int t = blockIdx.x; t < total; t += gridDim.x) {
     const int view = t / a.tiles, lt = t - view * a.tiles;
     const int ty = lt / a.tiles_x, tx = lt - ty * a.tiles_x;
     const TileCells tc = tile_cells(a, tx, ty);
+    CellStage<kFwdWaves> cells;
+    cells.request(a, view, tc, wv);
     __syncthreads();  // the previous tile's patches are no longer read
-    stage_cells(a, S, view, tc);
+    cells.put(S, wv);
     __syncthreads();
+    const int px = tx * kFT + n, py = ty * kFT + wv;
+    const float xq[4] = {xn[0], xn[1], xn[2], xn[3]};
+    if (t + (int)gridDim.x < total) fetch(t + gridDim.x);
+    float h[32], unused[32];
+    const float qp = hidden<false>(S, xq, h, unused, [](int, const bf8v&, const bf8v&) {});
+    const Corners c = corners(a, tc, min(px, a.W - 1), min(py, a.H - 1));
+    const float ap = patch_product<false>(S, c, h, unused);
+    float beta, nF;
+    pixel_scalars(S, tc, c, beta, nF);
+    const float q = fmaxf(col_sum(qp) + a.mvec[kFHid], 0.f);
+    const float den = sqrtf(fmaxf(nF, 0.f)) * sqrtf(q);
+    const float cosv = (col_sum(ap) + beta) / (den >= 1e-12f ? den : 1e-12f);
     float acc = 0.f;
-    for (int row = wv; row < kFT; row += kFwdWaves) {
-      LanePix L;
-      lane_forward(a, S, tc, view, tx * kFT + n, ty * kFT + row, L);
-      if (L.valid && g == 0) {
-        a.cosine[(int64_t)view * a.W * a.H + L.p] = L.cos;
-        acc += 1.f - L.cos;
-      }
+    if (px < a.W && py < a.H && g == 0) {
+      a.cosine[((int64_t)view * a.H + py) * a.W + px] = cosv;
+      acc = 1.f - cosv;
     }
     for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
     if (lane == 0) tl[wv] = acc;
@@ -492,299 +546,317 @@ __global__ void __launch_bounds__(256) k_feat_loss(FeatArgs a, float* loss) {
 
 // ---------------------------------------------------------------------------
 // Backward: persistent workgroups (kBwdWG, a fixed number so that every sum
-// keeps its order on any device) of 4 waves over the tiles; a round is 4
-// rows of 16 pixels (64 pixels, one row per wave).
+// keeps its order on any device) of eight waves over the tiles, two rows of 16
+// pixels per wave and tile.
 // ---------------------------------------------------------------------------
-constexpr int kBwdWaves = 4;
-constexpr int kRP = 64;  // pixels per round
-
-// [128 units][64 pixels] bfloat16 with the 8-pixel chunks of row k at chunk ^ (k & 7)
-ASGS_DEV int rp_index(int k, int pxl) { return k * kRP + ((((pxl >> 3) ^ (k & 7)) << 3) | (pxl & 7)); }
+constexpr int kBwdWaves = 8;
+constexpr int kBwdRows = kFT / kBwdWaves;
 
 struct BwdShared {
   FeatShared F;
-  uint16_t Hhi[kFHid * kRP], Hlo[kFHid * kRP];    // h
-  uint16_t Ghi[kFHid * kRP], Glo[kFHid * kRP];    // dL/dz
-  float X[kFIn][kRP];                             // x
-  float Wc[kSlots][kRP];                          // g s1 w_c at each pixel's corner slots
+  bf8v dx[2][4][64];  // A operands of dL/dx = W1^T dL/dz, high and low: K block, lane (g, n): W1[32 g + 8 kb + i][n]
+  // per wave, high and low: [16 pixels][128 units] bfloat16, the 8-unit chunks
+  // of pixel p at chunk ^ table_swz(p); between the tiles 16 x 128 sums of each wave
+  uint16_t T[kBwdWaves][2][kFT * kFHid];
+  float al[kBwdWaves][kFT];  // g s1 of the wave's pixels; between the tiles dbeta per slot
 };
 
-// A or B fragment of a [128][64] bf16 table: row k, pixels 32 kb + 8 (lane / 16) .. + 7
-ASGS_DEV bf8v tab_frag(const uint16_t* T, int k, int kb, int lane) {
-  const int p0 = 32 * kb + 8 * (lane >> 4);
-  return *reinterpret_cast<const bf8v*>(T + rp_index(k, p0));
-}
-// A fragment of a [rows][64] fp32 table (row r, the same pixels), split on the fly
-ASGS_DEV void f32_frag(const float (*T)[kRP], int r, int kb, int lane, bf8v& hi, bf8v& lo) {
-  const int p0 = 32 * kb + 8 * (lane >> 4);
-  uint16_t h[8], l[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) bf_split(T[r][p0 + i], h[i], l[i]);
-  hi = as_bf8(h);
-  lo = as_bf8(l);
-}
+typedef short s4v __attribute__((ext_vector_type(4)));
 
-// Backward, first pass (per round of 64 pixels): the forward again, dL/dz and
-// dL/dx (written), dq per pixel (for the second pass), and on the matrix
-// cores dQ += (g s1 w_c)^T h per patch slot, dW1^T += x^T dL/dz and
-// db1 += 1^T dL/dz (a row of ones).
+// Swizzle of pixel p's chunks: sixteen different values, so that sixteen pixels'
+// writes of one chunk fall in different banks, and pairs apart for four
+// consecutive pixels, so that the transposing reads of a chunk pair do too.
+ASGS_DEV int table_swz(int p) { return ((p & 7) << 1) | (p >> 3); }
+
+// First pass: the forward again, dL/dz and dL/dx (written), dq per pixel (for
+// the second pass), and on the matrix cores dQ += (g s1 w_c)^T h per patch
+// slot, dW1^T += x^T dL/dz; db1 += 1^T dL/dz.
+//
+// A wave has one pixel per lane column with 32 units per lane, as the products
+// over units (M h, dL/dx) take and give them. The products over pixels need
+// one unit per lane: a row's h and later its dL/dz go through 8 KB of LDS of
+// the wave's own, in by pixel, out by unit with the transposing read
+// (ds_read_b64_tr_b16: lane (g, n) gets pixels 4 g .. 4 g + 3 of unit n), so
+// that the waves only meet at the ends of a tile. The K = 32 of such a product
+// is 16 pixels' high and low parts: (high | high) . (high | low), then
+// (low | 0) . (high | low).
+//
+// Latency bounds it: LDS holds one workgroup, two waves per SIMD, that wait 57 %
+// of their time for it. 640x480, 384 channels, 256 workgroups of 4 or 5 tiles:
+// 121 us (22 a tile, 8 before the first). Four waves that met twice per four
+// rows, with h and dL/dz of 64 pixels in two tables for the whole workgroup,
+// read by unit without transposing (one wave per SIMD): 189.
 __global__ void __launch_bounds__(64 * kBwdWaves) k_feat_bwd(FeatArgs a) {
   __shared__ __attribute__((aligned(16))) BwdShared S;
   stage_weights(a, S.F);
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, g = lane >> 4, n = lane & 15;
-  // dW1^T and db1 column blocks 2 wv, 2 wv + 1; dQ column blocks wv, wv + 4 (and 8 = dbeta on wave 0)
-  f4v accW[2], accB[2], accQ[3];
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 4, n = lane & 15;
+  if (wv < 4) {
+    float w[8];
 #pragma unroll
-  for (int i = 0; i < 2; ++i) accW[i] = accB[i] = f4v{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < 8; ++i) w[i] = a.params[(32 * g + 8 * wv + i) * kFIn + n];
+    bf8v hi, lo;
+    split8(w, hi, lo);
+    S.dx[0][wv][lane] = hi;
+    S.dx[1][wv][lane] = lo;
+  }
   const int total = a.tiles * a.V;
   const int64_t HW = (int64_t)a.W * a.H;
-  // A operand of the row of ones (row 0 of the block, exact in bfloat16)
-  bf8v ones;
+  f4v accW[8];   // dW1^T: channels 4 g + j, unit 16 b + n
+  float db[8];   // db1: unit 16 b + n over the pixels 4 g .. 4 g + 3
+#pragma unroll
+  for (int b = 0; b < 8; ++b) {
+    accW[b] = f4v{0.f, 0.f, 0.f, 0.f};
+    db[b] = 0.f;
+  }
+  auto wave_sync = [&]() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  // Byte offsets in the wave's table (the low parts follow the high ones).
+  // Writing, units 32 g + 8 kb .. + 7 of pixel n: chunk 4 g + kb. Reading,
+  // units 16 b + 4 (n % 4) .. + 3 of pixel 4 g + n / 4: chunk 2 b + n % 4 / 2.
+  // kb and 2 b are bits of their own in the chunk, hence in the offset.
+  char* const T = reinterpret_cast<char*>(S.T[wv]);
+  constexpr int kTLo = kFT * kFHid * 2;
+  const int rp = 4 * g + (n >> 2);
+  int tw0 = n * kFHid * 2 + (((4 * g) ^ table_swz(n)) << 4);
+  int tr0 = rp * kFHid * 2 + ((((n >> 1) & 1) ^ table_swz(rp)) << 4) + 8 * (n & 1);
+  auto put = [&](int kb, const bf8v& hi, const bf8v& lo) {
+    bf8v* at = reinterpret_cast<bf8v*>(T + (tw0 ^ (kb << 4)));
+    at[0] = hi;
+    at[kTLo / 16] = lo;
+  };
+  // pixels 4 g .. 4 g + 3 of unit 16 b + n, high parts then low parts
+  auto column = [&](int b) {
+    typedef __attribute__((address_space(3))) s4v lds_s4v;
+    lds_s4v* at = (lds_s4v*)(T + (tr0 ^ (b << 5)));
+    const s4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(at);
+    const s4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(at + kTLo / 8);
+    typedef short s8v __attribute__((ext_vector_type(8)));
+    return __builtin_bit_cast(bf8v, (s8v)__builtin_shufflevector(hi, lo, 0, 1, 2, 3, 4, 5, 6, 7));
+  };
+  // four values as the operands (high | high) and (low | 0)
+  auto pair4 = [&](const float (&v)[4], bf8v& hh, bf8v& l0) {
+    const float w[8] = {v[0], v[1], v[2], v[3], 0.f, 0.f, 0.f, 0.f};
+    bf8v hi;
+    split8(w, hi, l0);
+    hh = __builtin_shufflevector(hi, hi, 0, 1, 2, 3, 0, 1, 2, 3);
+  };
+  // A row's features 4 s + g, requested one row ahead (clamped into the image;
+  // what lies outside is zeroed where it is used).
+  float xn[4];
+  auto fetch = [&](int t, int r) {
+    int gl = g, nl = n;
+    asm volatile("" : "+s"(t), "+v"(gl), "+v"(nl));  // addresses are formed here, not held in registers
+    const int view = t / a.tiles, lt = t - view * a.tiles;
+    const int ty = lt / a.tiles_x, tx = lt - ty * a.tiles_x;
+    const int y = min(ty * kFT + wv + kBwdWaves * r, a.H - 1);
+    const float* fx = a.feat + (int64_t)view * kFIn * HW + (int64_t)y * a.W + gl * HW + min(tx * kFT + nl, a.W - 1);
+#pragma unroll
+    for (int st = 0; st < 4; ++st) xn[st] = fx[4 * st * HW];
+  };
+  int t = blockIdx.x;
   {
-    uint16_t o[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) o[e] = n == 0 ? bf_rne(1.f) : (uint16_t)0;
-    ones = as_bf8(o);
+    const int lt = t % a.tiles;
+    CellStage<kBwdWaves> cells;
+    cells.request(a, t / a.tiles, tile_cells(a, lt % a.tiles_x, lt / a.tiles_x), wv);
+    fetch(t, 0);
+    cells.put(S.F, wv);
   }
-  // A operands of dL/dx = W1^T dL/dz: lane (g, n) supplies W1[32 g + 8 kb + i][n]
-  bf8v dxh[4], dxl[4];
-#pragma unroll
-  for (int kb = 0; kb < 4; ++kb) {
-    uint16_t wh[8], wl[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) bf_split(a.params[(32 * g + 8 * kb + i) * kFIn + n], wh[i], wl[i]);
-    dxh[kb] = as_bf8(wh);
-    dxl[kb] = as_bf8(wl);
-  }
-  for (int t = blockIdx.x; t < total; t += gridDim.x) {
+  __syncthreads();
+  for (; t < total; t += gridDim.x) {
     const int view = t / a.tiles, lt = t - view * a.tiles;
     const int ty = lt / a.tiles_x, tx = lt - ty * a.tiles_x;
     const TileCells tc = tile_cells(a, tx, ty);
+    f4v accQ[8];       // dQ: slots 4 g + j, unit 16 b + n
+    float dbeta = 0.f;  // slot n over the pixels 4 g .. 4 g + 3
 #pragma unroll
-    for (int i = 0; i < 3; ++i) accQ[i] = f4v{0.f, 0.f, 0.f, 0.f};
-    __syncthreads();
-    stage_cells(a, S.F, view, tc);
-    for (int round = 0; round < kFT / kBwdWaves; ++round) {
-      __syncthreads();  // patches staged; the previous round's tables are no longer read
-      const int row = round * kBwdWaves + wv;
-      // The forward of the lane's pixel and its 32 hidden units again (as in
-      // lane_forward), then dL/dz; M h + m is kept at the lane's units for
-      // dL/dh (after the cosine's scalars are known).
-      const int px = tx * kFT + n, py = ty * kFT + row;
+    for (int b = 0; b < 8; ++b) accQ[b] = f4v{0.f, 0.f, 0.f, 0.f};
+    // weight of patch column n % ncx at the pixels 4 g + i
+    const int sy = n / tc.ncx, sx = n - sy * tc.ncx;
+    float wxs[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      int x0, x1;
+      float wx;
+      bilin(min(tx * kFT + 4 * g + i, a.W - 1), a.Wp, a.sx, x0, x1, wx);
+      wxs[i] = (sx == x0 - tc.cx0 ? 1.f - wx : 0.f) + (sx == x1 - tc.cx0 ? wx : 0.f);
+    }
+#pragma unroll 1
+    for (int r = 0; r < kBwdRows; ++r) {
+      // (lane coordinates of the row's own, so that what follows from them is
+      // not held in registers over the rows)
+      int gl = g, nl = n;
+      asm volatile("" : "+v"(tw0), "+v"(tr0), "+v"(gl), "+v"(nl));
+      const int px = tx * kFT + nl, py = ty * kFT + wv + kBwdWaves * r;
       const bool valid = px < a.W && py < a.H;
       const int cpx = min(px, a.W - 1), cpy = min(py, a.H - 1);
-      const int64_t p = (int64_t)cpy * a.W + cpx;
-      const int pr = wv * 16 + n;  // pixel of the round
-      // unit 32 g + u sits at hpos = 4 u + g: per-lane bases with constant offsets
-      const float* const b1g = S.F.b1 + g;
-      const float* const mg = S.F.m + g;
-      float h[32];
-      bf8v bh[4], bl[4];
+      const float gpn = a.dcos[((int64_t)view * a.H + cpy) * a.W + cpx];
+      float xq[4], h[32], mh[32];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) xq[i] = valid ? xn[i] : 0.f;
+      const int r2 = r + 1 < kBwdRows ? r + 1 : 0, t2 = r2 ? t : t + (int)gridDim.x;
+      if (t2 < total) fetch(t2, r2);
+      const float qp = hidden<true>(S.F, xq, h, mh, put);
+      // feature n of the pixels 4 g + i, for dW1
+      float xtn[4];
       {
-        float xq[4];
-        const float* fx = a.feat + (int64_t)view * kFIn * HW + (int64_t)g * HW + p;
+        const float* ft = a.feat + (int64_t)view * kFIn * HW + (int64_t)cpy * a.W + nl * HW;
 #pragma unroll
-        for (int st = 0; st < 4; ++st) xq[st] = valid ? fx[4 * st * HW] : 0.f;
-#pragma unroll
-        for (int st = 0; st < 4; ++st) S.X[4 * st + g][pr] = xq[st];
-        first_layer(S.F.w1, b1g, xq, lane, h);
-#pragma unroll
-        for (int kb = 0; kb < 4; ++kb) {
-          uint16_t hi[8], lo[8];
-#pragma unroll
-          for (int i = 0; i < 8; ++i) {
-            const int u = 8 * kb + i, k = 32 * g + u;
-            bf_split(h[u], hi[i], lo[i]);
-            S.Hhi[rp_index(k, pr)] = hi[i];
-            S.Hlo[rp_index(k, pr)] = lo[i];
-            if (i & 1) __builtin_amdgcn_sched_barrier(0);
-          }
-          bh[kb] = as_bf8(hi);
-          bl[kb] = as_bf8(lo);
-        }
+        for (int i = 0; i < 4; ++i) xtn[i] = ft[min(tx * kFT + 4 * gl + i, a.W - 1)];
       }
-      __builtin_amdgcn_sched_barrier(0);
-      // bilinear corners of the pixel in the tile's patch table
-      LanePix L;  // corners only
-      int ys[4], xs[4];
-      {
-        int y0, y1, x0, x1;
-        float wy, wx;
-        bilin(cpy, a.Hp, a.sy, y0, y1, wy);
-        bilin(cpx, a.Wp, a.sx, x0, x1, wx);
-        ys[0] = ys[1] = y0;
-        ys[2] = ys[3] = y1;
-        xs[0] = xs[2] = x0;
-        xs[1] = xs[3] = x1;
-        L.cw[0] = (1.f - wy) * (1.f - wx);
-        L.cw[1] = (1.f - wy) * wx;
-        L.cw[2] = wy * (1.f - wx);
-        L.cw[3] = wy * wx;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) L.cs[c] = (ys[c] - tc.cy0) * tc.ncx + (xs[c] - tc.cx0);
-      }
-      const uint16_t* fr = S.F.frag + lane * 8;
-      // row block mb of M h: units 32 g + 4 mb + j of the lane's pixel
-      auto mh_block = [&](int mb) {
-        f4v d = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int kb = 0; kb < 4; ++kb) {
-          const bf8v ah = *reinterpret_cast<const bf8v*>(fr + ((mb * 4 + kb) * 2 + 0) * 512);
-          const bf8v alo = *reinterpret_cast<const bf8v*>(fr + ((mb * 4 + kb) * 2 + 1) * 512);
-          d = mfma_bf(ah, bh[kb], d);
-          d = mfma_bf(ah, bl[kb], d);
-          d = mfma_bf(alo, bh[kb], d);
-        }
-        return d;
-      };
-      float qp = 0.f, ap = 0.f;
-      float mh[32];  // (M h + m) at the lane's units
-#pragma unroll
-      for (int mb = 0; mb < 8; ++mb) {
-        const f4v d = mh_block(mb);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int u = 4 * mb + j;
-          mh[u] = d[j] + mg[4 * u];
-          qp = fmaf(h[u], mh[u] + mg[4 * u], qp);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      const float* cb[4];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) cb[c] = &S.F.cell[L.cs[c]][32 * g];
-      auto csum = [&](int u) {
-        float r = 0.f;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) r = fmaf(L.cw[c], cb[c][u], r);
-        return r;
-      };
-#pragma unroll
-      for (int u = 0; u < 32; ++u) {
-        ap = fmaf(csum(u), h[u], ap);
-        if ((u & 3) == 3) __builtin_amdgcn_sched_barrier(0);  // four units' corner reads at a time
-      }
+      // the pixel's patch vector at the lane's units
+      const Corners c = corners(a, tc, cpx, cpy);
+      float cs[32];
+      const float ap = patch_product<true>(S.F, c, h, cs);
       const float q = fmaxf(col_sum(qp) + a.mvec[kFHid], 0.f);
-      float beta = 0.f, nF = 0.f;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        beta = fmaf(L.cw[c], S.F.cell[L.cs[c]][128], beta);
-        nF = fmaf(L.cw[c] * L.cw[c], patch_dot(S.F, tc, ys[c], xs[c], ys[c], xs[c]), nF);
-#pragma unroll
-        for (int e = c + 1; e < 4; ++e)
-          nF = fmaf(2.f * L.cw[c] * L.cw[e], patch_dot(S.F, tc, ys[c], xs[c], ys[e], xs[e]), nF);
-      }
+      float beta, nF;
+      pixel_scalars(S.F, tc, c, beta, nF);
       const float av = col_sum(ap) + beta;
       const float den0 = sqrtf(fmaxf(nF, 0.f)) * sqrtf(q);
       const bool floored = !(den0 >= 1e-12f);
       const float den = floored ? 1e-12f : den0;
       const float cosv = av / den;
-      const float gp = valid ? a.dcos[(int64_t)view * HW + p] : 0.f;
+      const float gp = valid ? gpn : 0.f;
       const float al = gp / den;
       const float dq = floored ? 0.f : -0.5f * gp * cosv / q;
-      if (g == 0 && valid) a.dqpix[(int64_t)view * HW + p] = dq;
-      __builtin_amdgcn_sched_barrier(0);
-      // dL/dz at the lane's units: into the table (dW1, db1 below) and, as
-      // they are, the B operand of dL/dx
-      uint16_t zh[32], zl[32];
-#pragma unroll
-      for (int mb = 0; mb < 8; ++mb) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int u = 4 * mb + j, k = 32 * g + u;
-          const float dh = fmaf(al, csum(u), 2.f * dq * mh[u]);
-          const float dz = h[u] > 0.f ? dh : 0.f;
-          bf_split(dz, zh[u], zl[u]);
-          S.Ghi[rp_index(k, pr)] = zh[u];
-          S.Glo[rp_index(k, pr)] = zl[u];
-        }
-        __builtin_amdgcn_sched_barrier(0);
+      if (g == 0) {
+        if (valid) a.dqpix[(int64_t)view * HW + (int64_t)py * a.W + px] = dq;
+        S.al[wv][n] = al;
       }
-      // dL/dx (channels x the wave's 16 pixels) = W1^T dL/dz, K = the lane
-      // group's own units 32 g + 8 kb .. + 7: A = W1^T (channel n, those
-      // units), B = dL/dz at pixel n; lane (n, g) receives channels 4 g + j
-      // of its own pixel
+      wave_sync();
+      // dQ and dbeta: A = slots x pixels, B = h
       {
-        f4v dxa = {0.f, 0.f, 0.f, 0.f};
+        const f4v al4 = *reinterpret_cast<const f4v*>(&S.al[wv][4 * g]);
+        const float wys = (sy == c.ys[0] - tc.cy0 ? 1.f - c.wy : 0.f) + (sy == c.ys[2] - tc.cy0 ? c.wy : 0.f);
+        float w[4];
 #pragma unroll
-        for (int kb = 0; kb < 4; ++kb) {
-          const bf8v bh = as_bf8(&zh[8 * kb]), bl = as_bf8(&zl[8 * kb]);
-          dxa = mfma_bf(dxh[kb], bh, dxa);
-          dxa = mfma_bf(dxh[kb], bl, dxa);
-          dxa = mfma_bf(dxl[kb], bh, dxa);
-        }
-        if (valid) {
-          float* dfx = a.dfeat + (int64_t)view * kFIn * HW + p;
+        for (int i = 0; i < 4; ++i) w[i] = al4[i] * (wys * wxs[i]);
+        dbeta += (w[0] + w[1]) + (w[2] + w[3]);
+        bf8v whh, wl0;
+        pair4(w, whh, wl0);
 #pragma unroll
-          for (int j = 0; j < 4; ++j) dfx[(4 * g + j) * HW] = dxa[j];
+        for (int b = 0; b < 8; ++b) {
+          const bf8v hb = column(b);
+          accQ[b] = mfma_bf(whh, hb, accQ[b]);
+          accQ[b] = mfma_bf(wl0, hb, accQ[b]);
         }
       }
-      if (g == 1) {
-        float wc[kSlots];
+      wave_sync();
+      // dL/dz at the lane's units: into the table (dW1, db1 below) and, as they
+      // are, the B operand of dL/dx (channels x the row's pixels) = W1^T dL/dz:
+      // lane (n, g) receives channels 4 g + j of its own pixel
+      f4v dxa = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int sl = 0; sl < kSlots; ++sl) wc[sl] = 0.f;
+      for (int kb = 0; kb < 4; ++kb) {
+        float dz[8];
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
-#pragma unroll
-          for (int sl = 0; sl < kSlots; ++sl) wc[sl] += (L.cs[c] == sl) ? al * L.cw[c] : 0.f;
-#pragma unroll
-        for (int sl = 0; sl < kSlots; ++sl) S.Wc[sl][pr] = wc[sl];
+        for (int i = 0; i < 8; ++i) {
+          const int u = 8 * kb + i;
+          const float dh = fmaf(al, cs[u], 2.f * dq * mh[u]);
+          dz[i] = h[u] > 0.f ? dh : 0.f;
+        }
+        bf8v zh, zl;
+        split8(dz, zh, zl);
+        put(kb, zh, zl);
+        const bf8v wh = S.dx[0][kb][lane], wl = S.dx[1][kb][lane];
+        dxa = mfma_bf(wh, zh, dxa);
+        dxa = mfma_bf(wh, zl, dxa);
+        dxa = mfma_bf(wl, zh, dxa);
       }
-      __syncthreads();
+      if (valid) {
+        float* dfx = a.dfeat + (int64_t)view * kFIn * HW + (int64_t)py * a.W + px + 4 * gl * HW;
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb) {
-        // dQ += Wc^T h (rows = slots), and the constant-one column for dbeta
-        bf8v wh, wl;
-        f32_frag(S.Wc, n, kb, lane, wh, wl);
+        for (int j = 0; j < 4; ++j) dfx[j * HW] = dxa[j];
+      }
+      wave_sync();
+      // dW1^T (A = features x pixels, B = dL/dz) and db1
+      {
+        float xt[4];
 #pragma unroll
-        for (int i = 0; i < 3; ++i) {
-          const int nb = i == 0 ? wv : (i == 1 ? wv + 4 : 8);
-          if (nb == 8 && wv != 0) continue;
-          bf8v bh, bl;
-          if (nb < 8) {
-            bh = tab_frag(S.Hhi, 16 * nb + n, kb, lane);
-            bl = tab_frag(S.Hlo, 16 * nb + n, kb, lane);
-          } else {
-            bh = ones;
-            uint16_t zero[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-            bl = as_bf8(zero);
-          }
-          accQ[i] = mfma_bf(wh, bh, accQ[i]);
-          accQ[i] = mfma_bf(wh, bl, accQ[i]);
-          accQ[i] = mfma_bf(wl, bh, accQ[i]);
+        for (int i = 0; i < 4; ++i) xt[i] = py < a.H && tx * kFT + 4 * gl + i < a.W ? xtn[i] : 0.f;
+        bf8v xhh, xl0;
+        pair4(xt, xhh, xl0);
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+          const bf8v zb = column(b);
+          accW[b] = mfma_bf(xhh, zb, accW[b]);
+          accW[b] = mfma_bf(xl0, zb, accW[b]);
+          float s[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) s[i] = (float)zb[i];
+          db[b] += ((s[0] + s[4]) + (s[1] + s[5])) + ((s[2] + s[6]) + (s[3] + s[7]));
         }
-        // dW1^T += x^T dL/dz and db1 += 1^T dL/dz: columns 16 nb + n
-        bf8v xh, xl;
-        f32_frag(S.X, n, kb, lane, xh, xl);
+      }
+      wave_sync();
+    }
+    // the next tile's patches, put below
+    CellStage<kBwdWaves> cells;
+    const int t2 = t + (int)gridDim.x;
+    if (t2 < total) {
+      const int lt2 = t2 % a.tiles;
+      cells.request(a, t2 / a.tiles, tile_cells(a, lt2 % a.tiles_x, lt2 / a.tiles_x), wv);
+    }
+    // the tile's patch gradients: the eight waves' sums through their tables
+    float* tw = reinterpret_cast<float*>(S.T[wv]);
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          const int ck = 16 * (2 * wv + i) + n;
-          const bf8v zh = tab_frag(S.Ghi, ck, kb, lane), zl = tab_frag(S.Glo, ck, kb, lane);
-          accW[i] = mfma_bf(xh, zh, accW[i]);
-          accW[i] = mfma_bf(xh, zl, accW[i]);
-          accW[i] = mfma_bf(xl, zh, accW[i]);
-          accB[i] = mfma_bf(ones, zh, accB[i]);
-          accB[i] = mfma_bf(ones, zl, accB[i]);
-        }
+    for (int b = 0; b < 8; ++b)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) tw[(4 * g + j) * kFHid + 16 * b + n] = accQ[b][j];
+    dbeta = col_sum(dbeta);
+    if (g == 0) S.al[wv][n] = dbeta;
+    __syncthreads();
+    {
+      float* dqt = a.dqt + (int64_t)t * kSlots * kDQ;
+      const int sl = threadIdx.x >> 5, u = 4 * (threadIdx.x & 31);
+      if (sl < tc.ncy * tc.ncx) {
+        f4v sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < kBwdWaves; ++w)
+          sum += *reinterpret_cast<const f4v*>(reinterpret_cast<const float*>(S.T[w]) + sl * kFHid + u);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) dqt[sl * kDQ + u + i] = sum[i];
+      }
+      if (threadIdx.x < tc.ncy * tc.ncx) {
+        float sum = 0.f;
+#pragma unroll
+        for (int w = 0; w < kBwdWaves; ++w) sum += S.al[w][threadIdx.x];
+        dqt[threadIdx.x * kDQ + kFHid] = sum;
       }
     }
-    // the tile's patch gradients: rows = slots 4 (lane / 16) + j, column 16 nb + n
-    float* dqt = a.dqt + (int64_t)t * kSlots * kDQ;
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      const int nb = i == 0 ? wv : (i == 1 ? wv + 4 : 8);
-      if (nb == 8 && (wv != 0 || n != 0)) continue;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) dqt[(4 * g + j) * kDQ + 16 * nb + n] = accQ[i][j];
-    }
+    if (t2 < total) cells.put(S.F, wv);
+    __syncthreads();
   }
-  // workgroup partials: dW1^T rows 4 g + j, db1 (row 0 of the ones block)
-  float* part = a.part + (int64_t)blockIdx.x * kPartStride;
+  // workgroup partials: dW1^T rows 4 g + j, then db1
+  float* part = a.part + (int64_t)blockIdx.x * kPartStride + 16384;
+  {
+    float* tw = reinterpret_cast<float*>(S.T[wv]);
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
+    for (int b = 0; b < 8; ++b)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) part[16384 + (4 * g + j) * kFHid + 16 * (2 * wv + i) + n] = accW[i][j];
-    if (g == 0) part[16384 + 2048 + 16 * (2 * wv + i) + n] = accB[i][0];
+      for (int j = 0; j < 4; ++j) tw[(4 * g + j) * kFHid + 16 * b + n] = accW[b][j];
+  }
+  __syncthreads();
+  {
+    const int at = 4 * threadIdx.x;
+    f4v sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < kBwdWaves; ++w) sum += *reinterpret_cast<const f4v*>(reinterpret_cast<const float*>(S.T[w]) + at);
+    *reinterpret_cast<f4v*>(part + at) = sum;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int b = 0; b < 8; ++b) {
+    db[b] = col_sum(db[b]);
+    if (g == 0) reinterpret_cast<float*>(S.T[wv])[16 * b + n] = db[b];
+  }
+  __syncthreads();
+  if (threadIdx.x < kFHid) {
+    float sum = 0.f;
+#pragma unroll
+    for (int w = 0; w < kBwdWaves; ++w) sum += reinterpret_cast<const float*>(S.T[w])[threadIdx.x];
+    part[2048 + threadIdx.x] = sum;
   }
 }
 
@@ -800,37 +872,21 @@ __global__ void __launch_bounds__(64 * kBwdWaves) k_feat_bwd(FeatArgs a) {
 // on and above the diagonal are formed; the partial holds T with
 // T + T^T = S + S^T (off-diagonal blocks doubled, diagonal blocks once, blocks
 // below the diagonal zero). The four waves' sums are added in a fixed order.
+constexpr int kSWaves = 4;  // waves per workgroup
 constexpr int kSPix = 32;  // pixels per wave step
 constexpr int kSBlk = 36;  // blocks of S on and above the diagonal
 
 struct SShared {
   uint4 wfrag[8][2][64];                  // first-layer B fragments: unit block, (high, low), lane
   float red[2][kSBlk * 4 * 64];           // cross-wave sums of S
-  float dm[kBwdWaves][kFHid];
-  float dmu[kBwdWaves];
+  float dm[kSWaves][kFHid];
+  float dmu[kSWaves];
 };
 
-// the lane's 8 values of the first-layer accumulators as high and low bfloat16
-// operands (element j: pixel 4 g + j of the first 16, then of the second 16)
-ASGS_DEV void split8(const float (&v)[8], bf8v& hi, bf8v& lo) {
-  typedef float f2v __attribute__((ext_vector_type(2)));
-  typedef __bf16 bf2v __attribute__((ext_vector_type(2)));
-#pragma unroll
-  for (int j = 0; j < 8; j += 2) {
-    const bf2v h = __builtin_convertvector((f2v{v[j], v[j + 1]}), bf2v);
-    const uint32_t u = __builtin_bit_cast(uint32_t, h);
-    const bf2v l = __builtin_convertvector(
-        (f2v{v[j] - __uint_as_float(u << 16), v[j + 1] - __uint_as_float(u & 0xffff0000u)}), bf2v);
-    hi[j] = h[0];
-    hi[j + 1] = h[1];
-    lo[j] = l[0];
-    lo[j + 1] = l[1];
-  }
-}
 // max(z, 0) on the bits: negative floats (and -0) are negative integers
 ASGS_DEV float relu_bits(float z) { return __int_as_float(max(__float_as_int(z), 0)); }
 
-__global__ void __launch_bounds__(64 * kBwdWaves) k_feat_bwd_s(FeatArgs a) {
+__global__ void __launch_bounds__(64 * kSWaves) k_feat_bwd_s(FeatArgs a) {
   __shared__ __attribute__((aligned(16))) SShared S;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, g = lane >> 4, n = lane & 15;
   // B fragment of unit block b for lane (lg, ln): unit 16 b + ln, features
@@ -860,7 +916,7 @@ __global__ void __launch_bounds__(64 * kBwdWaves) k_feat_bwd_s(FeatArgs a) {
   const int HW = a.W * a.H;
   const int cpv = (HW + kSPix - 1) / kSPix;
   const int nchunk = a.V * cpv;
-  const int stride = gridDim.x * kBwdWaves;
+  const int stride = gridDim.x * kSWaves;
   // features and dq of one chunk, loads clamped into the view (the pixels
   // past its end are masked where they are used: their dq is zero)
   float xn[2][8], dqn[8];
@@ -879,7 +935,7 @@ __global__ void __launch_bounds__(64 * kBwdWaves) k_feat_bwd_s(FeatArgs a) {
     }
     limn = HW - base;
   };
-  int c = blockIdx.x * kBwdWaves + wv;
+  int c = blockIdx.x * kSWaves + wv;
   if (c < nchunk) fetch(c);
   for (; c < nchunk; c += stride) {
     float x[2][8], dq[8];
@@ -1238,7 +1294,7 @@ void launch_feature_forward(const FeatCall& c, const FeatLayout& L, char* work, 
   const FeatArgs a = feat_args(c, L, work);
   launch_prep(a, L, work, s);
   const int total = a.tiles * a.V;
-  hipLaunchKernelGGL(k_feat_fwd, dim3((unsigned)(total < 512 ? total : 512)), dim3(64 * kFwdWaves), 0, s, a);
+  hipLaunchKernelGGL(k_feat_fwd, dim3((unsigned)(total < 256 ? total : 256)), dim3(64 * kFwdWaves), 0, s, a);
   if (c.loss) hipLaunchKernelGGL(k_feat_loss, dim3((unsigned)a.V), dim3(256), 0, s, a, c.loss);
 }
 
@@ -1248,7 +1304,7 @@ void launch_feature_backward(const FeatCall& c, const FeatLayout& L, char* work,
   const int total = a.tiles * a.V;
   const int nwg = total < kBwdWG ? total : kBwdWG;
   hipLaunchKernelGGL(k_feat_bwd, dim3((unsigned)nwg), dim3(64 * kBwdWaves), 0, s, a);
-  hipLaunchKernelGGL(k_feat_bwd_s, dim3((unsigned)nwg), dim3(64 * kBwdWaves), 0, s, a);
+  hipLaunchKernelGGL(k_feat_bwd_s, dim3((unsigned)nwg), dim3(64 * kSWaves), 0, s, a);
   float* red = reinterpret_cast<float*>(work + L.red);
   hipLaunchKernelGGL(k_feat_reduce, dim3((kPart + 63) / 64), dim3(256), 0, s, a.part, nwg, red);
   float* dqc = reinterpret_cast<float*>(work + L.dqc);

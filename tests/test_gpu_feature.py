@@ -99,6 +99,14 @@ def test_feature_lift_matches_oracle(V, H, W, Hp, Wp, nh):
     _run(V, H, W, Hp, Wp, nh, seed=10 + H + W)
 
 
+@pytest.mark.parametrize("V,H,W,Hp,Wp,nh", [(1, 8, 8, 1, 1, 16), (1, 8, 17, 1, 2, 20), (1, 48, 48, 6, 6, 33),
+                                             (3, 271, 257, 9, 11, 16)])
+def test_feature_lift_tile_edges(V, H, W, Hp, Wp, nh):
+    """Half a tile, one pixel past a tile, all 16 patches of a tile in use, and
+    867 tiles whose last row and column hold one line of pixels."""
+    _run(V, H, W, Hp, Wp, nh, seed=100 + H + W)
+
+
 @pytest.mark.slow
 def test_feature_lift_full_frame():
     """The 640x480 frame with the 34x46 DINO patch grid and 384 channels."""
