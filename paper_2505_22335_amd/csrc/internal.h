@@ -321,12 +321,26 @@ ASGS_DEV void bilin(int p, int n_in, float scale, int& i0, int& i1, float& w1) {
 // one per thread. A block's intersections reach the per-tile counters through
 // an LDS grid over the bounding box of its Gaussians' rectangles (Gaussians of
 // one block are mostly neighbours in space), so a hot tile takes one global
-// atomic per block instead of one per Gaussian. Gaussians with a rectangle
-// of more than kBoxRect tiles, and every Gaussian of a block whose box has
-// more than kBoxCells tiles, use the global counters directly.
+// atomic per block instead of one per Gaussian. In views of more than kBoxCells
+// tiles, Gaussians with a rectangle of more than kBoxRect tiles, and every
+// Gaussian of a block whose box has more than kBoxCells, use the global
+// counters directly.
 // ---------------------------------------------------------------------------
 constexpr int kBoxCells = 4096;
 constexpr int kBoxRect = 64;
+
+// Rectangles of more than kFewTiles tiles of a block, one wave each: a thread
+// that walked one alone kept its wave waiting (a room's volume, up to 130 tiles a
+// Gaussian at 640x480, 20k anchors: the emission 65 us so, with a global atomic
+// awaited per tile of more than 64; 19 with waves and the LDS grid).
+constexpr uint32_t kFewTiles = 16;
+
+static_assert(kScanThreads <= 256, "a thread's number in a byte");
+struct RectQueue {
+  short4 rect[kScanThreads];
+  uint8_t thread[kScanThreads];
+  int n;
+};
 
 struct TileBox {
   int x0, y0, w, area;  // LDS cell of tile (tx, ty): (ty - y0) * w + tx - x0
@@ -339,11 +353,18 @@ ASGS_DEV T wave_min(T v) {
   return v;
 }
 
-// Bounding box of the rects of the lanes with small set; clears its cells.
-ASGS_DEV TileBox tile_box(short4 r, bool small, int* red, uint32_t* cell) {
+// Bounding box of the rects of the lanes with small set; clears its cells. The
+// queue takes the rects of more than kFewTiles tiles.
+ASGS_DEV TileBox tile_box(short4 r, bool small, uint32_t cnt, int* red, uint32_t* cell, RectQueue& q) {
   const int t = threadIdx.x;
   if (t < 4) red[t] = 0x7FFFFFFF;
+  if (t == 4) q.n = 0;
   __syncthreads();
+  if (cnt > kFewTiles) {
+    const int k = atomicAdd(&q.n, 1);  // in any order
+    q.rect[k] = r;
+    q.thread[k] = (uint8_t)t;
+  }
   const int big = 0x7FFFFFFF;
   const int x0 = wave_min(small ? (int)r.x : big), nx1 = wave_min(small ? -(int)r.y : big);
   const int y0 = wave_min(small ? (int)r.z : big), ny1 = wave_min(small ? -(int)r.w : big);
@@ -366,6 +387,27 @@ ASGS_DEV TileBox tile_box(short4 r, bool small, int* red, uint32_t* cell) {
     for (int c = t; c < b.area; c += kScanThreads) cell[c] = 0u;
   __syncthreads();
   return b;
+}
+
+// f(tx, ty, tiles, v) for every tile of every thread's rectangle r (cnt tiles),
+// with the thread's v = value(thread); the queued ones by whole waves.
+template <class G, class F>
+ASGS_DEV void for_tiles(short4 r, uint32_t cnt, const RectQueue& q, G value, F f) {
+  if (cnt > 0u && cnt <= kFewTiles) {
+    const auto v = value((int)threadIdx.x);
+    for (int ty = r.z; ty <= r.w; ++ty)
+      for (int tx = r.x; tx <= r.y; ++tx) f(tx, ty, cnt, v);
+  }
+  const int nq = __builtin_amdgcn_readfirstlane(q.n);
+  for (int k = threadIdx.x >> 6; k < nq; k += kScanThreads / 64) {
+    const short4 b = q.rect[k];
+    const auto v = value((int)q.thread[k]);
+    const int w = b.y - b.x + 1, n = w * (b.w - b.z + 1);
+    for (int i = threadIdx.x & 63; i < n; i += 64) {
+      const int y = i / w;
+      f(b.x + i - y * w, b.z + y, (uint32_t)n, v);
+    }
+  }
 }
 
 // View of a global tile key (views are stored in tile_base order).

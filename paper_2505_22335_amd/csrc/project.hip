@@ -259,18 +259,17 @@ __global__ void __launch_bounds__(256) k_project(RenderConst rc, asgs_gaussians 
   __shared__ uint32_t vred[256 / 64];
   __shared__ int bred[4];
   __shared__ uint32_t cell[kBoxCells];
+  __shared__ RectQueue queue;
   const uint32_t cnt = vis ? (uint32_t)((tx1 - tx0 + 1) * (ty1 - ty0 + 1)) : 0u;
   const short4 r = vis ? make_short4((short)tx0, (short)tx1, (short)ty0, (short)ty1) : make_short4(1, 0, 1, 0);
   uint32_t* tcount = ctx_ptr<uint32_t>(ctx, L.tcur);
-  const bool small = cnt > 0u && cnt <= (uint32_t)kBoxRect;
-  const TileBox bx = tile_box(r, small, bred, cell);
-  const bool via_lds = bx.lds && small;
-  for (int ty = r.z; ty <= r.w; ++ty)
-    for (int tx = r.x; tx <= r.y; ++tx) {
-      if (via_lds) atomicAdd(&cell[(ty - bx.y0) * bx.w + tx - bx.x0], 1u);
-      else __hip_atomic_fetch_add(&tcount[V.tile_base + ty * V.TX + tx], 1u, __ATOMIC_RELAXED,
-                                  __HIP_MEMORY_SCOPE_AGENT);
-    }
+  const bool few = V.TX * V.TY <= kBoxCells;  // the grid holds any box
+  const bool small = cnt > 0u && (few || cnt <= (uint32_t)kBoxRect);
+  const TileBox bx = tile_box(r, small, cnt, bred, cell, queue);
+  for_tiles(r, cnt, queue, [](int) { return 0; }, [&](int tx, int ty, uint32_t n, int) {
+    if (bx.lds && (few || n <= (uint32_t)kBoxRect)) atomicAdd(&cell[(ty - bx.y0) * bx.w + tx - bx.x0], 1u);
+    else __hip_atomic_fetch_add(&tcount[V.tile_base + ty * V.TX + tx], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  });
   __syncthreads();
   if (bx.lds)
     for (int c = threadIdx.x; c < bx.area; c += blockDim.x) {

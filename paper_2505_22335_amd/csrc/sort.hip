@@ -250,6 +250,7 @@ __global__ void __launch_bounds__(kScanThreads) k_dup_emit(RenderConst rc, const
   __shared__ uint32_t wvp[kScanThreads / 64], wvc[kScanThreads / 64];
   __shared__ int bred[4];
   __shared__ uint32_t cell[kBoxCells];
+  __shared__ RectQueue queue;
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const ScanBlock sb = scan_block(rc);
   const ViewDev& V = views[sb.view];
@@ -273,8 +274,9 @@ __global__ void __launch_bounds__(kScanThreads) k_dup_emit(RenderConst rc, const
     wvp[wv] = wv == 0 ? vpre : 0u;
     wvc[wv] = (uint32_t)__popcll(vbits);
   }
-  const bool small = cnt > 0u && cnt <= (uint32_t)kBoxRect;
-  const TileBox bx = tile_box(r, small, bred, cell);  // synchronises: wred, wsum are complete
+  const bool few = V.TX * V.TY <= kBoxCells;  // the grid holds any box
+  const bool small = cnt > 0u && (few || cnt <= (uint32_t)kBoxRect);
+  const TileBox bx = tile_box(r, small, cnt, bred, cell, queue);  // synchronises: wred, wsum are complete
   unsigned long long off = 0;
   for (int w = 0; w < kScanThreads / 64; ++w) off += wred[w] + (w < wv ? wsum[w] : 0u);
   off += incl - cnt;
@@ -284,11 +286,12 @@ __global__ void __launch_bounds__(kScanThreads) k_dup_emit(RenderConst rc, const
     for (int w = 0; w < kScanThreads / 64; ++w) vp += wvp[w] + (w < wv ? wvc[w] : 0u);
     ctx_ptr<uint32_t>(ctx, L.vlist)[(int64_t)sb.view * rc.n + vp] = (uint32_t)sb.j;
   }
-  const bool via_lds = bx.lds && small;
   // count the block's places per tile, reserve them, then hand them out
-  if (via_lds)
-    for (int ty = r.z; ty <= r.w; ++ty)
-      for (int tx = r.x; tx <= r.y; ++tx) atomicAdd(&cell[(ty - bx.y0) * bx.w + tx - bx.x0], 1u);
+  auto cell_of = [&](int tx, int ty) { return (ty - bx.y0) * bx.w + tx - bx.x0; };
+  auto via_lds = [&](uint32_t n) { return bx.lds && (few || n <= (uint32_t)kBoxRect); };
+  for_tiles(r, cnt, queue, [](int) { return 0; }, [&](int tx, int ty, uint32_t n, int) {
+    if (via_lds(n)) atomicAdd(&cell[cell_of(tx, ty)], 1u);
+  });
   __syncthreads();
   if (bx.lds)
     for (int c = t; c < bx.area; c += kScanThreads) {
@@ -299,16 +302,17 @@ __global__ void __launch_bounds__(kScanThreads) k_dup_emit(RenderConst rc, const
       }
     }
   __syncthreads();
-  if (cnt == 0u) return;
-  const unsigned long long key = ((unsigned long long)ctx_ptr<const uint32_t>(ctx, L.dkey)[sb.j] << 32) |
-                                 (uint32_t)sb.j;
   const uint64_t cap = (uint64_t)rc.cap;
-  for (int ty = r.z; ty <= r.w; ++ty)
-    for (int tx = r.x; tx <= r.y; ++tx) {
-      const uint32_t pos = via_lds ? atomicAdd(&cell[(ty - bx.y0) * bx.w + tx - bx.x0], 1u)
+  const uint32_t* dkey = ctx_ptr<const uint32_t>(ctx, L.dkey);
+  auto key = [&](int th) {
+    const uint32_t j = (uint32_t)(sb.j - t + th);
+    return (unsigned long long)dkey[j] << 32 | j;
+  };
+  for_tiles(r, cnt, queue, key, [&](int tx, int ty, uint32_t n, unsigned long long k) {
+    const uint32_t pos = via_lds(n) ? atomicAdd(&cell[cell_of(tx, ty)], 1u)
                                    : atomicAdd(&tcur[V.tile_base + ty * V.TX + tx], 1u);
-      if (pos < cap) ukey[pos] = key;
-    }
+    if (pos < cap) ukey[pos] = k;
+  });
 }
 
 // ---------------------------------------------------------------------------

@@ -1,5 +1,5 @@
-"""The blend kernels at the edges of their rounds, list cuts and quarter
-masks, against the FP64 oracle (tolerances and guard band of the render
+"""The blend, projection and binning kernels at the edges of their rounds, list
+cuts, quarter masks and rectangle queues, against the FP64 oracle (tolerances and guard band of the render
 parity tests: images 1e-4, gradients 1e-3)."""
 import numpy as np
 import pytest
@@ -7,7 +7,8 @@ import torch
 
 import oracle
 import synth
-from tests.gpu_util import GRAD_TOL, IMG_TOL, guard_report, log, oracle_opts, rel_err, to_np, upstream
+from tests.gpu_util import (GRAD_TOL, IMG_TOL, check_binning_self_consistent, guard_report, log, oracle_opts, rel_err,
+                            to_np, upstream)
 
 pytestmark = pytest.mark.gpu
 
@@ -173,3 +174,29 @@ def test_gradients_over_many_tiles(n, nf):
     log("case many tiles", n, nf, "largest", int(tiles.max()), "16:", int((tiles == 16).sum()), "17:", int((tiles == 17).sum()))
     assert tiles.max() > 16 and (n < 300 or ((tiles == 16).any() and (tiles == 17).any()))
     _check(sc, cam, nf, "many tiles n=%d nf=%d" % (n, nf), 0.15)
+
+
+@pytest.mark.parametrize("n", [5, 256, 700])
+@pytest.mark.parametrize("W,H", [(640, 480), (1024, 1024), (1040, 1024)])
+def test_binning_of_wide_rectangles(W, H, n):
+    """Rectangles of one tile to several hundred in views of 1200, 4096 (the
+    LDS grid's limit) and 4160 tiles: small ones by their thread, larger ones
+    by a wave, over the grid or the global counters. Lists, ranges and order
+    equal their integer re-derivation."""
+    rng = np.random.default_rng(W + n)
+    z = rng.uniform(2.0, 4.0, n)
+    f = 500.0
+    px = np.exp(rng.uniform(np.log(1.0), np.log(70.0), (2, n)))  # standard deviations in pixels
+    q = rng.normal(size=(4, n))
+    sc = synth.PlainScene(
+        mean=np.stack([(rng.uniform(0, W, n) - W / 2) * z / f, (rng.uniform(0, H, n) - H / 2) * z / f, z]).astype(np.float32),
+        scale=np.stack([px[0] * z / f, px[1] * z / f, px[1] * z / f]).astype(np.float32), rot=q.astype(np.float32),
+        opacity=rng.uniform(0.05, 0.6, n).astype(np.float32), rgb=rng.uniform(0, 1, (3, n)).astype(np.float32))
+    cam = synth.Camera(W, H, f, f, W / 2 - 0.5, H / 2 - 0.5, np.eye(3, 4, dtype=np.float32))
+    g = P.gaussians_to_device(sc.arrays())
+    rc = P.RenderContext([cam], n, n_feat=0)
+    rc.fit(g)
+    rc.forward(g)
+    torch.cuda.synchronize()
+    st, _ = check_binning_self_consistent(rc, "wide rectangles %dx%d n=%d" % (W, H, n))
+    assert n < 256 or (st["ntiles"].max() > 64 and ((st["ntiles"] > 0) & (st["ntiles"] <= 16)).any())
