@@ -200,3 +200,26 @@ def test_binning_of_wide_rectangles(W, H, n):
     torch.cuda.synchronize()
     st, _ = check_binning_self_consistent(rc, "wide rectangles %dx%d n=%d" % (W, H, n))
     assert n < 256 or (st["ntiles"].max() > 64 and ((st["ntiles"] > 0) & (st["ntiles"] <= 16)).any())
+
+
+@pytest.mark.parametrize("n", [2, 64, 65, 255, 256, 257, 511, 512, 513, 1023, 1024, 1025, 2047, 2048, 2049, 4097])
+def test_list_order_at_run_edges(n):
+    """One tile's list of n entries, a third of them at equal depths (ordered by
+    index): every length at which the sort changes its number of keys per
+    thread, its runs or their merging."""
+    rng = np.random.default_rng(n)
+    z = rng.uniform(2.0, 4.0, n)
+    z[rng.permutation(n)[:n // 3]] = 3.0
+    q = rng.normal(size=(4, n))
+    sc = synth.PlainScene(
+        mean=np.stack([rng.uniform(-0.2, 0.2, n), rng.uniform(-0.2, 0.2, n), z]).astype(np.float32),
+        scale=rng.uniform(1.5, 4.0, (3, n)).astype(np.float32), rot=q.astype(np.float32),
+        opacity=rng.uniform(0.006, 0.02, n).astype(np.float32), rgb=rng.uniform(0, 1, (3, n)).astype(np.float32))
+    cam = synth.Camera(16, 16, 20.0, 20.0, 7.5, 7.5, np.eye(3, 4, dtype=np.float32))
+    g = P.gaussians_to_device(sc.arrays())
+    rc = P.RenderContext([cam], n, n_feat=0)
+    rc.fit(g)
+    rc.forward(g)
+    torch.cuda.synchronize()
+    st, _ = check_binning_self_consistent(rc, "one list n=%d" % n)
+    assert st["n_isect"] == n
