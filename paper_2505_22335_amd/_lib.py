@@ -8,9 +8,12 @@ fallback path.
 from __future__ import annotations
 
 import ctypes as C
+import math
 import os
 import re
 from typing import Dict, Optional, Sequence
+
+import numpy as np
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(PKG, "libasgs.so")
@@ -207,13 +210,14 @@ def make_cameras(cams: Sequence) -> "C.Array":
     """Objects with width, height, fx, fy, cx, cy, T_wc (3x4) and optionally
     t (frame time, default 0) -> Camera[]."""
     arr = (Camera * len(cams))()
-    for i, c in enumerate(cams):
-        arr[i].width, arr[i].height = int(c.width), int(c.height)
-        arr[i].fx, arr[i].fy, arr[i].cx, arr[i].cy = float(c.fx), float(c.fy), float(c.cx), float(c.cy)
-        T = [float(x) for row in c.T_wc for x in row]
-        for k in range(12):
-            arr[i].T_wc[k] = T[k]
-        arr[i].t = float(getattr(c, "t", 0.0))
+    for a, c in zip(arr, cams):
+        a.width, a.height = int(c.width), int(c.height)
+        a.fx, a.fy, a.cx, a.cy = float(c.fx), float(c.fy), float(c.cx), float(c.cy)
+        # (one call instead of twelve scalars taken from an array, the usual form)
+        rows = c.T_wc.tolist() if isinstance(c.T_wc, np.ndarray) else c.T_wc
+        T = [float(x) for row in rows for x in row]
+        a.T_wc[:] = T[:12]
+        a.t = float(getattr(c, "t", 0.0))
     return arr
 
 
@@ -246,7 +250,7 @@ def make_gaussians(g: Dict[str, "object"], n: int) -> Gaussians:
             continue
         per_view = (t.dim() == 3) or (f == "opacity" and t.dim() == 2)
         setattr(s, f, t.data_ptr())
-        s.view_stride[i] = t[0].numel() if per_view else 0
+        s.view_stride[i] = math.prod(t.shape[1:]) if per_view else 0
     return s
 
 

@@ -14,7 +14,8 @@ sum_n ad(xi)^n / (n+1)! with ad(xi) = [[phi^, rho^], [0, phi^]], evaluated
 exactly as the upper-right block of the exponential of [[ad, I], [0, 0]].
 
 The forward reads xi to the host (one small synchronising copy) to place the
-cameras; all other work stays on the device. A renderer keeps one
+cameras, and with check the intersection count of its render; all other work
+stays on the device. A renderer keeps one
 forward/backward context: the backward must follow its own forward before the
 renderer's next forward (checked).
 """
@@ -121,6 +122,25 @@ class TrackedRenderer:
         self.base = self.poses(np.asarray(xi, np.float64))
 
 
+def _jacobians(xi: np.ndarray, device) -> torch.Tensor:
+    """Left Jacobians of the twists, on their way to the device without waiting
+    for the work ahead of them in the stream (pinned memory, which its allocator
+    keeps until the copy has run)."""
+    J = torch.empty((len(xi), 6, 6), dtype=torch.float32, pin_memory=True)
+    J.copy_(torch.from_numpy(np.stack([se3_left_jacobian(x) for x in xi])))
+    return J.to(device, non_blocking=True)
+
+
+def _fit_forward(rc: RenderContext, g: Dict[str, torch.Tensor], img: Dict[str, torch.Tensor]):
+    """Render again with a context of the right size if the render of g into img
+    overflowed it. A render that fits, the common case, pays one header read
+    instead of the count's projection and its wait before the render."""
+    need, _, ov = rc.status()
+    if ov:
+        rc.ensure(int(need * 1.25) + 1024)
+        rc.forward(g, out=img)
+
+
 class _DecodeRender(torch.autograd.Function):
     @staticmethod
     def forward(ctx, xi, xyz, feat, off, params, tr: TrackedRenderer, check: bool):
@@ -130,15 +150,12 @@ class _DecodeRender(torch.autograd.Function):
         tr.r.a = DeviceAnchors(xyz=xyz.detach(), feat=feat.detach(), off=off.detach(), params=params.detach(),
                                k=a.k, n_feat=a.n_feat, l_o=a.l_o, l_s=a.l_s)
         tr.r.decode()
-        if check:
-            need = tr.r.rc.count(tr.r.g)
-            if need > tr.r.rc.capacity:
-                tr.r.rc.ensure(int(need * 1.25) + 1024)
         img = tr.r.rc.forward(tr.r.g, out=None)
         tr.generation += 1
         ctx.tr, ctx.gen = tr, tr.generation
-        ctx.J = torch.as_tensor(np.stack([se3_left_jacobian(x) for x in xi_h]), dtype=torch.float32,
-                                device=xi.device)
+        ctx.J = _jacobians(xi_h, xi.device)
+        if check:
+            _fit_forward(tr.r.rc, tr.r.g, img)
         ctx.nf = "feat" in img
         ctx.shapes = {k: v.shape for k, v in img.items()}
         outs = (img["rgb"], img["depth"], img["alpha"], img["feat"] if ctx.nf else img["depth"].new_zeros(0))
@@ -157,7 +174,7 @@ class _DecodeRender(torch.autograd.Function):
         if ctx.nf:
             dimg["feat"] = g(d_feat, "feat")
         out = tr.r.backward(dimg, pose=True)
-        d_xi = torch.bmm(ctx.J.transpose(1, 2).contiguous(), out["d_pose"][:, :, None])[:, :, 0]
+        d_xi = (ctx.J * out["d_pose"][:, :, None]).sum(1)  # J^T g
         return (d_xi, out["d_xyz"], out["d_feat"], out["d_off"], out["d_params"], None, None)
 
 
@@ -169,7 +186,8 @@ def decode_render(xi: torch.Tensor, xyz: torch.Tensor, feat: torch.Tensor, off: 
     params (packed head parameters): float32 device tensors. Returns rgb
     (V,3,H,W), depth (V,H,W), alpha (V,H,W) and, with a feature head, feat
     (V,16,H,W). check=True sizes the render context for the new poses (one
-    synchronising count pass); check=False trusts the current capacity.
+    synchronising header read, and a second render where the context was too
+    small); check=False trusts the current capacity.
     """
     rgb, depth, alpha, fimg = _DecodeRender.apply(xi, xyz, feat, off, params, tr, check)
     out = {"rgb": rgb, "depth": depth, "alpha": alpha}
@@ -222,15 +240,14 @@ class _RenderGaussians(torch.autograd.Function):
              "rgb": rgb.detach().contiguous()}
         if gr.nf:
             g["feat"] = feat.detach().contiguous()
-        if check:
-            gr.rc.fit(g)
         img = gr.rc.forward(g)
         gr.generation += 1
         ctx.gr, ctx.gen, ctx.g = gr, gr.generation, g
         ctx.pose = xi is not None
         if ctx.pose:
-            ctx.J = torch.as_tensor(np.stack([se3_left_jacobian(x) for x in xi_h]), dtype=torch.float32,
-                                    device=mean.device)
+            ctx.J = _jacobians(xi_h, mean.device)
+        if check:
+            _fit_forward(gr.rc, g, img)
         ctx.shapes = {k: v.shape for k, v in img.items()}
         return img["rgb"], img["depth"], img["alpha"], img["feat"] if gr.nf else img["depth"].new_zeros(0)
 
@@ -249,7 +266,7 @@ class _RenderGaussians(torch.autograd.Function):
         dg, d_pose = gr.rc.backward(ctx.g, dimg, pose=ctx.pose)
         d_xi = None
         if ctx.pose:
-            d_xi = torch.bmm(ctx.J.transpose(1, 2).contiguous(), d_pose[:, :, None])[:, :, 0]
+            d_xi = (ctx.J * d_pose[:, :, None]).sum(1)  # J^T g
         # the views share one set of Gaussians: their gradients add up
         red = {k: v.sum(0) for k, v in dg.items()}
         return (d_xi, red["mean"], red["scale"], red["rot"], red["opacity"], red["rgb"],

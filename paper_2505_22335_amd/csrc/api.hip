@@ -382,8 +382,7 @@ int asgs_render_count(const asgs_camera* cams, int32_t n_views, const asgs_gauss
   char* c = static_cast<char*>(ctx);
   if ((st = run_front(P, g, c, s))) return st;
   CtxHeader h;
-  hipError_t e = hipMemcpyAsync(&h, c + P.L.hdr, sizeof(h), hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  const hipError_t e = hipMemcpyWithStream(&h, c + P.L.hdr, sizeof(h), hipMemcpyDeviceToHost, s);  // waits for the copy
   if (e != hipSuccess) return fail(ASGS_E_DEVICE, "count readback: %s", hipGetErrorString(e));
   *n_isect = (int64_t)h.n_isect;
   return ASGS_OK;
@@ -502,8 +501,7 @@ int asgs_ctx_status(const void* ctx, void* stream, int64_t* n_isect, int64_t* n_
   if (!ctx) return fail(ASGS_E_INVALID, "ctx is NULL");
   CtxHeader h;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  hipError_t e = hipMemcpyAsync(&h, ctx, sizeof(h), hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  const hipError_t e = hipMemcpyWithStream(&h, ctx, sizeof(h), hipMemcpyDeviceToHost, s);  // waits for the copy
   if (e != hipSuccess) return fail(ASGS_E_DEVICE, "ctx readback: %s", hipGetErrorString(e));
   if (n_isect) *n_isect = (int64_t)h.n_isect;
   if (n_visible) *n_visible = (int64_t)h.n_visible;
