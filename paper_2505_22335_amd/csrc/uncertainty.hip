@@ -69,10 +69,12 @@ ASGS_DEV TileCells tile_cells(const UncArgs& a, int tx, int ty) {
 // Z_c = W1 F_c + b1: one workgroup per 16 patches x 16 hidden units of a
 // view, one (patch, unit) per thread; weight and feature blocks of kKC input
 // channels staged in LDS, the next block's loads issued before the current
-// block is used.
+// block is used. Both are staged with the channels along the rows and read four
+// at a time: 11.9 us (1530 patches, 384 channels; 15.5 with single reads), a
+// chain of six blocks.
 __global__ void __launch_bounds__(256) k_fu_grid(UncArgs a) {
-  __shared__ float ws[kGU][kKC + 1];
-  __shared__ float fs[kKC][kGC];
+  __shared__ __attribute__((aligned(16))) float ws[kGU][kKC + 4];
+  __shared__ __attribute__((aligned(16))) float fs[kGC][kKC + 4];
   const int v = blockIdx.z;
   const int plane = a.Hp * a.Wp;
   const int c0 = blockIdx.x * kGC, u0 = blockIdx.y * kGU;
@@ -99,12 +101,19 @@ __global__ void __launch_bounds__(256) k_fu_grid(UncArgs a) {
     for (int i = 0; i < kPer; ++i) {
       const int q = t + 256 * i;
       ws[q / kKC][q % kKC] = wn[i];
-      fs[q / kGC][q % kGC] = fn[i];
+      fs[q % kGC][q / kGC] = fn[i];
     }
     __syncthreads();
     if (k0 + kKC < a.nh) load(k0 + kKC);
-#pragma unroll 8
-    for (int k = 0; k < kKC; ++k) acc = fmaf(ws[uu][k], fs[k][pc], acc);
+#pragma unroll 4
+    for (int k = 0; k < kKC; k += 4) {
+      const float4 w = *reinterpret_cast<const float4*>(&ws[uu][k]);
+      const float4 f = *reinterpret_cast<const float4*>(&fs[pc][k]);
+      acc = fmaf(w.x, f.x, acc);
+      acc = fmaf(w.y, f.y, acc);
+      acc = fmaf(w.z, f.z, acc);
+      acc = fmaf(w.w, f.w, acc);
+    }
   }
   if (c0 + pc < plane) a.zg[((int64_t)v * plane + c0 + pc) * kHid + u0 + uu] = acc + a.params[(int64_t)kHid * a.nh + u0 + uu];
 }
@@ -129,29 +138,22 @@ struct PixShared {
   float bred[4];
 };
 
-// weight of patch slot sl at a pixel whose corners are (cs, cw)
-ASGS_DEV float slot_weight(const int (&cs)[4], const float (&cw)[4], int sl) {
-  float w = 0.f;
-#pragma unroll
-  for (int c = 0; c < 4; ++c) w += cs[c] == sl ? cw[c] : 0.f;
-  return w;
+// Weight of a patch slot at a pixel: the sum of the pixel's bilinear weights over
+// the corners (y0 x0, y0 x1, y1 x0, y1 x1) that fall on the slot. The slot's
+// column takes part with (x0, x1), once per tile, its row with (y0, y1), once
+// per row of pixels; zero where a corner lies elsewhere.
+struct AxisWeight {
+  float w0, w1;
+};
+ASGS_DEV AxisWeight axis_weight(int p, int n_in, float scale, int at) {
+  int i0, i1;
+  float w;
+  bilin(p, n_in, scale, i0, i1, w);
+  return {i0 == at ? 1.f - w : 0.f, i1 == at ? w : 0.f};
 }
-
-// corners (cs, cw) of pixel column px in a row whose patch rows are r0, r1
-// (slot offsets) with weight wy
-ASGS_DEV void col_corners(const UncArgs& a, const TileCells& tc, int px, int r0, int r1, float wy, int (&cs)[4],
-                          float (&cw)[4]) {
-  int x0, x1;
-  float wx;
-  bilin(px, a.Wp, a.sx, x0, x1, wx);
-  cs[0] = r0 + x0 - tc.cx0;
-  cs[1] = r0 + x1 - tc.cx0;
-  cs[2] = r1 + x0 - tc.cx0;
-  cs[3] = r1 + x1 - tc.cx0;
-  cw[0] = (1.f - wy) * (1.f - wx);
-  cw[1] = (1.f - wy) * wx;
-  cw[2] = wy * (1.f - wx);
-  cw[3] = wy * wx;
+ASGS_DEV float slot_weight(const AxisWeight& y, const AxisWeight& x) {
+#pragma clang fp contract(off)  // the sum of the four products, each rounded
+  return ((y.w0 * x.w0 + y.w0 * x.w1) + y.w1 * x.w0) + y.w1 * x.w1;
 }
 
 template <int kCtrl>
@@ -181,14 +183,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
   // requested first (clamped into the view; pixels outside it are masked
   // where used)
   const int rr = n & 3;
-  float Rq[4];
-  if (a.R) {
-#pragma unroll
-    for (int pb = 0; pb < 4; ++pb) {
-      const int px = min(tx * kT + 4 * g + rr, a.W - 1), py = min(ty * kT + 4 * wv + pb, a.H - 1);
-      Rq[pb] = a.R[v * HW + (int64_t)py * a.W + px];
-    }
-  }
   // ---- stage the patches' Z (zero past the tile's patches) and w2 ----
   for (int q = t; q < kSlots * kHid; q += 256) {
     const int sl = q / kHid, u = q - sl * kHid;
@@ -207,6 +201,16 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
 #pragma unroll
   for (int b = 0; b < 8; ++b) w2n[b] = S.w2[16 * b + n];
   const bool grad = a.dzt != nullptr;
+  // patch coordinates of the lane's slots (a row past the tile's patches takes no weight)
+  auto slot_y = [&](int sl) { return tc.cy0 + sl / tc.ncx; };
+  auto slot_x = [&](int sl) { return tc.cx0 + sl % tc.ncx; };
+  AxisWeight xA[4], xB[4];  // slots 4 s + g at pixel n; slot n at pixels 4 g + r
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int pxa = tx * kT + n, pxr = tx * kT + 4 * g + i;
+    xA[i] = axis_weight(pxa < a.W ? pxa : 0, a.Wp, a.sx, slot_x(4 * i + g));
+    xB[i] = axis_weight(pxr < a.W ? pxr : 0, a.Wp, a.sx, slot_x(n));
+  }
   f4v dz[8];
   float aw2[8];
 #pragma unroll
@@ -214,31 +218,28 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
     dz[b] = f4v{0.f, 0.f, 0.f, 0.f};
     aw2[b] = 0.f;
   }
-  double lsum = 0.0;
+  float sigl = 1.f, Rl = 0.f;  // sigma and R of the lane's pixel of the loss: row n / 4, column 4 g + n % 4
+  bool inl = false;
   float dbs = 0.f;
-#pragma unroll
+#pragma unroll 1
   for (int pb = 0; pb < 4; ++pb) {
     const int py = ty * kT + 4 * wv + pb;
-    int y0, y1;
-    float wy;
-    bilin(py < a.H ? py : 0, a.Hp, a.sy, y0, y1, wy);
-    const int r0 = (y0 - tc.cy0) * tc.ncx, r1 = (y1 - tc.cy0) * tc.ncx;
+    float Rp = 0.f;
+    if (a.R) Rp = a.R[v * HW + (int64_t)min(py, a.H - 1) * a.W + min(tx * kT + 4 * g + rr, a.W - 1)];
+    const int pyc = py < a.H ? py : 0;
     // A of z: the weights of slots 4 s + g at pixel n of the row
     f4v z[8];
     {
-      int cs[4];
-      float cw[4];
-      const int pxa = tx * kT + n;
-      col_corners(a, tc, pxa < a.W ? pxa : 0, r0, r1, wy, cs, cw);
       float wA[4];
 #pragma unroll
-      for (int st = 0; st < 4; ++st) wA[st] = slot_weight(cs, cw, 4 * st + g);
+      for (int st = 0; st < 4; ++st) wA[st] = slot_weight(axis_weight(pyc, a.Hp, a.sy, slot_y(4 * st + g)), xA[st]);
 #pragma unroll
       for (int b = 0; b < 8; ++b) z[b] = f4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int st = 0; st < 4; ++st)
+        if (4 * st < nslots)  // the other slots hold zeros
 #pragma unroll
-        for (int b = 0; b < 8; ++b) z[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(wA[st], zb[st][b], z[b], 0, 0, 0);
+          for (int b = 0; b < 8; ++b) z[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(wA[st], zb[st][b], z[b], 0, 0, 0);
     }
     // y at pixels 4 g + r: w2 . relu(z) over the units, summed over the row group's lanes
     float yr[4];
@@ -258,7 +259,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
     const float sig = a.sigma_min + sp;
     float dy = 0.f;
     if (a.R && in) {
-      const float R = Rq[pb];
+      const float R = Rp;
       // dL_u/dsigma = (-R / sigma^3 + lam3 / sigma) / HW, dsigma/dy = sigmoid(y)
       const float dsig = (-R / (sig * sig * sig) + a.lam3 / sig) * a.inv_hw;
       dy = dsig / (1.f + expf(-y));
@@ -267,10 +268,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
       const int64_t q = v * HW + (int64_t)py * a.W + px;
       if (a.sigma) a.sigma[q] = sig;
       if (a.dynamic) a.dynamic[q] = 2.f * sig * sig > 1.f ? 1u : 0u;
-      if (a.R) {
-        const double sd = (double)sig;
-        lsum += (double)Rq[pb] / (2.0 * sd * sd) + (double)a.lam3 * log(sd);
-      }
+    }
+    if (pb == n >> 2) {
+      sigl = sig;
+      Rl = Rp;
+      inl = in;
     }
     if (grad) {
       // dy of pixels 4 g + r in every lane of the quad
@@ -280,15 +282,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
       dyr[2] = dpp<0xAA>(dy);
       dyr[3] = dpp<0xFF>(dy);
       // A of dZ, step r: the weight of slot n at pixel 4 g + r
+      const AxisWeight yB = axis_weight(pyc, a.Hp, a.sy, slot_y(n));
       float wB[4];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        int cs[4];
-        float cw[4];
-        const int pxr = tx * kT + 4 * g + r;
-        col_corners(a, tc, pxr < a.W ? pxr : 0, r0, r1, wy, cs, cw);
-        wB[r] = slot_weight(cs, cw, n);
-      }
+      for (int r = 0; r < 4; ++r) wB[r] = slot_weight(yB, xB[r]);
 #pragma unroll
       for (int r = 0; r < 4; ++r)
 #pragma unroll
@@ -302,6 +299,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
     }
   }
   if (a.partial) {
+    double lsum = 0.0;
+    if (a.R && inl) {
+      const double sd = (double)sigl;
+      lsum = (double)Rl / (2.0 * sd * sd) + (double)a.lam3 * log(sd);
+    }
     for (int o = 32; o > 0; o >>= 1) lsum += __shfl_xor(lsum, o);
     if (lane == 0) S.lred[wv] = lsum;
   }
