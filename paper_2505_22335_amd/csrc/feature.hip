@@ -353,12 +353,14 @@ constexpr int kQC = 16;  // patches per workgroup (the M side of the product)
 
 // Per run of 16 consecutive patches (flat index): Q = W2^T G for all 16 on
 // the matrix cores (v_mfma_f32_16x16x4f32, FP32; M = patches, N = units,
-// K = channels four at a time; wave w takes the unit blocks 2 (w % 4),
-// 2 (w % 4) + 1 over one half of the channels, the halves added in a fixed
-// order), so W2 is read once per run; then beta and the neighbour dot
-// products, one patch per lane column and the channels split over the 32
-// lane groups of the workgroup, summed in a fixed order.
-__global__ void __launch_bounds__(512) k_feat_cells(FeatArgs a, float* cells) {
+// K = channels four at a time; of the first eight waves w takes the unit blocks
+// 2 (w % 4), 2 (w % 4) + 1 over one half of the channels, the halves added in a
+// fixed order), so W2 is read once per run; beta and the neighbour dot products
+// by the other eight, one patch per lane column and the channels split over
+// their 32 lane groups, summed in a fixed order. Bound by the chain of loads
+// (98 workgroups for 34 x 46 patches): 12.3 us, where the same eight waves did
+// one after the other 17.3.
+__global__ void __launch_bounds__(1024) k_feat_cells(FeatArgs a, float* cells) {
   __shared__ float qh[kQC][kFHid];
   __shared__ float red[8][kQC][6];
   const int c0 = blockIdx.x * kQC, view = blockIdx.y;
@@ -366,30 +368,40 @@ __global__ void __launch_bounds__(512) k_feat_cells(FeatArgs a, float* cells) {
   const float* G = a.dino + (int64_t)view * a.nh * plane;
   const float* W2 = a.params + kFHid * kFIn + kFHid;
   const float* b2 = W2 + (int64_t)a.nh * kFHid;
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6, g = lane >> 4, f = lane & 15;
-  const int ub = wv & 3, kh = wv >> 2;
+  const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6), g = lane >> 4, f = lane & 15;
+  const bool qwave = wv < 8;  // the first eight waves form Q, the others beta and the dot products
+  const int ub = wv & 3, kh = (wv >> 2) & 1;
   const int half = ((a.nh + 63) / 64) * 32;  // channels of the first half (a multiple of 32)
   f4v q0 = {0.f, 0.f, 0.f, 0.f}, q1 = q0;
-  {
+  if (qwave) {
     // A: channel 4 s + g of patch c0 + f; B: W2 rows 4 s + g, units 32 ub + f (+ 16)
-    const float* Ga = G + min(c0 + f, plane - 1);
-    const float* Wb = W2 + 32 * ub + f;
+    const int ao = g * plane + min(c0 + f, plane - 1), bo = g * kFHid + 32 * ub + f;
     const int cb = kh * half, ce = min(a.nh, cb + half);
-    for (int c = cb + g; c < ce + g; c += 32) {
+    int c = cb;
+    // whole blocks of 32 channels: scalar addresses, no masks
+#pragma unroll 2
+    for (; c + 32 <= ce; c += 32) {
       float av[8], b0[8], b1[8];
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        const int ch = c + 4 * i;
-        const bool ok = ch < ce;
-        av[i] = ok ? Ga[(int64_t)ch * plane] : 0.f;
-        b0[i] = ok ? Wb[(int64_t)ch * kFHid] : 0.f;
-        b1[i] = ok ? Wb[(int64_t)ch * kFHid + 16] : 0.f;
+        av[i] = (G + (int64_t)(c + 4 * i) * plane)[ao];
+        const float* Wb = W2 + (int64_t)(c + 4 * i) * kFHid;
+        b0[i] = Wb[bo];
+        b1[i] = Wb[bo + 16];
       }
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         q0 = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i], b0[i], q0, 0, 0, 0);
         q1 = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i], b1[i], q1, 0, 0, 0);
       }
+    }
+    for (; c < ce; c += 4) {
+      const bool ok = c + g < ce;
+      const float* Wb = W2 + (int64_t)c * kFHid;
+      const float av = ok ? (G + (int64_t)c * plane)[ao] : 0.f;
+      const float b0 = ok ? Wb[bo] : 0.f, b1 = ok ? Wb[bo + 16] : 0.f;
+      q0 = __builtin_amdgcn_mfma_f32_16x16x4f32(av, b0, q0, 0, 0, 0);
+      q1 = __builtin_amdgcn_mfma_f32_16x16x4f32(av, b1, q1, 0, 0, 0);
     }
     if (kh == 1) {
       // rows: patches 4 g + r; columns: units 32 ub + f (+ 16)
@@ -401,49 +413,59 @@ __global__ void __launch_bounds__(512) k_feat_cells(FeatArgs a, float* cells) {
     }
   }
   // beta, |G|^2 and the neighbour products of patch c0 + i, i = t % 16,
-  // channels t / 16 + 32 k, four at a time
-  const int i = t & (kQC - 1), cg = t >> 4;
+  // channels t / 16 + 32 k, four at a time where whole
+  const int i = f;
   const int cell = min(c0 + i, plane - 1);
   const int gy = cell / a.Wp, gx = cell - gy * a.Wp;
   const bool rx = gx + 1 < a.Wp, dy = gy + 1 < a.Hp;
   const int i1 = rx ? cell + 1 : cell, i2 = dy ? cell + a.Wp : cell, i3 = rx && dy ? cell + a.Wp + 1 : cell;
   const float f1 = rx ? 1.f : 0.f, f2 = dy ? 1.f : 0.f, f3 = rx && dy ? 1.f : 0.f;
   float p[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  for (int c = cg; c < a.nh; c += 128) {
+  auto dots = [&](float v0, float v1, float v2, float v3, float vb) {
+    v1 *= f1;
+    v2 *= f2;
+    v3 *= f3;
+    p[0] = fmaf(vb, v0, p[0]);
+    p[1] = fmaf(v0, v0, p[1]);
+    p[2] = fmaf(v0, v1, p[2]);
+    p[3] = fmaf(v0, v2, p[3]);
+    p[4] = fmaf(v0, v3, p[4]);
+    p[5] = fmaf(v1, v2, p[5]);
+  };
+  const int go = g * plane;
+  int c = qwave ? a.nh : 4 * (wv - 8);  // the wave's channels c + g
+#pragma unroll 2
+  for (; c + 100 <= a.nh; c += 128) {
     float v0[4], v1[4], v2[4], v3[4], vb[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      const int ch = min(c + 32 * k, a.nh - 1);
-      const float* Gc = G + (int64_t)ch * plane;
-      const float m = c + 32 * k < a.nh ? 1.f : 0.f;
-      v0[k] = m * Gc[cell];
-      v1[k] = f1 * Gc[i1];
-      v2[k] = f2 * Gc[i2];
-      v3[k] = f3 * Gc[i3];
-      vb[k] = b2[ch];
+      const float* Gc = G + (int64_t)(c + 32 * k) * plane;
+      v0[k] = Gc[go + cell];
+      v1[k] = Gc[go + i1];
+      v2[k] = Gc[go + i2];
+      v3[k] = Gc[go + i3];
+      vb[k] = b2[c + 32 * k + g];
     }
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      p[0] = fmaf(vb[k], v0[k], p[0]);
-      p[1] = fmaf(v0[k], v0[k], p[1]);
-      p[2] = fmaf(v0[k], v1[k], p[2]);
-      p[3] = fmaf(v0[k], v2[k], p[3]);
-      p[4] = fmaf(v0[k], v3[k], p[4]);
-      p[5] = fmaf(v1[k] * (c + 32 * k < a.nh ? 1.f : 0.f), v2[k], p[5]);
-    }
+    for (int k = 0; k < 4; ++k) dots(v0[k], v1[k], v2[k], v3[k], vb[k]);
   }
+  for (; c < a.nh; c += 32)
+    if (c + g < a.nh) {
+      const float* Gc = G + (int64_t)c * plane;
+      dots(Gc[go + cell], Gc[go + i1], Gc[go + i2], Gc[go + i3], b2[c + g]);
+    }
   // lanes i, i + 16, i + 32, i + 48 of the wave, then the eight waves
 #pragma unroll
   for (int k = 0; k < 6; ++k) {
     p[k] += __shfl_xor(p[k], 16);
     p[k] += __shfl_xor(p[k], 32);
   }
-  if (lane < kQC) {
+  if (!qwave && lane < kQC) {
 #pragma unroll
-    for (int k = 0; k < 6; ++k) red[wv][i][k] = p[k];
+    for (int k = 0; k < 6; ++k) red[wv - 8][i][k] = p[k];
   }
   __syncthreads();
-  if (kh == 0) {
+  if (qwave && kh == 0) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int cl = c0 + 4 * g + r;
@@ -1285,7 +1307,7 @@ void launch_prep(const FeatArgs& a, const FeatLayout& L, char* work, hipStream_t
   launch_colgemm(g, gm, s);
   hipLaunchKernelGGL(k_feat_frag, dim3((kFrag / 2 + 255) / 256), dim3(256), 0, s, a, (const float*)gm,
                      reinterpret_cast<uint16_t*>(work + L.mfrag), reinterpret_cast<float*>(work + L.mvec));
-  hipLaunchKernelGGL(k_feat_cells, dim3((unsigned)((a.Hp * a.Wp + kQC - 1) / kQC), (unsigned)a.V), dim3(512), 0, s, a,
+  hipLaunchKernelGGL(k_feat_cells, dim3((unsigned)((a.Hp * a.Wp + kQC - 1) / kQC), (unsigned)a.V), dim3(1024), 0, s, a,
                      reinterpret_cast<float*>(work + L.cells));
 }
 }  // namespace
