@@ -892,15 +892,18 @@ __global__ void __launch_bounds__(64 * kBwdWaves) k_feat_bwd(FeatArgs a) {
 // S = (dq h) h^T with K = the 32 pixels (rows: units of dq h, columns: units
 // of h), so h never goes through LDS. S is symmetric: the 36 blocks of 16 x 16
 // on and above the diagonal are formed; the partial holds T with
-// T + T^T = S + S^T (off-diagonal blocks doubled, diagonal blocks once, blocks
-// below the diagonal zero). The four waves' sums are added in a fixed order.
+// T + T^T = S + S^T (off-diagonal blocks doubled, diagonal blocks once; blocks
+// below the diagonal count as zero). The four waves' sums are added in a fixed
+// order.
 constexpr int kSWaves = 4;  // waves per workgroup
 constexpr int kSPix = 32;  // pixels per wave step
 constexpr int kSBlk = 36;  // blocks of S on and above the diagonal
 
 struct SShared {
-  uint4 wfrag[8][2][64];                  // first-layer B fragments: unit block, (high, low), lane
-  float red[2][kSBlk * 4 * 64];           // cross-wave sums of S
+  union {
+    uint4 wfrag[8][2][64];                // first-layer B fragments: unit block, (high, low), lane
+    float red[kSWaves][kSBlk * 4 * 64];   // at the end: each wave's sums of S
+  };
   float dm[kSWaves][kFHid];
   float dmu[kSWaves];
 };
@@ -1028,45 +1031,23 @@ __global__ void __launch_bounds__(64 * kSWaves) k_feat_bwd_s(FeatArgs a) {
     for (int b = 0; b < 8; ++b) S.dm[wv][16 * b + n] = dmacc[b];
   }
   if (lane == 0) S.dmu[wv] = dmuacc;
-  // S over the waves: (w0 + w1) + (w2 + w3)
-  if (wv & 1) {
+  // S over the waves, (w0 + w1) + (w2 + w3); wave w adds rows 4 g + w of every block
+  __syncthreads();  // the fragments are no longer read
 #pragma unroll
-    for (int i = 0; i < kSBlk; ++i)
+  for (int i = 0; i < kSBlk; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) S.red[wv >> 1][(4 * i + j) * 64 + lane] = acc[i][j];
-  }
-  __syncthreads();
-  if (!(wv & 1)) {
-#pragma unroll
-    for (int i = 0; i < kSBlk; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc[i][j] += S.red[wv >> 1][(4 * i + j) * 64 + lane];
-  }
-  __syncthreads();
-  if (wv == 2) {
-#pragma unroll
-    for (int i = 0; i < kSBlk; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) S.red[0][(4 * i + j) * 64 + lane] = acc[i][j];
-  }
+    for (int j = 0; j < 4; ++j) S.red[wv][(4 * i + j) * 64 + lane] = acc[i][j];
   __syncthreads();
   float* part = a.part + (int64_t)blockIdx.x * kPartStride;
-  if (wv == 0) {
-    // rows 16 bi + 4 g + j, columns 16 bj + n; zero blocks below the diagonal
+  // rows 16 bi + 4 g + j, columns 16 bj + n (blocks below the diagonal are not read)
 #pragma unroll
-    for (int bj = 0; bj < 8; ++bj)
+  for (int bj = 0; bj < 8; ++bj)
 #pragma unroll
-      for (int bi = 0; bi <= bj; ++bi) {
-        const int i = bj * (bj + 1) / 2 + bi;
-        const float f = bi == bj ? 1.f : 2.f;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const float s = acc[i][j] + S.red[0][(4 * i + j) * 64 + lane];
-          part[(16 * bi + 4 * g + j) * kFHid + 16 * bj + n] = f * s;
-          if (bi != bj) part[(16 * bj + 4 * g + j) * kFHid + 16 * bi + n] = 0.f;
-        }
-      }
-  }
+    for (int bi = 0; bi <= bj; ++bi) {
+      const int at = (4 * (bj * (bj + 1) / 2 + bi) + wv) * 64 + lane;
+      const float s = (S.red[0][at] + S.red[1][at]) + (S.red[2][at] + S.red[3][at]);
+      part[(16 * bi + 4 * g + wv) * kFHid + 16 * bj + n] = bi == bj ? s : 2.f * s;
+    }
   const int t = threadIdx.x;
   if (t < kFHid)
     part[16384 + 2048 + 128 + t] = 2.f * ((S.dm[0][t] + S.dm[1][t]) + (S.dm[2][t] + S.dm[3][t]));
@@ -1081,7 +1062,8 @@ __global__ void __launch_bounds__(256) k_feat_reduce(const float* __restrict__ p
   const int el = threadIdx.x & 63, q = threadIdx.x >> 6;
   const int e = blockIdx.x * 64 + el;
   float acc = 0.f;
-  if (e < kPart) {
+  // (blocks of S below the diagonal: zero, not read)
+  if (e < kPart && !(e < kFHid * kFHid && e / kFHid / 16 > e % kFHid / 16)) {
     for (int b0 = q; b0 < nwg; b0 += 64) {
       float v[16];
 #pragma unroll
