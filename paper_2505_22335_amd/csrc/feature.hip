@@ -73,11 +73,13 @@ ASGS_DEV void split8(const float (&v)[8], bf8v& hi, bf8v& lo) {
   }
 }
 // sum over the four lanes of one pixel column (lanes l, l^16, l^32, l^48);
-// every lane of the column gets the same bits
+// every lane of the column gets the same bits (a swap of v with itself gives
+// every lane both halves' values)
 ASGS_DEV float col_sum(float v) {
-  v += __shfl_xor(v, 16);
-  v += __shfl_xor(v, 32);
-  return v;
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 // LDS position of hidden unit k in tables read one unit per lane group at a
 // time (units 32 apart land in neighbouring rows)
@@ -605,9 +607,10 @@ ASGS_DEV int table_swz(int p) { return ((p & 7) << 1) | (p >> 3); }
 //
 // Latency bounds it: LDS holds one workgroup, two waves per SIMD, that wait 57 %
 // of their time for it. 640x480, 384 channels, 256 workgroups of 4 or 5 tiles:
-// 121 us (22 a tile, 8 before the first). Four waves that met twice per four
-// rows, with h and dL/dz of 64 pixels in two tables for the whole workgroup,
-// read by unit without transposing (one wave per SIMD): 189.
+// 110 us (20 a tile, 8 before the first); 121 with seventeen registers spilled,
+// whose reloads wait for the loads requested ahead. Four waves that met twice
+// per four rows, with h and dL/dz of 64 pixels in two tables for the whole
+// workgroup, read by unit without transposing (one wave per SIMD): 189.
 __global__ void __launch_bounds__(64 * kBwdWaves) k_feat_bwd(FeatArgs a) {
   __shared__ __attribute__((aligned(16))) BwdShared S;
   stage_weights(a, S.F);
@@ -695,16 +698,6 @@ __global__ void __launch_bounds__(64 * kBwdWaves) k_feat_bwd(FeatArgs a) {
     float dbeta = 0.f;  // slot n over the pixels 4 g .. 4 g + 3
 #pragma unroll
     for (int b = 0; b < 8; ++b) accQ[b] = f4v{0.f, 0.f, 0.f, 0.f};
-    // weight of patch column n % ncx at the pixels 4 g + i
-    const int sy = n / tc.ncx, sx = n - sy * tc.ncx;
-    float wxs[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      int x0, x1;
-      float wx;
-      bilin(min(tx * kFT + 4 * g + i, a.W - 1), a.Wp, a.sx, x0, x1, wx);
-      wxs[i] = (sx == x0 - tc.cx0 ? 1.f - wx : 0.f) + (sx == x1 - tc.cx0 ? wx : 0.f);
-    }
 #pragma unroll 1
     for (int r = 0; r < kBwdRows; ++r) {
       // (lane coordinates of the row's own, so that what follows from them is
@@ -721,13 +714,6 @@ __global__ void __launch_bounds__(64 * kBwdWaves) k_feat_bwd(FeatArgs a) {
       const int r2 = r + 1 < kBwdRows ? r + 1 : 0, t2 = r2 ? t : t + (int)gridDim.x;
       if (t2 < total) fetch(t2, r2);
       const float qp = hidden<true>(S.F, xq, h, mh, put);
-      // feature n of the pixels 4 g + i, for dW1
-      float xtn[4];
-      {
-        const float* ft = a.feat + (int64_t)view * kFIn * HW + (int64_t)cpy * a.W + nl * HW;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) xtn[i] = ft[min(tx * kFT + 4 * gl + i, a.W - 1)];
-      }
       // the pixel's patch vector at the lane's units
       const Corners c = corners(a, tc, cpx, cpy);
       float cs[32];
@@ -750,6 +736,16 @@ __global__ void __launch_bounds__(64 * kBwdWaves) k_feat_bwd(FeatArgs a) {
       wave_sync();
       // dQ and dbeta: A = slots x pixels, B = h
       {
+        // weight of patch column n % ncx at the pixels 4 g + i
+        const int sy = nl / tc.ncx, sx = nl - sy * tc.ncx;
+        float wxs[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          int x0, x1;
+          float wx;
+          bilin(min(tx * kFT + 4 * gl + i, a.W - 1), a.Wp, a.sx, x0, x1, wx);
+          wxs[i] = (sx == x0 - tc.cx0 ? 1.f - wx : 0.f) + (sx == x1 - tc.cx0 ? wx : 0.f);
+        }
         const f4v al4 = *reinterpret_cast<const f4v*>(&S.al[wv][4 * g]);
         const float wys = (sy == c.ys[0] - tc.cy0 ? 1.f - c.wy : 0.f) + (sy == c.ys[2] - tc.cy0 ? c.wy : 0.f);
         float w[4];
@@ -766,6 +762,13 @@ __global__ void __launch_bounds__(64 * kBwdWaves) k_feat_bwd(FeatArgs a) {
         }
       }
       wave_sync();
+      // feature n of the pixels 4 g + i, for dW1
+      float xtn[4];
+      {
+        const float* ft = a.feat + (int64_t)view * kFIn * HW + (int64_t)cpy * a.W + nl * HW;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) xtn[i] = ft[min(tx * kFT + 4 * gl + i, a.W - 1)];
+      }
       // dL/dz at the lane's units: into the table (dW1, db1 below) and, as they
       // are, the B operand of dL/dx (channels x the row's pixels) = W1^T dL/dz:
       // lane (n, g) receives channels 4 g + j of its own pixel
