@@ -1,19 +1,22 @@
 // Front-to-back alpha compositing of colour, depth and the low-dimensional
 // feature (UP-SLAM Sec. 3.1 Eq. 3, Sec. 3.3 Eq. 10) and its backward.
 //
-// One workgroup per 16x16 screen tile; each wave covers an 8x8 quarter of it
-// (the forward has two waves per quarter, see k_blend_fwd). The tile's
-// depth-ordered list is staged through LDS in rounds of records; a wave visits
-// only the entries whose alpha >= alpha_min ellipse can reach its quarter;
-// each pixel skips alpha < alpha_min, stops before the transmittance would
-// fall below T_min, and accumulates w = alpha * T times (rgb, z, feature).
-// The workgroup leaves as soon as every pixel has stopped.
+// A wave covers an 8x8 quarter of a 16x16 screen tile, a pixel per lane. It
+// visits the entries of the tile's depth-ordered list whose alpha >= alpha_min
+// ellipse can reach the quarter (the mask the list sort left with each entry);
+// an entry is the same for all lanes, so its record comes through scalar loads,
+// one entry ahead, and takes no vector register or LDS. Each pixel skips alpha
+// < alpha_min, stops before the transmittance would fall below T_min, and
+// accumulates w = alpha * T times (rgb, z, feature). In the forward a workgroup
+// is one quarter (two waves, each half of a round of the list), and leaves as
+// soon as its pixels have stopped.
 //
-// The backward replays each pixel's list back to front from its last
-// composited Gaussian, recovering T_k = T_{k+1} / (1 - alpha_k), and sums each
-// entry's gradient over the tile's pixels on the matrix cores (see
-// k_blend_bwd); every entry's gradient slot is written once, without global
-// atomics. The projection backward then sums each Gaussian's slots.
+// The backward (a workgroup per tile or segment of a long list, a wave per
+// quarter) replays each pixel's list back to front from its last composited
+// Gaussian, recovering T_k = T_{k+1} / (1 - alpha_k), and sums each entry's
+// gradient over the tile's pixels on the matrix cores (see k_blend_bwd); every
+// entry's gradient slot is written once, without global atomics. The projection
+// backward then sums each Gaussian's slots.
 #include "internal.h"
 
 namespace asgs {
