@@ -23,8 +23,8 @@
 //   dW2 = sum_c G_c dQ_c^T + W2 (S + S^T) + b2 dm^T,
 //   db2 = sum_c dbeta_c G_c + W2 dm + 2 dmu b2.
 // The pixel sums dQ and dW1 are matrix products with K = pixels, taken on
-// the matrix cores from per-round LDS tiles of h, the corner weights, x and
-// dL/dz; S comes from a second pass whose register layout needs no tiles.
+// the matrix cores row by row, h and dL/dz transposed through LDS of the wave's
+// own; S comes from a second pass whose register layout needs no LDS.
 // Every sum has a fixed order (deterministic).
 #include "internal.h"
 
