@@ -198,6 +198,8 @@ int prepare(const asgs_camera* cams, int32_t n_views, int64_t n, const asgs_rend
   rc.n = n;
   rc.nv = n * n_views;
   rc.total_tiles = P.total_tiles;
+  rc.min_view_tiles = P.total_tiles;
+  for (int v = 0; v < n_views; ++v) rc.min_view_tiles = std::min(rc.min_view_tiles, P.views[v].TX * P.views[v].TY);
   rc.total_pix = P.total_pix;
   rc.cap = capacity;
   rc.n_cu = device_cu_count();

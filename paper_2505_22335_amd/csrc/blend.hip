@@ -8,8 +8,8 @@
 // one entry ahead, and takes no vector register or LDS. Each pixel skips alpha
 // < alpha_min, stops before the transmittance would fall below T_min, and
 // accumulates w = alpha * T times (rgb, z, feature). In the forward a workgroup
-// is one quarter (two waves, each half of a round of the list), and leaves as
-// soon as its pixels have stopped.
+// is one quarter (two or four waves, each a part of a round of the list), and
+// leaves as soon as its pixels have stopped.
 //
 // The backward (a workgroup per tile or segment of a long list, a wave per
 // quarter) replays each pixel's list back to front from its last composited
@@ -17,6 +17,8 @@
 // gradient over the tile's pixels on the matrix cores (see k_blend_bwd); every
 // entry's gradient slot is written once, without global atomics. The projection
 // backward then sums each Gaussian's slots.
+#include <type_traits>
+
 #include "internal.h"
 
 namespace asgs {
@@ -82,38 +84,46 @@ struct SRec<20> {
   ASGS_DEV void keep() const { asm volatile("" ::"s"(g[7])); }
 };
 
-constexpr int kFwdThreads = 128;  // two waves per 8x8 quarter: front and back half of its list
 constexpr int kFwdRound = 256;    // list entries per round
+// Views of up to this many tiles cut a round's list into four parts, a wave
+// each, larger ones into two (a rule on the view alone: its images do not depend
+// on the views rendered with it). Few tiles leave the chip to the chains of the
+// longest lists: 80 tiles of 50k entries 50 us with two waves, 38 with four; 300
+// tiles of 20k anchors 49 and 38; eight such views of 50k 208 and 163; 475 tiles
+// of 5k anchors 18 and 15. Beyond, more waves only add their share of the rounds
+// where lists are short: 690 tiles of 3k anchors 12 and 15, of 50k 95 and 75;
+// 1200 tiles of 130 entries 32 and 38, of 645 160 both.
+constexpr int kFwdSmallView = 512;
 constexpr int kSplitMin = 16;     // a round's quarter list shorter than this stays on the front wave
 
-// Forward compositing, one workgroup of two waves per 8x8 quarter of a tile.
-// Per round of up to 256 list entries, the entries that can reach one of the
-// quarter's pixels (the sort's quarter masks) are split in list order: the
-// front wave composites the first half onto the running state (T, channels,
-// last contributor), the back wave the second half from T = 1 at the same
-// time, both with the records in scalar registers (requested one entry ahead,
-// their cache lines touched at the start of the round); then the front wave
-// appends the back half's result,
-//   C <- C + T C_back,  T <- T T_back,
-// which equals compositing the two halves in order as long as the
-// transmittance cannot have crossed T_min inside the back half
-// (T T_back >= T_min, T being monotone). Pixels where it could re-run the
-// back half on the front wave with the sequential rule.
+// Forward compositing, one workgroup of two or four waves per 8x8 quarter of a
+// tile. Per round of up to 256 list entries, the entries that can reach one of
+// the quarter's pixels (the sort's quarter masks) are split in list order into a
+// part per wave: the front wave composites the first part onto the running
+// state (T, channels, last contributor), the others theirs from T = 1 at the
+// same time, all with the records in scalar registers (requested one entry
+// ahead, their cache lines touched at the start of the round); then the front
+// wave appends the other parts' results in turn,
+//   C <- C + T C_part,  T <- T T_part,
+// which equals compositing them in order as long as the transmittance cannot
+// have crossed T_min inside the part (T T_part >= T_min, T being monotone).
+// Pixels where it could re-run the part on the front wave with the sequential
+// rule.
 //
 // Bound by the vector ALU (about 42 instructions per used entry) and, on few
 // tiles, by the longest lists. One 512-thread workgroup per tile with the
 // records and an FP64 box test per entry staged through LDS waited at its
 // barriers two thirds of the time: one 640x480 view of 157k intersections
 // 48 us, now 32 us; 774k intersections 265 us, now 158; eight 320x240 views
-// with 986k 337 us, now 208; 80 tiles of 50k (no features) 70 us, now 50.
+// with 986k 337 us, now 163; 80 tiles of 50k (no features) 70 us, now 38.
 //
 // With L1, the output stage also forms the weighted L1 residual of the maps
 // against the targets and its gradient (the terms of the L1 loss kernel, in
 // the same arithmetic), and each quarter's loss partial.
 ASGS_DEV float l1_sgn(float d) { return d > 0.f ? 1.f : (d < 0.f ? -1.f : 0.f); }
 
-template <int NF, bool L1>
-__global__ void __launch_bounds__(kFwdThreads) k_blend_fwd(RenderConst rc, const ViewDev* __restrict__ views,
+template <int NF, bool L1, int NW>
+__global__ void __launch_bounds__(64 * NW) k_blend_fwd(RenderConst rc, const ViewDev* __restrict__ views,
                                                            char* ctx, CtxLayout L, asgs_images out, BlendL1 l1) {
   constexpr int CS = 4 + NF;
   // 32 consecutive workgroups are the four quarters of eight tiles, those of a
@@ -130,13 +140,15 @@ __global__ void __launch_bounds__(kFwdThreads) k_blend_fwd(RenderConst rc, const
   const int ty = lt / V.TX, tx = lt - ty * V.TX;
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const bool back = wv == 1;     // back half of the quarter's list
+  const bool back = wv > 0;  // not the first part of the round's list
   const int tq = (qd << 6) | lane;
   const int px = tx * kTile + tile_lx(tq);
   const int py = ty * kTile + tile_ly(tq);
   const bool inside = px < V.W && py < V.H;
   const float pxf = (float)px, pyf = (float)py;
   const uint2 rg = make_uint2(bi.y, bi.z);
+  const int P = NW > 2 && V.TX * V.TY <= kFwdSmallView ? NW : 2;  // parts of a round's list
+  if (wv >= P) return;  // a larger view among small ones (a barrier waits for the waves that are left)
   prioritise(bpos, rc.n_cu);
   const uint32_t* pairgid = ctx_ptr<const uint32_t>(ctx, L.pairgid);
   const float* geom = ctx_ptr<const float>(ctx, L.geom);
@@ -150,8 +162,8 @@ __global__ void __launch_bounds__(kFwdThreads) k_blend_fwd(RenderConst rc, const
   constexpr int SA = split_first(CS);
   float* sp = ctx_ptr<float>(ctx, L.split) + (size_t)(sl ? (sl & kSplitSlotMask) - 1u : 0u) * split_floats(CS);
 
-  __shared__ uint2 swl[2][kFwdRound];   // per wave: the quarter's entries of the round
-  __shared__ float xch[CS + 2][64];     // back-half state per pixel: T, channels, last
+  __shared__ uint2 swl[kFwdRound];                  // the quarter's entries of the round (every wave writes the same)
+  __shared__ float xch[NW - 1][CS + 2][64];  // later parts' state per pixel: T, channels, last
   __shared__ uint64_t qdone;            // front lanes already stopped
 
   // L1 targets and weight of the pixel, requested now and used in the output stage
@@ -185,10 +197,10 @@ __global__ void __launch_bounds__(kFwdThreads) k_blend_fwd(RenderConst rc, const
   // Composite the positions [i0, i1) of this wave's list of the round on the
   // lanes with reach = 0 (others: -inf, below every power); a lane stops
   // (reach = -inf) before T would fall below tstop (T_min, or -1 for a local
-  // back-half state).
+  // later part's state).
   constexpr float kNoReach = -__builtin_inff();
   auto run = [&](int i0, int i1, float& reach, float tstop) {
-    const uint2* lst = swl[wv];
+    const uint2* lst = swl;
     // one entry at list position pos; false when every lane has stopped
     auto entry = [&](const SRec<CS>& rec, uint32_t pos) -> bool {
       rec.keep();
@@ -250,7 +262,7 @@ __global__ void __launch_bounds__(kFwdThreads) k_blend_fwd(RenderConst rc, const
     if (!~dm) break;
     rstep = min((uint32_t)kFwdRound, min(segend, rg.y) - base);
     // the quarter's entries of the round (those that can reach one of its
-    // pixels), in list order, compacted into swl (the same list on both waves):
+    // pixels), in list order, compacted into swl (the same list on every wave):
     // the Gaussian and the position in the tile's list plus one
     int n = 0;
 #pragma unroll
@@ -258,18 +270,20 @@ __global__ void __launch_bounds__(kFwdThreads) k_blend_fwd(RenderConst rc, const
       const bool mine = (msk[k] >> qd) & 1u;
       const uint64_t bits = __ballot(mine);
       if (mine)
-        swl[wv][n + __builtin_amdgcn_mbcnt_hi((uint32_t)(bits >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bits, 0u))] =
+        swl[n + __builtin_amdgcn_mbcnt_hi((uint32_t)(bits >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bits, 0u))] =
             make_uint2(gid[k], base - rg.x + 64 * k + lane + 1u);
       n += __builtin_popcountll(bits);
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const int nf = n < kSplitMin ? n : (n + 1) / 2;
-    // touch the records of this wave's half, and request the next round's ids
+    // part w: list positions [cut(w), cut(w + 1))
+    const int len = n < kSplitMin ? n : (n + P - 1) / P;
+    const int p0 = min(n, wv * len), p1 = min(n, p0 + len);
+    // touch the records of this wave's part, and request the next round's ids
     float touch = 0.f;
-    for (int i = (back ? nf : 0) + lane; i < (back ? n : nf); i += 64) {
-      const size_t g = swl[wv][i].x;
+    for (int i = p0 + lane; i < p1; i += 64) {
+      const size_t g = swl[i].x;
       touch += geom[g * kGeomStride] + chan[g * CS] + chan[g * CS + CS - 1];
     }
     {
@@ -283,34 +297,41 @@ __global__ void __launch_bounds__(kFwdThreads) k_blend_fwd(RenderConst rc, const
       last = 0u;
       const bool skip = !inside || ((dm >> lane) & 1u);
       float reach = skip ? kNoReach : 0.f;
-      if (nf < n) run(nf, n, reach, -1.f);
-      xch[0][lane] = T;
+      if (p0 < p1) run(p0, p1, reach, -1.f);
+      xch[wv - 1][0][lane] = T;
 #pragma unroll
-      for (int c = 0; c < CS; ++c) xch[1 + c][lane] = acc[c];
-      xch[CS + 1][lane] = __uint_as_float(last);
+      for (int c = 0; c < CS; ++c) xch[wv - 1][1 + c][lane] = acc[c];
+      xch[wv - 1][CS + 1][lane] = __uint_as_float(last);
     } else if (n > 0) {
       float reach = done ? kNoReach : 0.f;
-      run(0, nf, reach, tmin);
+      run(0, p1, reach, tmin);
       done = reach != 0.f;
     }
     asm volatile("" ::"v"(touch));  // the touching loads are kept, and waited for here
     __syncthreads();
-    if (!back && nf != n) {
-      // append the back half
-      const float Tb = xch[0][lane];
-      const uint32_t lastb = __float_as_uint(xch[CS + 1][lane]);
+    // append part w
+    auto append = [&](int w) {
+      const int q0 = min(n, w * len), q1 = min(n, q0 + len);
+      if (q0 >= q1) return;
+      const float Tb = xch[w - 1][0][lane];
+      const uint32_t lastb = __float_as_uint(xch[w - 1][CS + 1][lane]);
       const bool fix = !done && T * Tb < tmin;
       if (!done && !fix) {
 #pragma unroll
-        for (int c = 0; c < CS; ++c) acc[c] = fmaf(T, xch[1 + c][lane], acc[c]);
+        for (int c = 0; c < CS; ++c) acc[c] = fmaf(T, xch[w - 1][1 + c][lane], acc[c]);
         T *= Tb;
         if (lastb) last = lastb;
       }
       if (any_lane(fix)) {
         float reach = fix ? 0.f : kNoReach;
-        run(nf, n, reach, tmin);
+        run(q0, q1, reach, tmin);
         done = done || (fix && reach != 0.f);
       }
+    };
+    if (!back) {
+      if (NW == 2) append(1);
+      else
+        for (int w = 1; w < P; ++w) append(w);
     }
     const bool ends = base + rstep == segend;
     if (ends && !back && segend < rg.y) {
@@ -839,14 +860,18 @@ void launch_blend_forward(const RenderConst& rc, const CtxLayout& L, char* ctx, 
                           const BlendL1* l1, hipStream_t s) {
   const ViewDev* views = reinterpret_cast<const ViewDev*>(ctx + L.views);
   const BlendL1 a = l1 ? *l1 : BlendL1{};
-  const dim3 grid((unsigned)((rc.total_tiles + 7) / 8 * 32)), block(kFwdThreads);
-  if (rc.nf == 16) {
-    if (l1) hipLaunchKernelGGL((k_blend_fwd<16, true>), grid, block, 0, s, rc, views, ctx, L, out, a);
-    else hipLaunchKernelGGL((k_blend_fwd<16, false>), grid, block, 0, s, rc, views, ctx, L, out, a);
-  } else {
-    if (l1) hipLaunchKernelGGL((k_blend_fwd<0, true>), grid, block, 0, s, rc, views, ctx, L, out, a);
-    else hipLaunchKernelGGL((k_blend_fwd<0, false>), grid, block, 0, s, rc, views, ctx, L, out, a);
-  }
+  const dim3 grid((unsigned)((rc.total_tiles + 7) / 8 * 32));
+  auto launch = [&](auto nf, auto nw) {
+    constexpr int kNf = decltype(nf)::value, kNw = decltype(nw)::value;
+    if (l1) hipLaunchKernelGGL((k_blend_fwd<kNf, true, kNw>), grid, dim3(64 * kNw), 0, s, rc, views, ctx, L, out, a);
+    else hipLaunchKernelGGL((k_blend_fwd<kNf, false, kNw>), grid, dim3(64 * kNw), 0, s, rc, views, ctx, L, out, a);
+  };
+  auto waves = [&](auto nf) {
+    if (rc.min_view_tiles <= kFwdSmallView) launch(nf, std::integral_constant<int, 4>{});
+    else launch(nf, std::integral_constant<int, 2>{});
+  };
+  if (rc.nf == 16) waves(std::integral_constant<int, 16>{});
+  else waves(std::integral_constant<int, 0>{});
 }
 
 void launch_l1_tile_loss(const RenderConst& rc, const CtxLayout& L, char* ctx, float* loss, hipStream_t s) {

@@ -42,6 +42,7 @@ struct RenderConst {
   int64_t n;           // Gaussians per view
   int64_t nv;          // n * n_views
   int32_t total_tiles;
+  int32_t min_view_tiles;  // tiles of the smallest view
   int32_t total_pix;
   int64_t cap;         // intersection capacity
   int32_t n_cu;        // compute units of the device (issue-priority bands of the blend kernels)

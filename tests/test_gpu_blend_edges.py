@@ -223,3 +223,25 @@ def test_list_order_at_run_edges(n):
     torch.cuda.synchronize()
     st, _ = check_binning_self_consistent(rc, "one list n=%d" % n)
     assert st["n_isect"] == n
+
+
+@pytest.mark.parametrize("nf", [0, 16])
+@pytest.mark.parametrize("n", [15, 16, 17, 31, 257, 600])
+def test_list_parts_of_a_large_view(n, nf):
+    """n specks on one tile of a 512x272 view (544 tiles: a round's list in two
+    parts, where the one-tile views above take four), some of them opaque
+    enough to end pixels inside the second part."""
+    rng = np.random.default_rng(100 + n)
+    z = rng.uniform(2.0, 4.0, n)
+    f = 100.0
+    u, v = rng.uniform(242.0, 253.0, n), rng.uniform(130.0, 141.0, n)
+    sig = rng.uniform(2.0, 4.0, (3, n))
+    o = np.where(rng.uniform(size=n) < 0.1, 0.9, rng.uniform(0.006, 0.03, n))
+    q = rng.normal(size=(4, n))
+    sc = synth.PlainScene(
+        mean=np.stack([(u - 255.5) * z / f, (v - 135.5) * z / f, z]).astype(np.float32),
+        scale=(sig * z / f).astype(np.float32), rot=q.astype(np.float32), opacity=o.astype(np.float32),
+        rgb=rng.uniform(0, 1, (3, n)).astype(np.float32),
+        feat=rng.normal(size=(nf, n)).astype(np.float32) if nf else None)
+    cam = synth.Camera(512, 272, f, f, 255.5, 135.5, np.eye(3, 4, dtype=np.float32))
+    _check(sc, cam, nf, "large view n=%d nf=%d" % (n, nf), 0.01)
