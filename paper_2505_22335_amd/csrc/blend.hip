@@ -84,21 +84,28 @@ struct SRec<20> {
   ASGS_DEV void keep() const { asm volatile("" ::"s"(g[7])); }
 };
 
-constexpr int kFwdRound = 256;    // list entries per round
 // Views of up to this many tiles cut a round's list into four parts, a wave
 // each, larger ones into two (a rule on the view alone: its images do not depend
 // on the views rendered with it). Few tiles leave the chip to the chains of the
-// longest lists: 80 tiles of 50k entries 50 us with two waves, 38 with four; 300
-// tiles of 20k anchors 49 and 38; eight such views of 50k 208 and 163; 475 tiles
-// of 5k anchors 18 and 15. Beyond, more waves only add their share of the rounds
-// where lists are short: 690 tiles of 3k anchors 12 and 15, of 50k 95 and 75;
-// 1200 tiles of 130 entries 32 and 38, of 645 160 both.
+// longest lists: 80 tiles of 50k entries 42 us with two waves, 38 with four; 300
+// tiles of 20k anchors 97 and 82; eight such views of 50k 194 and 162 (where they
+// look through a volume, the hidden entries that later waves composite cost more:
+// 217 and 270); 475 tiles of 5k anchors 25 and 20. Beyond, more waves only add
+// their share of the rounds: 690 tiles of 3k anchors 16 and 20, of 50k 98 and 117;
+// 1200 tiles of 130 entries 32 and 38.
 constexpr int kFwdSmallView = 512;
+// List entries per round: what the later waves composite behind the point where
+// the pixels stop is lost, and a round costs two barriers. Two parts, rounds of
+// 256, 192, 128 and 64: 640x480 surfaces 32, 32, 32 and 34.5 us, volume 101, 96, 89
+// and 86, 1M Gaussians 158, -, 144 and 142, 1920x1080 308, -, 291 and 287. Four
+// parts, rounds of 256, 192 and 128: eight keyframes 162, 167 and 175, 80 tiles 38,
+// 37 and 35, one view of 80 volume tiles 151, 145 and 164.
+constexpr int fwd_round(int parts) { return parts > 2 ? 256 : 128; }
 constexpr int kSplitMin = 16;     // a round's quarter list shorter than this stays on the front wave
 
 // Forward compositing, one workgroup of two or four waves per 8x8 quarter of a
-// tile. Per round of up to 256 list entries, the entries that can reach one of
-// the quarter's pixels (the sort's quarter masks) are split in list order into a
+// tile. Per round of the list, the entries that can reach one of the quarter's
+// pixels (the sort's quarter masks) are split in list order into a
 // part per wave: the front wave composites the first part onto the running
 // state (T, channels, last contributor), the others theirs from T = 1 at the
 // same time, all with the records in scalar registers (requested one entry
@@ -114,8 +121,8 @@ constexpr int kSplitMin = 16;     // a round's quarter list shorter than this st
 // tiles, by the longest lists. One 512-thread workgroup per tile with the
 // records and an FP64 box test per entry staged through LDS waited at its
 // barriers two thirds of the time: one 640x480 view of 157k intersections
-// 48 us, now 32 us; 774k intersections 265 us, now 158; eight 320x240 views
-// with 986k 337 us, now 163; 80 tiles of 50k (no features) 70 us, now 38.
+// 48 us, now 32 us; 774k intersections 265 us, now 144; eight 320x240 views
+// with 986k 337 us, now 162; 80 tiles of 50k (no features) 70 us, now 38.
 //
 // With L1, the output stage also forms the weighted L1 residual of the maps
 // against the targets and its gradient (the terms of the L1 loss kernel, in
@@ -126,6 +133,7 @@ template <int NF, bool L1, int NW>
 __global__ void __launch_bounds__(64 * NW) k_blend_fwd(RenderConst rc, const ViewDev* __restrict__ views,
                                                            char* ctx, CtxLayout L, asgs_images out, BlendL1 l1) {
   constexpr int CS = 4 + NF;
+  constexpr int kRound = fwd_round(NW);
   // 32 consecutive workgroups are the four quarters of eight tiles, those of a
   // tile eight apart, so that they share an XCD's L2 (workgroups go to the
   // XCDs round-robin)
@@ -149,6 +157,7 @@ __global__ void __launch_bounds__(64 * NW) k_blend_fwd(RenderConst rc, const Vie
   const uint2 rg = make_uint2(bi.y, bi.z);
   const int P = NW > 2 && V.TX * V.TY <= kFwdSmallView ? NW : 2;  // parts of a round's list
   if (wv >= P) return;  // a larger view among small ones (a barrier waits for the waves that are left)
+  const uint32_t round = P > 2 ? kRound : fwd_round(2);
   prioritise(bpos, rc.n_cu);
   const uint32_t* pairgid = ctx_ptr<const uint32_t>(ctx, L.pairgid);
   const float* geom = ctx_ptr<const float>(ctx, L.geom);
@@ -162,7 +171,7 @@ __global__ void __launch_bounds__(64 * NW) k_blend_fwd(RenderConst rc, const Vie
   constexpr int SA = split_first(CS);
   float* sp = ctx_ptr<float>(ctx, L.split) + (size_t)(sl ? (sl & kSplitSlotMask) - 1u : 0u) * split_floats(CS);
 
-  __shared__ uint2 swl[kFwdRound];                  // the quarter's entries of the round (every wave writes the same)
+  __shared__ uint2 swl[kRound];                     // the quarter's entries of the round (every wave writes the same)
   __shared__ float xch[NW - 1][CS + 2][64];  // later parts' state per pixel: T, channels, last
   __shared__ uint64_t qdone;            // front lanes already stopped
 
@@ -242,16 +251,16 @@ __global__ void __launch_bounds__(64 * NW) k_blend_fwd(RenderConst rc, const Vie
   uint32_t seg = 0u, segend = rg.x + seglen;  // current segment and its end
   uint32_t rstep = 0u;                        // entries of the round
   // the round's Gaussian ids and quarter masks, lane l entry 64 k + l
-  uint32_t gid[kFwdRound / 64], msk[kFwdRound / 64];
+  uint32_t gid[kRound / 64], msk[kRound / 64];
   auto fetch = [&](uint32_t base, uint32_t end) {
 #pragma unroll
-    for (int k = 0; k < kFwdRound / 64; ++k) {
+    for (int k = 0; k < kRound / 64; ++k) {
       const uint32_t p = base + 64 * k + lane;
       gid[k] = p < end ? pairgid[p] : 0u;
       msk[k] = p < end ? pmask[p] : 0u;
     }
   };
-  fetch(rg.x, min(rg.y, min(segend, rg.x + kFwdRound)));
+  fetch(rg.x, min(rg.y, min(segend, rg.x + round)));
   for (uint32_t base = rg.x; base < rg.y; base += rstep) {
     {
       const uint64_t dm = __ballot(done);
@@ -260,13 +269,13 @@ __global__ void __launch_bounds__(64 * NW) k_blend_fwd(RenderConst rc, const Vie
     __syncthreads();
     const uint64_t dm = qdone;
     if (!~dm) break;
-    rstep = min((uint32_t)kFwdRound, min(segend, rg.y) - base);
+    rstep = min(round, min(segend, rg.y) - base);
     // the quarter's entries of the round (those that can reach one of its
     // pixels), in list order, compacted into swl (the same list on every wave):
     // the Gaussian and the position in the tile's list plus one
     int n = 0;
 #pragma unroll
-    for (int k = 0; k < kFwdRound / 64; ++k) {
+    for (int k = 0; k < kRound / 64; ++k) {
       const bool mine = (msk[k] >> qd) & 1u;
       const uint64_t bits = __ballot(mine);
       if (mine)
@@ -288,7 +297,7 @@ __global__ void __launch_bounds__(64 * NW) k_blend_fwd(RenderConst rc, const Vie
     }
     {
       const uint32_t nb = base + rstep, nend = nb == segend ? segend + seglen : segend;
-      fetch(nb, min(rg.y, min(nend, nb + kFwdRound)));
+      fetch(nb, min(rg.y, min(nend, nb + round)));
     }
     if (back) {
       T = 1.f;

@@ -245,3 +245,43 @@ def test_list_parts_of_a_large_view(n, nf):
         feat=rng.normal(size=(nf, n)).astype(np.float32) if nf else None)
     cam = synth.Camera(512, 272, f, f, 255.5, 135.5, np.eye(3, 4, dtype=np.float32))
     _check(sc, cam, nf, "large view n=%d nf=%d" % (n, nf), 0.01)
+
+
+@pytest.mark.parametrize("n", [127, 128, 129, 257, 400])
+def test_large_view_among_small_ones(n):
+    """A view of 544 tiles renders the same bits alone and between two small
+    views (whose workgroups have more waves and longer rounds), and so do
+    these."""
+    rng = np.random.default_rng(200 + n)
+    z = rng.uniform(2.0, 4.0, n)
+    f = 100.0
+    u, v = rng.uniform(2.0, 13.0, n), rng.uniform(2.0, 13.0, n)
+    q = rng.normal(size=(4, n))
+    sc = synth.PlainScene(
+        mean=np.stack([(u - 7.5) * z / f, (v - 7.5) * z / f, z]).astype(np.float32),
+        scale=(rng.uniform(2.0, 4.0, (3, n)) * z / f).astype(np.float32), rot=q.astype(np.float32),
+        opacity=np.where(rng.uniform(size=n) < 0.05, 0.9, rng.uniform(0.006, 0.03, n)).astype(np.float32),
+        rgb=rng.uniform(0, 1, (3, n)).astype(np.float32))
+    pose = np.eye(3, 4, dtype=np.float32)
+    cams = [synth.Camera(w, h, f, f, 7.5, 7.5, pose) for w, h in ((16, 16), (512, 272), (40, 24))]
+    g = P.gaussians_to_device(sc.arrays())
+
+    def render(cs):
+        pix = sum(int(c.width) * int(c.height) for c in cs)
+        opts = L.make_opts(0)
+        ctx = torch.empty(L.render_ctx_size(cs, n, opts, 64 * n), dtype=torch.uint8, device="cuda")
+        out = dict(rgb=torch.zeros(3 * pix, device="cuda"), depth=torch.zeros(pix, device="cuda"),
+                   alpha=torch.zeros(pix, device="cuda"))
+        L.render_forward(cs, L.make_gaussians(g, n), opts, L.make_images(out), ctx)
+        torch.cuda.synchronize()
+        return {k: to_np(t) for k, t in out.items()}
+
+    log("case", "large view among small ones n=%d" % n)
+    mixed = render(cams)
+    at = 0
+    for c in cams:
+        one, p = render([c]), int(c.width) * int(c.height)
+        assert one["alpha"].max() > 0.05
+        for k, ch in (("rgb", 3), ("depth", 1), ("alpha", 1)):
+            assert np.array_equal(mixed[k][ch * at:ch * (at + p)], one[k]), (c.width, k)
+        at += p
