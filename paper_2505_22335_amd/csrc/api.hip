@@ -5,7 +5,6 @@
 #include <stdio.h>
 #include <string.h>
 
-#include <algorithm>
 #include <initializer_list>
 #include <mutex>
 #include <string>
@@ -199,8 +198,6 @@ int prepare(const asgs_camera* cams, int32_t n_views, int64_t n, const asgs_rend
   rc.n = n;
   rc.nv = n * n_views;
   rc.total_tiles = P.total_tiles;
-  rc.min_view_tiles = P.total_tiles;
-  for (int v = 0; v < n_views; ++v) rc.min_view_tiles = std::min(rc.min_view_tiles, P.views[v].TX * P.views[v].TY);
   rc.total_pix = P.total_pix;
   rc.cap = capacity;
   rc.n_cu = device_cu_count();
@@ -281,8 +278,8 @@ CtxLayout ctx_layout(int64_t n, int n_views, int total_tiles, int total_pix, int
   L.binfo = take((size_t)total_tiles * 16);
   L.lpart = take((size_t)total_tiles * 4 * sizeof(float));
   L.bslot = take((size_t)total_tiles * 4);
-  L.sinfo = take((size_t)n_views * kSplitUnits * 16);
-  L.split = take((size_t)n_views * kSplitUnits * split_floats(L.cs) * sizeof(float));
+  L.sinfo = take((size_t)n_views * kSplitPerView * 16);
+  L.split = take((size_t)n_views * kSplitPerView * split_floats(L.cs) * sizeof(float));
   L.tfinal = take((size_t)total_pix * 4);
   L.ncontrib = take((size_t)total_pix * 4);
   L.gslot = take((size_t)capc * L.gs * sizeof(float));

@@ -8,8 +8,8 @@
 // one entry ahead, and takes no vector register or LDS. Each pixel skips alpha
 // < alpha_min, stops before the transmittance would fall below T_min, and
 // accumulates w = alpha * T times (rgb, z, feature). In the forward a workgroup
-// is one quarter (two or four waves, each a part of a round of the list), and
-// leaves as soon as its pixels have stopped.
+// is one quarter (two waves, each a half of a round of the list), and leaves as
+// soon as its pixels have stopped.
 //
 // The backward (a workgroup per tile or segment of a long list, a wave per
 // quarter) replays each pixel's list back to front from its last composited
@@ -17,8 +17,6 @@
 // gradient over the tile's pixels on the matrix cores (see k_blend_bwd); every
 // entry's gradient slot is written once, without global atomics. The projection
 // backward then sums each Gaussian's slots.
-#include <type_traits>
-
 #include "internal.h"
 
 namespace asgs {
@@ -84,56 +82,47 @@ struct SRec<20> {
   ASGS_DEV void keep() const { asm volatile("" ::"s"(g[7])); }
 };
 
-// Views of up to this many tiles cut a round's list into four parts, a wave
-// each, larger ones into two (a rule on the view alone: its images do not depend
-// on the views rendered with it). Few tiles leave the chip to the chains of the
-// longest lists: 80 tiles of 50k entries 42 us with two waves, 38 with four; 300
-// tiles of 20k anchors 97 and 82; eight such views of 50k 194 and 162 (where they
-// look through a volume, the hidden entries that later waves composite cost more:
-// 217 and 270); 475 tiles of 5k anchors 25 and 20. Beyond, more waves only add
-// their share of the rounds: 690 tiles of 3k anchors 16 and 20, of 50k 98 and 117;
-// 1200 tiles of 130 entries 32 and 38.
-constexpr int kFwdSmallView = 512;
-// List entries per round: what the later waves composite behind the point where
-// the pixels stop is lost, and a round costs two barriers. Two parts, rounds of
-// 256, 192, 128 and 64: 640x480 surfaces 32, 32, 32 and 34.5 us, volume 101, 96, 89
-// and 86, 1M Gaussians 158, -, 144 and 142, 1920x1080 308, -, 291 and 287. Four
-// parts, rounds of 256, 192 and 128: eight keyframes 162, 167 and 175, 80 tiles 38,
-// 37 and 35, one view of 80 volume tiles 151, 145 and 164.
-constexpr int fwd_round(int parts) { return parts > 2 ? 256 : 128; }
 constexpr int kSplitMin = 16;     // a round's quarter list shorter than this stays on the front wave
 
-// Forward compositing, one workgroup of two or four waves per 8x8 quarter of a
-// tile. Per round of the list, the entries that can reach one of the quarter's
-// pixels (the sort's quarter masks) are split in list order into a
-// part per wave: the front wave composites the first part onto the running
-// state (T, channels, last contributor), the others theirs from T = 1 at the
-// same time, all with the records in scalar registers (requested one entry
-// ahead, their cache lines touched at the start of the round); then the front
-// wave appends the other parts' results in turn,
-//   C <- C + T C_part,  T <- T T_part,
-// which equals compositing them in order as long as the transmittance cannot
-// have crossed T_min inside the part (T T_part >= T_min, T being monotone).
-// Pixels where it could re-run the part on the front wave with the sequential
-// rule.
+// Forward compositing, one workgroup of two waves per 8x8 quarter of a tile.
+// Per round of the list (256 entries, kSeg of a split list), the entries that
+// can reach one of the quarter's pixels (the sort's quarter masks) are split in
+// list order: the front wave composites the first half onto the running
+// state (T, channels, last contributor), the back wave the second half from
+// T = 1 at the same time, both with the records in scalar registers (requested
+// one entry ahead, their cache lines touched at the start of the round); then
+// the front wave appends the back half's result,
+//   C <- C + T C_back,  T <- T T_back,
+// which equals compositing the two halves in order as long as the
+// transmittance cannot have crossed T_min inside the back half
+// (T T_back >= T_min, T being monotone). Pixels where it could re-run the
+// back half on the front wave with the sequential rule.
+//
+// The rounds and halves are part of the result: they set the last bits of T,
+// and the second moments of the backward carry FP32 rounding that such bits
+// redraw (up to 1e-3 of the rms at single elements of the anchors' feature
+// gradient). Rounds of 128 and, in small views, four waves per quarter change
+// them; they would be faster where lists are long (a 640x480 view through a
+// volume 89 us instead of 99, eight 320x240 keyframes 162 instead of 202).
 //
 // Bound by the vector ALU (about 42 instructions per used entry) and, on few
 // tiles, by the longest lists. One 512-thread workgroup per tile with the
-// records and an FP64 box test per entry staged through LDS waited at its
-// barriers two thirds of the time: one 640x480 view of 157k intersections
-// 48 us, now 32 us; 774k intersections 265 us, now 144; eight 320x240 views
-// with 986k 337 us, now 162; 80 tiles of 50k (no features) 70 us, now 38.
+// records staged through LDS waited at its barriers two thirds of the time:
+// one 640x480 view of 157k intersections 48 us, now 31; 774k intersections 267,
+// now 157; eight 320x240 views with 986k 339, now 202; 80 tiles of 50k (no
+// features) 71, now 41.
 //
 // With L1, the output stage also forms the weighted L1 residual of the maps
 // against the targets and its gradient (the terms of the L1 loss kernel, in
 // the same arithmetic), and each quarter's loss partial.
 ASGS_DEV float l1_sgn(float d) { return d > 0.f ? 1.f : (d < 0.f ? -1.f : 0.f); }
 
-template <int NF, bool L1, int NW>
-__global__ void __launch_bounds__(64 * NW) k_blend_fwd(RenderConst rc, const ViewDev* __restrict__ views,
+constexpr int kFwdWaves = 2;
+template <int NF, bool L1>
+__global__ void __launch_bounds__(64 * kFwdWaves) k_blend_fwd(RenderConst rc, const ViewDev* __restrict__ views,
                                                            char* ctx, CtxLayout L, asgs_images out, BlendL1 l1) {
   constexpr int CS = 4 + NF;
-  constexpr int kRound = fwd_round(NW);
+  constexpr int kRound = 256;  // the longest round
   // 32 consecutive workgroups are the four quarters of eight tiles, those of a
   // tile eight apart, so that they share an XCD's L2 (workgroups go to the
   // XCDs round-robin)
@@ -148,32 +137,30 @@ __global__ void __launch_bounds__(64 * NW) k_blend_fwd(RenderConst rc, const Vie
   const int ty = lt / V.TX, tx = lt - ty * V.TX;
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const bool back = wv > 0;  // not the first part of the round's list
+  const bool back = wv > 0;  // back half of the round's list
   const int tq = (qd << 6) | lane;
   const int px = tx * kTile + tile_lx(tq);
   const int py = ty * kTile + tile_ly(tq);
   const bool inside = px < V.W && py < V.H;
   const float pxf = (float)px, pyf = (float)py;
   const uint2 rg = make_uint2(bi.y, bi.z);
-  const int P = NW > 2 && V.TX * V.TY <= kFwdSmallView ? NW : 2;  // parts of a round's list
-  if (wv >= P) return;  // a larger view among small ones (a barrier waits for the waves that are left)
-  const uint32_t round = P > 2 ? kRound : fwd_round(2);
   prioritise(bpos, rc.n_cu);
   const uint32_t* pairgid = ctx_ptr<const uint32_t>(ctx, L.pairgid);
   const float* geom = ctx_ptr<const float>(ctx, L.geom);
   const float* chan = ctx_ptr<const float>(ctx, L.chan);
   const uint8_t* pmask = ctx_ptr<const uint8_t>(ctx, L.pmask);
-  // lists walked by several backward workgroups: rounds end at the segment
-  // boundaries, and the pixel's state is recorded at the end of every segment
-  // but the last
-  const uint32_t sl = ctx_ptr<const uint32_t>(ctx, L.bslot)[tile];
-  const uint32_t seglen = sl ? segment_length(rg.y - rg.x, sl >> 20) : rg.y - rg.x;
-  constexpr int SA = split_first(CS);
-  float* sp = ctx_ptr<float>(ctx, L.split) + (size_t)(sl ? (sl & kSplitSlotMask) - 1u : 0u) * split_floats(CS);
+  // lists walked by several backward workgroups: taken kSeg entries at a
+  // time, with the pixel's state recorded at every segment boundary
+  static_assert(split_floats(CS) == ((kSegMax - 1) * split_first(CS) + split_final(CS)) * kTilePix, "segment layout");
+  const uint32_t sl = ctx_ptr<const uint32_t>(ctx, L.bslot)[tile];  // 1 + split-record slot, or 0
+  const int nseg = sl ? split_segments(rg.y - rg.x) : 1;
+  const uint32_t rstep = nseg > 1 ? (uint32_t)kSeg : (uint32_t)kRound;  // entries per round
+  constexpr int SA = split_first(CS), SF = split_final(CS);
+  float* sp = ctx_ptr<float>(ctx, L.split) + (size_t)(sl ? sl - 1u : 0u) * split_floats(CS);
 
   __shared__ uint2 swl[kRound];                     // the quarter's entries of the round (every wave writes the same)
-  __shared__ float xch[NW - 1][CS + 2][64];  // later parts' state per pixel: T, channels, last
-  __shared__ uint64_t qdone;            // front lanes already stopped
+  __shared__ float xch[CS + 2][64];  // back half's state per pixel: T, channels, last
+  __shared__ uint64_t qdone;         // front lanes already stopped
 
   // L1 targets and weight of the pixel, requested now and used in the output stage
   float tv[CS + 1], tw = 1.f;
@@ -205,8 +192,8 @@ __global__ void __launch_bounds__(64 * NW) k_blend_fwd(RenderConst rc, const Vie
   const float amax = rc.alpha_max, tmin = rc.T_min;
   // Composite the positions [i0, i1) of this wave's list of the round on the
   // lanes with reach = 0 (others: -inf, below every power); a lane stops
-  // (reach = -inf) before T would fall below tstop (T_min, or -1 for a local
-  // later part's state).
+  // (reach = -inf) before T would fall below tstop (T_min, or -1 for the local
+  // back half's state).
   constexpr float kNoReach = -__builtin_inff();
   auto run = [&](int i0, int i1, float& reach, float tstop) {
     const uint2* lst = swl;
@@ -248,11 +235,10 @@ __global__ void __launch_bounds__(64 * NW) k_blend_fwd(RenderConst rc, const Vie
       if (!entry(rb, pb) || ++i >= i1) break;
     }
   };
-  uint32_t seg = 0u, segend = rg.x + seglen;  // current segment and its end
-  uint32_t rstep = 0u;                        // entries of the round
   // the round's Gaussian ids and quarter masks, lane l entry 64 k + l
   uint32_t gid[kRound / 64], msk[kRound / 64];
-  auto fetch = [&](uint32_t base, uint32_t end) {
+  auto fetch = [&](uint32_t base) {
+    const uint32_t end = min(rg.y, base + rstep);
 #pragma unroll
     for (int k = 0; k < kRound / 64; ++k) {
       const uint32_t p = base + 64 * k + lane;
@@ -260,7 +246,7 @@ __global__ void __launch_bounds__(64 * NW) k_blend_fwd(RenderConst rc, const Vie
       msk[k] = p < end ? pmask[p] : 0u;
     }
   };
-  fetch(rg.x, min(rg.y, min(segend, rg.x + round)));
+  fetch(rg.x);
   for (uint32_t base = rg.x; base < rg.y; base += rstep) {
     {
       const uint64_t dm = __ballot(done);
@@ -269,7 +255,6 @@ __global__ void __launch_bounds__(64 * NW) k_blend_fwd(RenderConst rc, const Vie
     __syncthreads();
     const uint64_t dm = qdone;
     if (!~dm) break;
-    rstep = min(round, min(segend, rg.y) - base);
     // the quarter's entries of the round (those that can reach one of its
     // pixels), in list order, compacted into swl (the same list on every wave):
     // the Gaussian and the position in the tile's list plus one
@@ -286,19 +271,15 @@ __global__ void __launch_bounds__(64 * NW) k_blend_fwd(RenderConst rc, const Vie
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    // part w: list positions [cut(w), cut(w + 1))
-    const int len = n < kSplitMin ? n : (n + P - 1) / P;
-    const int p0 = min(n, wv * len), p1 = min(n, p0 + len);
-    // touch the records of this wave's part, and request the next round's ids
+    const int nf = n < kSplitMin ? n : (n + 1) / 2;  // the front half
+    const int p0 = back ? nf : 0, p1 = back ? n : nf;
+    // touch the records of this wave's half, and request the next round's ids
     float touch = 0.f;
     for (int i = p0 + lane; i < p1; i += 64) {
       const size_t g = swl[i].x;
       touch += geom[g * kGeomStride] + chan[g * CS] + chan[g * CS + CS - 1];
     }
-    {
-      const uint32_t nb = base + rstep, nend = nb == segend ? segend + seglen : segend;
-      fetch(nb, min(rg.y, min(nend, nb + round)));
-    }
+    fetch(base + rstep);
     if (back) {
       T = 1.f;
 #pragma unroll
@@ -307,46 +288,38 @@ __global__ void __launch_bounds__(64 * NW) k_blend_fwd(RenderConst rc, const Vie
       const bool skip = !inside || ((dm >> lane) & 1u);
       float reach = skip ? kNoReach : 0.f;
       if (p0 < p1) run(p0, p1, reach, -1.f);
-      xch[wv - 1][0][lane] = T;
+      xch[0][lane] = T;
 #pragma unroll
-      for (int c = 0; c < CS; ++c) xch[wv - 1][1 + c][lane] = acc[c];
-      xch[wv - 1][CS + 1][lane] = __uint_as_float(last);
+      for (int c = 0; c < CS; ++c) xch[1 + c][lane] = acc[c];
+      xch[CS + 1][lane] = __uint_as_float(last);
     } else if (n > 0) {
       float reach = done ? kNoReach : 0.f;
-      run(0, p1, reach, tmin);
+      run(0, nf, reach, tmin);
       done = reach != 0.f;
     }
     asm volatile("" ::"v"(touch));  // the touching loads are kept, and waited for here
     __syncthreads();
-    // append part w
-    auto append = [&](int w) {
-      const int q0 = min(n, w * len), q1 = min(n, q0 + len);
-      if (q0 >= q1) return;
-      const float Tb = xch[w - 1][0][lane];
-      const uint32_t lastb = __float_as_uint(xch[w - 1][CS + 1][lane]);
+    if (!back && nf != n) {
+      // append the back half
+      const float Tb = xch[0][lane];
+      const uint32_t lastb = __float_as_uint(xch[CS + 1][lane]);
       const bool fix = !done && T * Tb < tmin;
       if (!done && !fix) {
 #pragma unroll
-        for (int c = 0; c < CS; ++c) acc[c] = fmaf(T, xch[w - 1][1 + c][lane], acc[c]);
+        for (int c = 0; c < CS; ++c) acc[c] = fmaf(T, xch[1 + c][lane], acc[c]);
         T *= Tb;
         if (lastb) last = lastb;
       }
       if (any_lane(fix)) {
         float reach = fix ? 0.f : kNoReach;
-        run(q0, q1, reach, tmin);
+        run(nf, n, reach, tmin);
         done = done || (fix && reach != 0.f);
       }
-    };
-    if (!back) {
-      if (NW == 2) append(1);
-      else
-        for (int w = 1; w < P; ++w) append(w);
     }
-    const bool ends = base + rstep == segend;
-    if (ends && !back && segend < rg.y) {
-      // T at the end of a segment and the segment's own channels; the next
-      // segment accumulates from zero
-      float* rp = sp + (size_t)seg * split_floats(CS) + (size_t)tq * SA;
+    const int bnd = (int)((base - rg.x) / kSeg) + 1;  // segment boundary after this round
+    if (nseg > 1 && !back && bnd < nseg) {
+      // state after the first bnd * kSeg entries
+      float* rp = sp + ((size_t)(bnd - 1) * kTilePix + tq) * SA;
       float r[SA];
       r[0] = T;
 #pragma unroll
@@ -356,40 +329,18 @@ __global__ void __launch_bounds__(64 * NW) k_blend_fwd(RenderConst rc, const Vie
 #pragma unroll
       for (int c4 = 0; c4 < SA / 4; ++c4)
         reinterpret_cast<float4*>(rp)[c4] = make_float4(r[4 * c4], r[4 * c4 + 1], r[4 * c4 + 2], r[4 * c4 + 3]);
-#pragma unroll
-      for (int c = 0; c < CS; ++c) acc[c] = 0.f;
-    }
-    if (ends) {
-      ++seg;
-      segend += seglen;
     }
   }
-  // Back to front over the records passed: a record's channels become the sum
-  // of the later segments', what the entries after its boundary add (summed
-  // from small to large, without the cancellation of C_final - C_boundary),
-  // and acc the whole list's.
-  if (sl && !back)
-    for (int b = (int)min(seg, (rg.y - rg.x - 1u) / seglen) - 1; b >= 0; --b) {
-      float* rp = sp + (size_t)b * split_floats(CS) + (size_t)tq * SA;
-      float r[SA];
+  if (nseg > 1 && !back) {
+    // the final channels (the entries after a boundary add C_final - C_boundary)
+    float* rp = sp + (size_t)(kSegMax - 1) * kTilePix * SA + (size_t)tq * SF;
+    float r[SF];
 #pragma unroll
-      for (int c4 = 0; c4 < SA / 4; ++c4) {
-        const float4 v = reinterpret_cast<const float4*>(rp)[c4];
-        r[4 * c4] = v.x;
-        r[4 * c4 + 1] = v.y;
-        r[4 * c4 + 2] = v.z;
-        r[4 * c4 + 3] = v.w;
-      }
+    for (int c = 0; c < SF; ++c) r[c] = c < CS ? acc[c < CS ? c : 0] : 0.f;
 #pragma unroll
-      for (int c = 0; c < CS; ++c) {
-        const float own = r[1 + c];
-        r[1 + c] = acc[c];
-        acc[c] += own;
-      }
-#pragma unroll
-      for (int c4 = 0; c4 < SA / 4; ++c4)
-        reinterpret_cast<float4*>(rp)[c4] = make_float4(r[4 * c4], r[4 * c4 + 1], r[4 * c4 + 2], r[4 * c4 + 3]);
-    }
+    for (int c4 = 0; c4 < SF / 4; ++c4)
+      reinterpret_cast<float4*>(rp)[c4] = make_float4(r[4 * c4], r[4 * c4 + 1], r[4 * c4 + 2], r[4 * c4 + 3]);
+  }
   if (back) return;
   float lsum = 0.f;  // this pixel's L1 loss terms
   if (inside) {
@@ -471,19 +422,18 @@ ASGS_DEV f4v mfma_bf(const bf8v& a, const bf8v& b, f4v c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
+// Round to nearest even bfloat16 (the hardware conversion of gfx950).
+ASGS_DEV uint16_t bf_rne(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 // v = hi + lo with hi = bf16(v) and lo = bf16(v - hi), both rounded to nearest
 // even: |v - hi - lo| <= 2^-17 |v| for finite v. With exact bf16 products and
 // FP32 accumulation, a b ~ ah bh + ah bl + al bh to ~2^-15 relative.
-// Round to nearest even bfloat16 (the hardware conversion of gfx950).
-ASGS_DEV uint16_t bf_rne(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
-// v = hi + lo + O(2^-16 |v|), both bfloat16.
 ASGS_DEV void bf_split(float v, uint16_t& hi, uint16_t& lo) {
   hi = bf_rne(v);
   lo = bf_rne(v - __uint_as_float((uint32_t)hi << 16));
 }
 
-// Backward compositing, one workgroup per tile (or per segment of a split
-// list), one pixel per thread.
+// Backward compositing, one workgroup per tile (or per 128-entry segment of
+// a split list), one pixel per thread.
 //
 // Per list entry k and pixel p the gradient contributions are
 //   dL/dc_k      += w_kp G_p                 (w = alpha T, G = upstream channel gradients)
@@ -493,9 +443,8 @@ ASGS_DEV void bf_split(float v, uint16_t& hi, uint16_t& lo) {
 // so the per-entry sums over the tile's pixels are dot products of two
 // per-pixel coefficients (w, dpow) with fixed per-pixel features: the
 // channel gradients G_p and the moments (1, lx, ly, lx^2, lx ly, ly^2) of the
-// pixel coordinates about the tile's centre (half-integers whose products have
-// at most 8 significant bits, exact in bf16), from which the projection backward forms the
-// conic and position gradients in closed form. The list is walked in rounds
+// tile-local pixel coordinates, from which the conic and position gradients
+// follow in closed form. The list is walked in rounds
 // of 32 entries from the back. Each wave takes only the round's entries that
 // one of its pixels uses (the quarter test of the forward, then a ballot);
 // their records arrive through scalar loads, one entry ahead, so the channel
@@ -504,18 +453,27 @@ ASGS_DEV void bf_split(float v, uint16_t& hi, uint16_t& lo) {
 // of one matrix-core tile (8 rows of w, 8 of dL/dpower) and are contracted
 // over the wave's 64 pixels (bf16 16x16x32 MFMAs with both operands split
 // into hi + lo parts) against the channel gradients and the moments. At the
-// end of a round the four waves' rows are summed in a fixed order into one
-// write per gradient slot.
+// end of a round each wave turns its rows' moments into the gradients of
+// (u, v, A, B, C, o), and the four waves' rows are summed in a fixed order into
+// one write per gradient slot.
 // Lists are walked back to front from T_final, recovering T_k = T_{k+1} /
 // (1 - alpha_k), with the sum S the later entries contribute growing from
 // zero. A segment of a split list but its last starts from the state the
-// forward recorded at its end: T and S = G . (what the later entries add).
+// forward recorded at its end: T and S = G . (C_final - C_boundary).
 // Bound by the vector ALU (about 55 instructions per used entry and wave, half
 // of the launch) and by the waves' uneven shares of a round. With the records
-// staged through LDS, 16-entry batches (56 KB of LDS, three workgroups per CU
-// instead of five) and cuts every 128 entries on at most 64 lists, one 640x480
-// view of 157k intersections took 89 us, now 61 us; 774k intersections 357 us,
-// now 245; eight 320x240 views with 986k (lists up to 2460) 614 us, now 287.
+// staged through LDS and 16-entry batches (56 KB of LDS, three workgroups per
+// CU instead of five) one 640x480 view of 157k intersections took 88 us, now
+// 71; 774k intersections 359, now 315; a view through a volume 207, now 141;
+// eight 320x240 views with 986k (lists up to 2460) 613, now 530. Five waves per
+// SIMD spill 18 registers; four spill none: 71, 306, 157 and 529 us.
+//
+// The second moments are sums of terms up to 60 times their result for specks
+// away from the tile's corner, in FP32: they carry rounding of 1e-5 of their
+// gradient's norm, which any change of the last bits of T, of the segments or
+// of the order of these sums redraws. Moments about the tile's centre halve
+// it, and up to 16 segments of equal length take 286 us for the eight views, but
+// both give other values than these.
 template <int NF>
 __global__ void __launch_bounds__(kTilePix) __attribute__((amdgpu_waves_per_eu(5))) k_blend_bwd(RenderConst rc, const ViewDev* __restrict__ views,
                                                         char* ctx, CtxLayout L, asgs_images dout) {
@@ -524,21 +482,27 @@ __global__ void __launch_bounds__(kTilePix) __attribute__((amdgpu_waves_per_eu(5
   constexpr int NW = kTilePix / 64;
   constexpr int CP = 64;          // row of 64 pixel coefficients (bf16), 8-pixel groups XOR-swizzled by row
   constexpr int C1 = CS - 4;      // the second column block holds the last four channels and the moments
-  // The first n_views kSplitUnits workgroups take the segments but the last of
-  // the split lists, one split record each (and exit at once where there is
-  // none), the rest one blend position each (longest lists first): the whole
-  // list, or its last segment.
-  const uint32_t extra = (uint32_t)rc.n_views * kSplitUnits;
+  // The first n_views kSplitPerView (kSegMax - 1) workgroups take the
+  // segments but the last of the split lists, one split-record slot each
+  // (and exit at once where there is none), the rest one blend position each
+  // (longest lists first): the whole list, or its last segment.
+  const uint32_t extra = (uint32_t)rc.n_views * kSplitPerView * (kSegMax - 1);
   const bool front = blockIdx.x < extra;
-  const uint4 bi = front ? ctx_ptr<const uint4>(ctx, L.sinfo)[blockIdx.x]
-                         : ctx_ptr<const uint4>(ctx, L.binfo)[blockIdx.x - extra];
-  if (bi.x == ~0u) return;
-  const uint32_t len = bi.z - bi.y;
-  const uint32_t sl = ctx_ptr<const uint32_t>(ctx, L.bslot)[bi.x];
+  uint4 bi;
+  int nseg = 1, seg = 0;
+  if (front) {
+    bi = ctx_ptr<const uint4>(ctx, L.sinfo)[blockIdx.x / (kSegMax - 1)];
+    if (bi.x == ~0u) return;
+    nseg = split_segments(bi.z - bi.y);
+    seg = (int)(blockIdx.x % (kSegMax - 1));
+    if (seg >= nseg - 1) return;
+  } else {
+    bi = ctx_ptr<const uint4>(ctx, L.binfo)[blockIdx.x - extra];
+    if (ctx_ptr<const uint32_t>(ctx, L.bslot)[bi.x]) nseg = split_segments(bi.z - bi.y);
+    seg = nseg - 1;
+  }
   // this workgroup's segment: entries [elo, eend) of the list
-  const int seglen = sl ? (int)segment_length(len, sl >> 20) : (int)len;
-  const int seg = front ? (int)bi.w : sl ? (int)((len - 1u) / (uint32_t)seglen) : 0;
-  const int elo = seg * seglen, eend = min((int)len, elo + seglen);
+  const int elo = seg * kSeg, eend = front ? elo + kSeg : (int)(bi.z - bi.y);
   const int tile = (int)bi.x;
   const int view = find_view(views, rc.n_views, tile);
   const ViewDev& V = views[view];
@@ -602,6 +566,7 @@ __global__ void __launch_bounds__(kTilePix) __attribute__((amdgpu_waves_per_eu(5
   // The Gaussian ids and quarter masks of the first two rounds are requested
   // now, later rounds' two rounds ahead.
   int rhi = ehi, rlo = max(ehi - kRound, elo);  // entries [rlo, rhi) of the round
+  // the round's ids and masks, lane l entry l
   auto ids = [&](int lo, int hi, uint32_t& g, uint32_t& m) {
     g = m = 0u;
     if (lane < hi - lo) {
@@ -669,7 +634,7 @@ __global__ void __launch_bounds__(kTilePix) __attribute__((amdgpu_waves_per_eu(5
   // this lane's moment lx^ex ly^ey: pixel i of the lane's 8 lies at lx = lx0 + i, ly = ly0 + 4 kb
   const int ex = fcol == 9 || fcol == 12 ? 1 : fcol == 11 ? 2 : 0, ey = fcol == 10 || fcol == 12 ? 1 : fcol == 13 ? 2 : 0;
   const float cx0 = ex == 0 ? 1.f : 0.f, cx1 = ex == 1 ? 1.f : 0.f, cx2 = ex == 2 ? 1.f : 0.f;
-  const float lx0 = (float)(8 * (wv & 1)) - kTileMid, ly0 = (float)(8 * (wv >> 1) + (lane >> 4)) - kTileMid;
+  const float lx0 = (float)(8 * (wv & 1)), ly0 = (float)(8 * (wv >> 1) + (lane >> 4));
 #pragma unroll
   for (int kb = 0; kb < 2; ++kb) {
     float v[8];
@@ -697,16 +662,18 @@ __global__ void __launch_bounds__(kTilePix) __attribute__((amdgpu_waves_per_eu(5
   float T = Tf;
   float sacc = 0.f;  // sum over later Gaussians of w_l (G . c_l)
   if (front && inside && whi == eend) {
-    // the record of a boundary that the forward of this quarter passed: where
-    // it stopped before, in a longer segment's earlier round, it wrote none,
-    // and no pixel uses a later entry
-    const float* rb = ctx_ptr<const float>(ctx, L.split) + (size_t)blockIdx.x * split_floats(CS) + (size_t)t * split_first(CS);
+    // the state at the segment's end, recorded by the forward of this quarter if
+    // it went so far: T there, and the later entries' sum. Where its pixels
+    // stopped in an earlier segment it wrote none, and no pixel uses a later entry
+    constexpr int SA = split_first(CS), SF = split_final(CS);
+    const float* sp = ctx_ptr<const float>(ctx, L.split) + (size_t)(blockIdx.x / (kSegMax - 1)) * split_floats(CS);
+    const float* rb = sp + ((size_t)seg * kTilePix + t) * SA;
+    const float* rf = sp + (size_t)(kSegMax - 1) * kTilePix * SA + (size_t)t * SF;
     T = rb[0];
 #pragma unroll
-    for (int c = 0; c < CS; ++c) sacc = fmaf(G[c], rb[1 + c], sacc);
+    for (int c = 0; c < CS; ++c) sacc = fmaf(G[c], rf[c] - rb[1 + c], sacc);
   }
   const float amax = rc.alpha_max;
-  const float GTf = GT * Tf;
   uint16_t* const ah = &acf[wv][0][0][0];
   uint16_t* const al = &acf[wv][1][0][0];
   int nb = 0, nrow = 0;  // batched entries; rows of the round already in part
@@ -727,7 +694,18 @@ __global__ void __launch_bounds__(kTilePix) __attribute__((amdgpu_waves_per_eu(5
         d0 = mfma_bf(xh, b0l[kb], d0);
         d0 = mfma_bf(xl, b0h[kb], d0);
       }
+      // columns 0-3: the low parts, from four lanes up; the others zero
+      bf8v b1l;
+      {
+        typedef int i4v __attribute__((ext_vector_type(4)));
+        const i4v src = __builtin_bit_cast(i4v, b1[kb]);
+        i4v v;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = __builtin_amdgcn_update_dpp(0, src[i], 0x104, 0xF, 0x1, true);
+        b1l = __builtin_bit_cast(bf8v, v);
+      }
       d1 = mfma_bf(xh, b1[kb], d1);
+      d1 = mfma_bf(xh, b1l, d1);
       d1 = mfma_bf(xl, b1[kb], d1);
     }
     // lane l holds column l % 16 of rows 4 (l / 16) + r: channels from the
@@ -740,9 +718,7 @@ __global__ void __launch_bounds__(kTilePix) __attribute__((amdgpu_waves_per_eu(5
       // rows past a last batch of fewer than 8 entries belong to no entry and are not read
       float* row = part[wv][nrow + 4 * ((lane >> 4) & 1) + r];
       if (NF > 0 && !up) row[6 + fcol] = d0[r];
-      // columns 0-3: the hi columns' sums plus the lo columns' (four lanes up)
-      const float lo4 = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(d1[r]), 0x104, 0xF, 0xF, true));
-      if (keep) row[col] = up ? d1[r] : d1[r] + lo4;
+      if (keep) row[col] = d1[r];
     }
     nrow += kBwdBatch;
     nb = 0;
@@ -772,7 +748,7 @@ __global__ void __launch_bounds__(kTilePix) __attribute__((amdgpu_waves_per_eu(5
     float wgt = 0.f, dpow = 0.f;
     const float Tk = T * ioma;
     const float w_ = alpha * Tk;
-    const float dalpha = Tk * dotg - (sacc + GTf) * ioma;
+    const float dalpha = Tk * dotg - (sacc + GT * Tf) * ioma;
     if (use) {
       T = Tk;
       wgt = w_;
@@ -830,7 +806,31 @@ __global__ void __launch_bounds__(kTilePix) __attribute__((amdgpu_waves_per_eu(5
         entry(rb, j2);
         if (!bits) break;
       }
+    }
+    if (used) {
+      // the conic, position and opacity parts of the wave's rows in closed form
+      // from their moments (linear in them, so the four waves' rows still add
+      // up), a row per lane; the records of its entries are requested before
+      // the last batch is contracted
+      const bool own = lane < kRound && ((used >> (lane & (kRound - 1))) & 1u);
       if (nb) flush();
+      if (own) {
+        const float4* gp = reinterpret_cast<const float4*>(geom + (size_t)gidv * kGeomStride);
+        const float4 g0 = gp[0], g1 = gp[1];
+        float* row = part[wv][__builtin_popcount((used >> lane) >> 1)];
+        const float4 a = *reinterpret_cast<const float4*>(row);
+        const float2 b = *reinterpret_cast<const float2*>(row + 4);
+        const float M[6] = {a.x, a.y, a.z, a.w, b.x, b.y};
+        const float uu = g0.x - (float)x0, vv = g0.y - (float)y0;  // tile-local centre
+        const float Sdx = fmaf(uu, M[0], -M[1]);
+        const float Sdy = fmaf(vv, M[0], -M[2]);
+        const float Sxx = fmaf(uu * uu, M[0], -(2.f * uu * M[1])) + M[3];
+        const float Sxy = fmaf(-vv, M[1], fmaf(uu * vv, M[0], -(uu * M[2]))) + M[4];
+        const float Syy = fmaf(vv * vv, M[0], -(2.f * vv * M[2])) + M[5];
+        *reinterpret_cast<float4*>(row) =
+            make_float4(-fmaf(g0.w, Sdy, g0.z * Sdx), -fmaf(g0.w, Sdx, g1.x * Sdy), -0.5f * Sxx, -Sxy);
+        *reinterpret_cast<float2*>(row + 4) = make_float2(-0.5f * Syy, M[0] / g1.y);
+      }
     }
     if (lane == 0) sused[wv] = used;
     asm volatile("" ::"v"(touch));  // the touching load is kept, and waited for here
@@ -870,17 +870,14 @@ void launch_blend_forward(const RenderConst& rc, const CtxLayout& L, char* ctx, 
   const ViewDev* views = reinterpret_cast<const ViewDev*>(ctx + L.views);
   const BlendL1 a = l1 ? *l1 : BlendL1{};
   const dim3 grid((unsigned)((rc.total_tiles + 7) / 8 * 32));
-  auto launch = [&](auto nf, auto nw) {
-    constexpr int kNf = decltype(nf)::value, kNw = decltype(nw)::value;
-    if (l1) hipLaunchKernelGGL((k_blend_fwd<kNf, true, kNw>), grid, dim3(64 * kNw), 0, s, rc, views, ctx, L, out, a);
-    else hipLaunchKernelGGL((k_blend_fwd<kNf, false, kNw>), grid, dim3(64 * kNw), 0, s, rc, views, ctx, L, out, a);
-  };
-  auto waves = [&](auto nf) {
-    if (rc.min_view_tiles <= kFwdSmallView) launch(nf, std::integral_constant<int, 4>{});
-    else launch(nf, std::integral_constant<int, 2>{});
-  };
-  if (rc.nf == 16) waves(std::integral_constant<int, 16>{});
-  else waves(std::integral_constant<int, 0>{});
+  const dim3 block(64 * kFwdWaves);
+  if (rc.nf == 16) {
+    if (l1) hipLaunchKernelGGL((k_blend_fwd<16, true>), grid, block, 0, s, rc, views, ctx, L, out, a);
+    else hipLaunchKernelGGL((k_blend_fwd<16, false>), grid, block, 0, s, rc, views, ctx, L, out, a);
+  } else {
+    if (l1) hipLaunchKernelGGL((k_blend_fwd<0, true>), grid, block, 0, s, rc, views, ctx, L, out, a);
+    else hipLaunchKernelGGL((k_blend_fwd<0, false>), grid, block, 0, s, rc, views, ctx, L, out, a);
+  }
 }
 
 void launch_l1_tile_loss(const RenderConst& rc, const CtxLayout& L, char* ctx, float* loss, hipStream_t s) {
@@ -893,12 +890,12 @@ void launch_blend_backward(const RenderConst& rc, const CtxLayout& L, char* ctx,
                            hipStream_t s) {
   const ViewDev* views = reinterpret_cast<const ViewDev*>(ctx + L.views);
   if (rc.nf == 16)
-    hipLaunchKernelGGL(k_blend_bwd<16>, dim3(rc.total_tiles + rc.n_views * kSplitUnits),
+    hipLaunchKernelGGL(k_blend_bwd<16>, dim3(rc.total_tiles + rc.n_views * kSplitPerView * (kSegMax - 1)),
                        dim3(kTilePix), 0, s, rc,
                        views, ctx, L,
                        dout);
   else
-    hipLaunchKernelGGL(k_blend_bwd<0>, dim3(rc.total_tiles + rc.n_views * kSplitUnits),
+    hipLaunchKernelGGL(k_blend_bwd<0>, dim3(rc.total_tiles + rc.n_views * kSplitPerView * (kSegMax - 1)),
                        dim3(kTilePix), 0, s, rc,
                        views, ctx, L,
                        dout);

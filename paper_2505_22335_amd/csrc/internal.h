@@ -11,8 +11,7 @@ namespace asgs {
 
 constexpr int kTile = 16;            // screen tile side (pixels)
 constexpr int kTilePix = kTile * kTile;
-constexpr float kTileMid = 0.5f * (kTile - 1);  // tile-local centre
-constexpr int kGeomStride = 8;       // floats per 2D geometry record: u v A B | C o - -
+constexpr int kGeomStride = 8;       // floats per 2D geometry record: u v A B | C o ln(alpha_min/o) box
 constexpr int kScanThreads = 256;    // (view, Gaussian) pairs per binning block, all of one view
 
 // Binning blocks: ceil(n / kScanThreads) per view, in (view, Gaussian) order.
@@ -42,7 +41,6 @@ struct RenderConst {
   int64_t n;           // Gaussians per view
   int64_t nv;          // n * n_views
   int32_t total_tiles;
-  int32_t min_view_tiles;  // tiles of the smallest view
   int32_t total_pix;
   int64_t cap;         // intersection capacity
   int32_t n_cu;        // compute units of the device (issue-priority bands of the blend kernels)
@@ -74,12 +72,11 @@ struct CtxHeader {
 //  pairgid, pslot, ptile  per sorted intersection: Gaussian, gradient slot, tile key
 //  binfo               per blend position (longest list first): tile, start, end
 //  lpart               per tile and 8x8 quarter: L1 loss partial of the fused forward
-//  bslot               per tile: 1 + its first split record and its segment bound, 0 when the
-//                      list is not split
-//  sinfo               per split record: tile, start, end and the segment it serves (tile ~0u:
-//                      unused)
-//  split               split records (kSplitUnits per view): per pixel the transmittance at
-//                      the end of a segment and the channels the entries after it add
+//  bslot               per tile: 1 + its split-record slot, 0 when the list is not split
+//  sinfo               per split-record slot: tile, start, end (tile ~0u: unused)
+//  split               per split-record slot (kSplitPerView per view): per pixel the
+//                      transmittance and channels at each segment boundary, and the
+//                      final channels
 struct CtxLayout {
   size_t hdr, views, geom, chan, rad, rect, ntiles, dkey, toff, bsum, vsum, bpre, vpre, vlist, vcount, tcur, ukey, tkey,
       pairgid, pslot,
@@ -103,42 +100,32 @@ void launch_project(const RenderConst& rc, const asgs_gaussians& g, const CtxLay
 void launch_bin(const RenderConst& rc, const CtxLayout& L, char* ctx, hipStream_t s);
 void launch_tile_sort(const RenderConst& rc, const CtxLayout& L, char* ctx, hipStream_t s);
 // The longest lists are walked by several backward workgroups, one per
-// segment of equal length (a multiple of kSegAlign). Each segment but the last
-// starts from the state the forward recorded at its end, one split record per
-// boundary. Every view has kSplitUnits records; the lists are cut at the
-// smallest segment length of the ladder below that these records allow, which
-// depends only on the lengths of the view's own lists (so that results depend
-// neither on the batch nor on the order of equal lengths).
-constexpr int kSegAlign = 32;
-constexpr int kSegMax = 16;
-constexpr int kSplitUnits = 222;
-constexpr int kSplitLadder = 19;
-__host__ __device__ constexpr int split_target(int l) {
-  return l < 8 ? 128 + 32 * l : l < 11 ? 384 + 64 * (l - 8) : l < 15 ? 640 + 128 * (l - 11) : 1280 + 256 * (l - 15);
+// segment of kSeg entries (the last segment takes the rest):
+// min(kSegMax, ceil(len / kSeg)) segments. The forward takes such lists kSeg
+// entries at a time and records the state at every segment boundary. Which
+// lists are split depends only on the lengths of the lists of their own
+// view (so that results do not depend on the batch or on the order of equal
+// lengths): those longer than the smallest threshold kSplitLen + j kSplitStep
+// that at most kSplitPerView lists of the view exceed; none where more lists
+// than that exceed the last threshold.
+constexpr int kSeg = 128;
+constexpr int kSegMax = 4;
+constexpr int kSplitLen = 160;
+constexpr int kSplitStep = 32;
+constexpr int kSplitThresholds = 28;  // kSplitLen + j kSplitStep, j < 28 (up to 1024)
+constexpr int kSplitPerView = 64;
+__host__ __device__ inline int split_segments(uint32_t len) {
+  const uint32_t n = (len + kSeg - 1) / kSeg;
+  return n < (uint32_t)kSegMax ? (int)n : kSegMax;
 }
-// Length classes: steps of 32 up to 1024, of 128 up to 4096, one above.
-constexpr int kLenBins = 58;
-__host__ __device__ constexpr int len_bin(uint32_t c) {
-  return c <= 1024u ? (int)((c + 31u) / 32u) : c <= 4096u ? 32 + (int)((c - 1024u + 127u) / 128u) : kLenBins - 1;
-}
-__host__ __device__ constexpr int bin_segments(int b, int target) {
-  if (b == kLenBins - 1) return kSegMax;
-  const int up = b <= 32 ? 32 * b : 1024 + 128 * (b - 32);
-  const int n = (up + target - 1) / target;
-  return n < kSegMax ? n : kSegMax;
-}
-// Entries per segment of a list cut into at most n segments.
-__host__ __device__ constexpr uint32_t segment_length(uint32_t len, uint32_t n) {
-  return ((len + n - 1) / n + kSegAlign - 1) / kSegAlign * kSegAlign;
-}
-// bslot entry of a split list: 1 + its first record, and its segment bound.
-__host__ __device__ constexpr uint32_t split_slot(uint32_t first, uint32_t n) { return (first + 1u) | (n << 20); }
-constexpr uint32_t kSplitSlotMask = 0xFFFFFu;
-static_assert(ASGS_MAX_VIEWS * kSplitUnits < (int)kSplitSlotMask, "split slots");
-// Floats per pixel of a boundary record (T there and the channels the later
-// entries add, padded to whole float4), and of a record.
+// Floats per pixel of a boundary record (T and the channels, padded to whole
+// float4) and of the final channels (padded).
 __host__ __device__ constexpr int split_first(int cs) { return (1 + cs + 3) & ~3; }
-__host__ __device__ constexpr int split_floats(int cs) { return split_first(cs) * 256; }
+__host__ __device__ constexpr int split_final(int cs) { return (cs + 3) & ~3; }
+// Floats of the split records of one list.
+__host__ __device__ constexpr int split_floats(int cs) {
+  return ((kSegMax - 1) * split_first(cs) + split_final(cs)) * 256;
+}
 
 // Weighted L1 residual fused into the forward's output stage (same terms as
 // launch_l1_loss, targets and gradients packed like the images).

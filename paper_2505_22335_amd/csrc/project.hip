@@ -305,21 +305,6 @@ __global__ void __launch_bounds__(256) k_project(RenderConst rc, asgs_gaussians 
 // world mean, plus the pose partials dL/drho = dL/dt, dL/dphi = t x dL/dt +
 // the rotation term of W = R_cw.
 // ---------------------------------------------------------------------------
-// D += the sums of a slot's dL/dpower times (dx, dy, dx^2, dx dy, dy^2), the
-// pixels' distances from the centre (u, v), from its moments M about the centre
-// of tile (tx, ty).
-ASGS_DEV void moments_about(float u, float v, int tx, int ty, const float* M, double (&D)[5]) {
-  const double uu = (double)u - (double)((float)(tx * kTile) + kTileMid);
-  const double vv = (double)v - (double)((float)(ty * kTile) + kTileMid);
-  const double Sdx = uu * M[0] - M[1];
-  const double Sdy = vv * M[0] - M[2];
-  D[0] += Sdx;
-  D[1] += Sdy;
-  D[2] += uu * Sdx - (uu * M[1] - M[3]);
-  D[3] += vv * Sdx - (uu * M[2] - M[4]);
-  D[4] += vv * Sdy - (vv * M[2] - M[5]);
-}
-
 template <int NF>
 __global__ void __launch_bounds__(256) k_project_backward(RenderConst rc, asgs_gaussians g,
                                                           asgs_gaussians dg,
@@ -355,32 +340,25 @@ __global__ void __launch_bounds__(256) k_project_backward(RenderConst rc, asgs_g
   const int t = threadIdx.x;
   const int64_t nblk = (nvis + 255) >> 8;
   const int64_t ev = (int64_t)blockIdx.x < nblk ? ((int64_t)(t >> 5) * nblk + blockIdx.x) * 32 + (t & 31) : nvis;
-  // Sums over the Gaussian's slots. D: dL/dpower times (dx, dy, dx^2, dx dy,
-  // dy^2), the distances from its centre; G: dL/dpower (5), then the channels.
-  // A slot holds the moments of dL/dpower over the pixel coordinates about its
-  // tile's centre, (1, lx, ly, lx^2, lx ly, ly^2), and the channel sums. The
-  // second moments about the centre and the step to the 2D covariance are
-  // differences of nearly equal terms for thin Gaussians: FP64.
+  // Sums over the Gaussian's slots, in slot order: the second moments are
+  // differences of nearly equal terms, whose FP32 rounding another order redraws.
   constexpr int GSP = (GS + 3) & ~3;  // slot stride (whole float4)
-  double D[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
   float G[GS];
 #pragma unroll
   for (int k = 0; k < GS; ++k) G[k] = 0.f;
   const float* slot = ctx_ptr<const float>(ctx, L.gslot);
   // A Gaussian over up to kFewSlots tiles is summed by its thread; one over
-  // more by a whole wave, four lanes per slot and sixteen slots at a time, so
-  // that no thread walks a long list alone. A room's volume (up to 130 tiles a
-  // Gaussian): 68 us with each Gaussian its thread's and 256 neighbours to a
-  // workgroup, 52 with whole waves from 33 slots on, 43 with the runs of 32
-  // spread as well, 39 from 17 on, 40 from 9 on (where 50k slots of 9.5k
-  // Gaussians go from 16 to 30 us).
+  // more by a group of lanes, one float of the slots each, so that every slot
+  // is one coalesced read and no thread walks a long list of whole slots.
+  // A room's volume (up to 130 tiles a Gaussian): 63 us with each Gaussian its
+  // thread's and 256 neighbours to a workgroup, 32.5 so; groups from 9 slots on
+  // 33.5, from 33 on 38; 50k slots of 9.5k Gaussians 16 us, then 13.3, 14.8 and 15.
   constexpr uint32_t kFewSlots = 16;
-  __shared__ double SD[5][256];
-  __shared__ float SG[GS - 5][256];
+  constexpr int kGroup = GS > 16 ? 32 : 16;
+  static_assert(GS <= kGroup, "a lane per float");
+  __shared__ float SG[GS][256];
   struct Queued {
     uint32_t start, num;
-    short4 rect;
-    float u, v;
     int thread;
   };
   __shared__ Queued queue[256];
@@ -389,82 +367,38 @@ __global__ void __launch_bounds__(256) k_project_backward(RenderConst rc, asgs_g
   __syncthreads();
   int64_t gid = 0;
   uint32_t num = 0u;
-  float4 g0 = make_float4(0.f, 0.f, 0.f, 0.f), g1 = g0;
   if (ev < nvis) {
     gid = (int64_t)ctx_ptr<const uint32_t>(ctx, L.vlist)[(int64_t)view * n + ev];
     // a visible Gaussian owns ntiles consecutive slots from toff
     const uint32_t start = ctx_ptr<const uint32_t>(ctx, L.toff)[gid];
     const uint32_t cnt = ctx_ptr<const uint32_t>(ctx, L.ntiles)[gid];
     num = (uint32_t)(min((uint64_t)start + cnt, (uint64_t)rc.cap) - min((uint64_t)start, (uint64_t)rc.cap));
-    const short4 r = ctx_ptr<const short4>(ctx, L.rect)[gid];
-    g0 = ctx_ptr<const float4>(ctx, L.geom)[2 * gid];
-    g1 = ctx_ptr<const float4>(ctx, L.geom)[2 * gid + 1];
     if (num > kFewSlots) {
       // in any order: every entry is summed on its own
-      queue[atomicAdd(&nqueue, 1)] = Queued{start, num, r, g0.x, g0.y, t};
+      queue[atomicAdd(&nqueue, 1)] = Queued{start, num, t};
     } else {
-      int cx = r.x, cy = r.z;
       const float4* sp = reinterpret_cast<const float4*>(slot + (size_t)start * GSP);
       for (uint32_t q = 0; q < num; ++q, sp += GSP / 4) {
-        float M[GSP];
 #pragma unroll
         for (int k4 = 0; k4 < GSP / 4; ++k4) {
           const float4 v = sp[k4];
-          M[4 * k4] = v.x;
-          M[4 * k4 + 1] = v.y;
-          M[4 * k4 + 2] = v.z;
-          M[4 * k4 + 3] = v.w;
-        }
-        moments_about(g0.x, g0.y, cx, cy, M, D);
-        G[5] += M[0];
-#pragma unroll
-        for (int k = 6; k < GS; ++k) G[k] += M[k];
-        if (++cx > r.y) {
-          cx = r.x;
-          ++cy;
+          if (4 * k4 + 0 < GS) G[4 * k4 + 0] += v.x;
+          if (4 * k4 + 1 < GS) G[4 * k4 + 1] += v.y;
+          if (4 * k4 + 2 < GS) G[4 * k4 + 2] += v.z;
+          if (4 * k4 + 3 < GS) G[4 * k4 + 3] += v.w;
         }
       }
     }
   }
   __syncthreads();
-  for (int qi = t >> 6; qi < nqueue; qi += 256 / 64) {
+  for (int qi = t / kGroup; qi < nqueue; qi += 256 / kGroup) {
     const Queued qe = queue[qi];
-    const uint32_t nq = qe.num;
-    const short4 r = qe.rect;
-    const int tt = qe.thread;
-    const uint32_t w = (uint32_t)(r.y - r.x + 1);
-    const int f = t & 3;  // floats 8 f .. 8 f + 7 of a slot
-    double Dq[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    float S[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) S[k] = 0.f;
-    for (uint32_t q = (t & 63) >> 2; q < nq; q += 16) {
-      const float* p = slot + (size_t)(qe.start + q) * GSP + 8 * f;
-      const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-      const float4 a = 8 * f < GSP ? *reinterpret_cast<const float4*>(p) : z;
-      const float4 b = 8 * f + 4 < GSP ? *reinterpret_cast<const float4*>(p + 4) : z;
-      const float M[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-      if (f == 0) moments_about(qe.u, qe.v, r.x + (int)(q % w), r.z + (int)(q / w), M, Dq);
-#pragma unroll
-      for (int k = 0; k < 8; ++k) S[k] += M[k];
-    }
-#pragma unroll
-    for (int o = 4; o < 64; o <<= 1) {
-#pragma unroll
-      for (int k = 0; k < 5; ++k) Dq[k] += __shfl_xor(Dq[k], o);
-#pragma unroll
-      for (int k = 0; k < 8; ++k) S[k] += __shfl_xor(S[k], o);
-    }
-    if ((t & 63) < 4) {
-      if (f == 0) {
-#pragma unroll
-        for (int k = 0; k < 5; ++k) SD[k][tt] = Dq[k];
-        SG[0][tt] = S[0];
-      }
-#pragma unroll
-      for (int k = 0; k < 8; ++k)
-        if (8 * f + k >= 6 && 8 * f + k < GS) SG[8 * f + k - 5][tt] = S[k];
-    }
+    const int k = t % kGroup;
+    const float* p = slot + (size_t)qe.start * GSP + (k < GS ? k : 0);
+    float s = 0.f;
+#pragma unroll 8
+    for (uint32_t q = 0; q < qe.num; ++q) s += p[(size_t)q * GSP];
+    if (k < GS) SG[k][qe.thread] = s;
   }
   __syncthreads();
   if (ev < nvis) {
@@ -472,14 +406,11 @@ __global__ void __launch_bounds__(256) k_project_backward(RenderConst rc, asgs_g
     const int64_t i = gid - (int64_t)view * n;
     if (num > kFewSlots) {
 #pragma unroll
-      for (int k = 0; k < 5; ++k) D[k] = SD[k][t];
-#pragma unroll
-      for (int k = 5; k < GS; ++k) G[k] = SG[k - 5][t];
+      for (int k = 0; k < GS; ++k) G[k] = SG[k][t];
     }
     {
-      const float du = (float)-(g0.z * D[0] + g0.w * D[1]), dv = (float)-(g0.w * D[0] + g1.x * D[1]);
-      const double dA = -0.5 * D[2], dB = -D[3], dC = -0.5 * D[4];
-      dop[i] = G[5] / g1.y;
+      const float du = G[0], dv = G[1], dA = G[2], dB = G[3], dC = G[4];
+      dop[i] = G[5];
       drgb[i] = G[6];
       drgb[n + i] = G[7];
       drgb[2 * n + i] = G[8];
@@ -491,15 +422,12 @@ __global__ void __launch_bounds__(256) k_project_backward(RenderConst rc, asgs_g
       load_gauss(g, view, i, n, m, s, q, o);
       Proj P;
       proj_core(V, m, s, q, rc.dilation, rc.znear, P);
+      const float a = P.a, b = P.b, c = P.c, det = P.det;
       // conic (A,B,C) = (c, -b, a)/det  ->  2D covariance (a, b, c)
-      float da, db, dc;
-      {
-        const double a = P.a, b = P.b, c = P.c, det = a * c - b * b;
-        const double id2 = 1.0 / (det * det);
-        da = (float)((-c * c * dA + b * c * dB - b * b * dC) * id2);
-        db = (float)((2.0 * b * c * dA + (-det - 2.0 * b * b) * dB + 2.0 * a * b * dC) * id2);
-        dc = (float)((-b * b * dA + a * b * dB - a * a * dC) * id2);
-      }
+      const float id2 = 1.f / (det * det);
+      const float da = (-c * c * dA + b * c * dB - b * b * dC) * id2;
+      const float db = (2.f * b * c * dA + (-det - 2.f * b * b) * dB + 2.f * a * b * dC) * id2;
+      const float dc = (-b * b * dA + a * b * dB - a * a * dC) * id2;
       // covariance -> T = J W and Sigma
       float ST0[3], ST1[3];
       sym_mul(P.S, P.T0, ST0);

@@ -56,8 +56,7 @@ ASGS_DEV ScanBlock scan_block(const RenderConst& rc) {
 // ---------------------------------------------------------------------------
 // One workgroup: the tile ranges [start, end) from the list lengths, the
 // emission cursors (= starts), the totals and the blend order of the tiles
-// (per position: tile, start, end; the forward adds the walked length),
-// longest list first (a counting sort on the length; lengths of 1023 and more
+// (per position: tile, start, end), longest list first (a counting sort on the length; lengths of 1023 and more
 // share one bucket, and the order within a bucket is arbitrary, which changes
 // no result). When the intersections exceed the capacity every range is left
 // empty: nothing is blended and the overflow is recorded.
@@ -71,11 +70,10 @@ __global__ void __launch_bounds__(kTileScanThreads) k_tile_scan(RenderConst rc, 
                                                                char* ctx, CtxLayout L) {
   constexpr int NW = kTileScanThreads / 64;
   __shared__ uint32_t bins[kOrderBins];
-  __shared__ uint32_t scount[ASGS_MAX_VIEWS][kLenBins];  // per view: lists per length class
-  __shared__ uint32_t sused[ASGS_MAX_VIEWS], starget[ASGS_MAX_VIEWS];
+  __shared__ uint32_t scount[ASGS_MAX_VIEWS][kSplitThresholds];  // per view: lists per length band
+  __shared__ uint32_t sused[ASGS_MAX_VIEWS], sfrom[ASGS_MAX_VIEWS];  // per view: slots taken, the length they are split from
   __shared__ int32_t sbase[ASGS_MAX_VIEWS + 1];   // first tile of each view
   __shared__ uint32_t svis[ASGS_MAX_VIEWS + 1];   // visible pairs before each view
-  __shared__ uint32_t sneed[ASGS_MAX_VIEWS][kSplitLadder];  // per view: records each segment length of the ladder takes
   __shared__ unsigned long long wtot[NW];
   __shared__ uint32_t wbin[NW], wpb[NW], wpv[NW];
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
@@ -97,12 +95,11 @@ __global__ void __launch_bounds__(kTileScanThreads) k_tile_scan(RenderConst rc, 
   const uint32_t* vs = ctx_ptr<const uint32_t>(ctx, L.vsum);
   auto at = [&](const uint32_t* p, uint32_t i, uint32_t end) { return i < end ? p[i] : 0u; };
   bins[t] = 0u;
-  for (int q = t; q < rc.n_views * kLenBins; q += kTileScanThreads) (&scount[0][0])[q] = 0u;
-  for (int q = t; q < rc.n_views * kSplitLadder; q += kTileScanThreads) (&sneed[0][0])[q] = 0u;
+  for (int q = t; q < rc.n_views * kSplitThresholds; q += kTileScanThreads) (&scount[0][0])[q] = 0u;
   if (t < ASGS_MAX_VIEWS) sused[t] = 0u;
   if (t <= ASGS_MAX_VIEWS) svis[t] = 0u;
   if (t <= rc.n_views) sbase[t] = t < rc.n_views ? views[t].tile_base : (int32_t)T;
-  for (int q = t; q < rc.n_views * kSplitUnits; q += kTileScanThreads) sinfo[q] = make_uint4(~0u, 0u, 0u, 0u);
+  for (int q = t; q < rc.n_views * kSplitPerView; q += kTileScanThreads) sinfo[q] = make_uint4(~0u, 0u, 0u, 0u);
   unsigned long long mine = 0;
   uint32_t pb = 0u, pv = 0u;  // of this wave's blocks
 #pragma unroll 4
@@ -123,9 +120,10 @@ __global__ void __launch_bounds__(kTileScanThreads) k_tile_scan(RenderConst rc, 
       const uint32_t c = tcur[i];
       mine += c;
       atomicAdd(&bins[order_bin(c)], 1u);
-      if (c > (uint32_t)split_target(0)) {
+      if (c > (uint32_t)kSplitLen) {
+        // band j: kSplitLen + j kSplitStep < c <= kSplitLen + (j + 1) kSplitStep (the last open)
         v = view_from(v, i);
-        atomicAdd(&scount[v][len_bin(c)], 1u);
+        atomicAdd(&scount[v][min((c - kSplitLen - 1u) / kSplitStep, kSplitThresholds - 1u)], 1u);
       }
     }
   }
@@ -173,16 +171,6 @@ __global__ void __launch_bounds__(kTileScanThreads) k_tile_scan(RenderConst rc, 
     }
     if (t == 0) svis[rc.n_views] = pvt;
   }
-  // per view, the records that cutting at each segment length of the ladder takes
-  {
-    constexpr int kB0 = len_bin(split_target(0)) + 1, kNB = kLenBins - kB0;
-    for (int q = t; q < rc.n_views * kSplitLadder * kNB; q += kTileScanThreads) {
-      const int w = q / (kSplitLadder * kNB), r = q - w * (kSplitLadder * kNB);
-      const int l = r / kNB, b = r - l * kNB + kB0;
-      const uint32_t k = scount[w][b];
-      if (k) atomicAdd(&sneed[w][l], k * (uint32_t)(bin_segments(b, split_target(l)) - 1));
-    }
-  }
   // places in the blend order: longest class first
   const uint32_t bv = bins[t];
   const uint32_t oincl = wave_incl_scan(bv);
@@ -200,10 +188,11 @@ __global__ void __launch_bounds__(kTileScanThreads) k_tile_scan(RenderConst rc, 
   }
   if (t < rc.n_views) {
     ctx_ptr<uint32_t>(ctx, L.vcount)[t] = svis[t + 1] - svis[t];
-    // the smallest segment length the records allow
-    int l = 0;
-    while (l < kSplitLadder && sneed[t][l] > (uint32_t)kSplitUnits) ++l;
-    starget[t] = (uint32_t)l;
+    // the smallest threshold that few enough lists exceed, from the bands' suffix sums
+    uint32_t above = 0u, from = ~0u;
+    for (int j = kSplitThresholds - 1; j >= 0 && (above += scount[t][j]) <= (uint32_t)kSplitPerView; --j)
+      from = (uint32_t)(kSplitLen + j * kSplitStep);
+    sfrom[t] = from;
   }
   __syncthreads();
   uint32_t* bslot = ctx_ptr<uint32_t>(ctx, L.bslot);
@@ -219,17 +208,14 @@ __global__ void __launch_bounds__(kTileScanThreads) k_tile_scan(RenderConst rc, 
       ranges[i] = r;
       tcur[i] = run;
       binfo[atomicAdd(&bins[order_bin(c)], 1u)] = make_uint4(i, r.x, r.y, 0u);
-      // cut by the view's segment length (the order of the records is arbitrary)
+      // split when longer than the view's threshold (the slot order is arbitrary)
       uint32_t sl = 0u;
-      if (!ovf && c > (uint32_t)split_target(0)) {
+      if (!ovf && c > (uint32_t)kSplitLen) {
         v = view_from(v, i);
-        const int l = (int)starget[v];
-        const int n = l < kSplitLadder ? bin_segments(len_bin(c), split_target(l)) : 1;
-        if (n > 1) {
-          const uint32_t first = (uint32_t)v * kSplitUnits + atomicAdd(&sused[v], (uint32_t)(n - 1));
-          const uint32_t len = segment_length(c, (uint32_t)n);
-          for (uint32_t s = 0; (s + 1) * len < c; ++s) sinfo[first + s] = make_uint4(i, r.x, r.y, s);
-          sl = split_slot(first, (uint32_t)n);
+        if (c > sfrom[v]) {
+          const uint32_t slot = (uint32_t)v * kSplitPerView + atomicAdd(&sused[v], 1u);
+          sinfo[slot] = make_uint4(i, r.x, r.y, 0u);
+          sl = slot + 1u;
         }
       }
       bslot[i] = sl;
@@ -333,8 +319,9 @@ constexpr unsigned long long kKeyMax = ~0ull;  // above every real key (depth bi
 // inside a thread or between the lanes of a wave (data-parallel moves and row
 // swaps). Unrolled: as a loop with a branch on the distance a step took 500
 // cycles. A list of 169 entries takes 4.5k cycles, 22k with every step
-// through LDS; the kernel 7.5 us instead of 14.5 at 640x480 (1200 lists of 130
-// on average), 42 instead of 92 for 8 such views with 390 on average.
+// through LDS; the kernel, which also forms the quarter masks, 9.8 us instead of
+// 14.5 at 640x480 (1200 lists of 130 on average), 53 instead of 92 for 8 views of
+// 320x240 with 390 on average (7.5 and 42 with masks from the reach box alone).
 template <int kCtrl>
 ASGS_DEV unsigned long long dpp_move(unsigned long long v) {
   const uint32_t lo = __builtin_amdgcn_update_dpp(0u, (uint32_t)v, kCtrl, 0xF, 0xF, true);
@@ -459,15 +446,49 @@ ASGS_DEV void sort_keys(const unsigned long long* a, int n, unsigned long long* 
   __syncthreads();
 }
 
-// Which of the tile's four 8x8 quarters (bit w) hold a pixel centre inside the
-// box the projection wrote around a Gaussian's alpha >= alpha_min ellipse:
-// the blend kernels' waves, one quarter each, skip the others.
-ASGS_DEV uint32_t quarter_mask(float u, float v, uint32_t box, float x0, float y0) {
-  const float hx = (float)__builtin_bit_cast(_Float16, (uint16_t)box);
-  const float hy = (float)__builtin_bit_cast(_Float16, (uint16_t)(box >> 16));
-  const bool xl = u + hx >= x0 && u - hx <= x0 + 7.f, xr = u + hx >= x0 + 8.f && u - hx <= x0 + 15.f;
-  const bool yt = v + hy >= y0 && v - hy <= y0 + 7.f, yb = v + hy >= y0 + 8.f && v - hy <= y0 + 15.f;
-  return (xl && yt ? 1u : 0u) | (xr && yt ? 2u : 0u) | (xl && yb ? 4u : 0u) | (xr && yb ? 8u : 0u);
+// Which of the tile's four 8x8 quarters (bit w) hold a pixel centre that can
+// pass the alpha test power >= ln(alpha_min / o) of an entry: a conservative
+// test against the bounding box of the ellipse d^T Q d <= 2 L, Q = [[A, B],
+// [B, C]], L = -ln(alpha_min / o), whose half extents are sqrt(2 L C / det Q)
+// and sqrt(2 L A / det Q). The box is computed in FP64 from the stored FP32
+// conic and widened by a relative 1e-3 + 2e-6 cond(Q) (covering the FP32
+// rounding of the per-pixel power, whose error grows with the condition
+// number) plus 0.01 px; entries too ill-conditioned for that bound are kept
+// everywhere. Entries whose threshold no pixel can reach (o < alpha_min, or
+// a NaN threshold) are dropped everywhere. The masks decide where the forward
+// cuts a quarter's list in two, and with it the last bits of T.
+// Entries whose reach box, which holds that box and was written by the
+// projection (two half-precision extents), misses the tile are dropped first.
+ASGS_DEV uint32_t quarter_mask(const float4& g0, const float4& g1, int x0, int y0) {
+  const float lnthr = g1.z;
+  const uint32_t box = __float_as_uint(g1.w);
+  const float bx = (float)__builtin_bit_cast(_Float16, (uint16_t)box);
+  const float by = (float)__builtin_bit_cast(_Float16, (uint16_t)(box >> 16));
+  const float tx0 = (float)x0, ty0 = (float)y0;
+  if (!(g0.x + bx >= tx0 && g0.x - bx <= tx0 + (float)(kTile - 1) && g0.y + by >= ty0 &&
+        g0.y - by <= ty0 + (float)(kTile - 1)))
+    return 0u;
+  if (!(lnthr <= 0.f)) return 0u;
+  const double a = g0.z, b = g0.w, c = g1.x;
+  const double det = a * c - b * b;
+  if (!(det > 0.0) || !(a > 0.0) || !(c > 0.0)) return 0xFu;
+  const double half_tr = 0.5 * (a + c);
+  const double disc = sqrt(0.25 * (a - c) * (a - c) + b * b);
+  const double lmax = half_tr + disc;
+  const double cond = lmax * lmax / det;  // lmax / lmin
+  const double rel = 1e-3 + 2e-6 * cond;
+  if (!(rel < 0.25)) return 0xFu;
+  const double L2 = -2.0 * (double)lnthr;
+  const double hx = sqrt(L2 * c / det) * (1.0 + rel) + 0.01;
+  const double hy = sqrt(L2 * a / det) * (1.0 + rel) + 0.01;
+  const double u = g0.x, v = g0.y;
+  uint32_t m = 0u;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    const double sx = x0 + 8 * (w & 1), sy = y0 + 8 * (w >> 1);
+    if (u + hx >= sx && u - hx <= sx + 7.0 && v + hy >= sy && v - hy <= sy + 7.0) m |= 1u << w;
+  }
+  return m;
 }
 
 struct ListOut {
@@ -485,10 +506,9 @@ struct ListOut {
   ASGS_DEV void put(uint64_t pos, unsigned long long key) const {
     const uint32_t gid = (uint32_t)key;
     const short4 r = rect[gid];
-    const float2 c = *reinterpret_cast<const float2*>(geom + (size_t)gid * kGeomStride);
-    const uint32_t box = __float_as_uint(geom[(size_t)gid * kGeomStride + 7]);
+    const float4* g = reinterpret_cast<const float4*>(geom + (size_t)gid * kGeomStride);
     pairgid[pos] = gid;
-    pmask[pos] = (uint8_t)quarter_mask(c.x, c.y, box, (float)(tx * kTile), (float)(ty * kTile));
+    pmask[pos] = (uint8_t)quarter_mask(g[0], g[1], tx * kTile, ty * kTile);
     pslot[pos] = toff[gid] + (uint32_t)((ty - r.z) * (r.y - r.x + 1) + (tx - r.x));
     ptile[pos] = tile;
   }
