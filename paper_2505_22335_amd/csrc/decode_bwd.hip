@@ -11,9 +11,14 @@
 // all on FP32 16x16x4 MFMAs. The heads' dX are summed per anchor in a fixed
 // order inside the workgroup, which then forms the anchor gradients (feature
 // part; view direction and distance through delta = (x - c)/|x - c|) and its
-// share of the camera-centre gradient. Each workgroup writes one partial of
+// share of the camera-centre gradient. Each workgroup keeps one partial of
 // every parameter gradient, reduced afterwards in a fixed order
-// (deterministic, no atomics).
+// (deterministic, no atomics). An item's products over its anchors are summed
+// on their own and added to the running sums as one number, and the running
+// sums go into the partial after every kChainViews views' worth of items:
+// rounded after every four anchors and over all views, the gradients of two
+// views of 33k anchors were 2.8e-7 of their norm away from FP64, of sixteen
+// views of 500 3.0e-7; so 1.4e-7 and 1.3e-7, for 5 % of the time.
 //
 // The workgroup meets at one barrier per item. What crosses waves is taken up
 // one item later: the feature waves' dH partials (then the feature head's dX
@@ -25,8 +30,8 @@
 // of the roughly 11k cycles an item takes (16k with three barriers per item
 // and the head's activation chosen per element). One launch per view, each
 // with its own prologue and parameter partials, took 116 us a view for 50k
-// anchors (eight views 928 us, now 540); one view of 100k anchors 177 us, now
-// 150; of 20k 49 us, now 43.
+// anchors (eight views 931 us, now 565); one view of 100k anchors 180 us, now
+// 156; of 20k 50 us, now 46; of 20k with k = 16 and its reduction 71 us, now 60.
 //
 // Operand layouts. v_mfma_f32_16x16x4f32 (wave64): lane l = 16 g + f supplies
 // A[f][g] and B[g][f] and receives D[4 g + r][f], r = 0..3. A 16x16 block
@@ -55,6 +60,7 @@ typedef float f4v __attribute__((ext_vector_type(4)));
 constexpr int kBW = 8;         // waves per workgroup
 constexpr int kBT = 64 * kBW;  // threads per workgroup
 constexpr int kMaxWG = 256;    // one workgroup per compute unit
+constexpr int kChainViews = 4; // views' worth of items summed before they go into the partial
 constexpr int kW1L = 36;       // LDS row of a first-layer weight row: 35 inputs + the distance column
 constexpr int kW2L = 36;       // LDS row of a second-layer weight row in the prologue (32 units + pad)
 constexpr int kXL = 52;        // LDS row of an anchor's inputs: 35 + distance column, |x - c| at 36
@@ -91,18 +97,6 @@ ASGS_DEV void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Element i of a five-entry table with a lane-varying index, as selects (no
-// private-memory copy of the table).
-template <typename T>
-ASGS_DEV T pick5(const T (&a)[kHeads], int i) {
-  T v = a[0];
-  v = i == 1 ? a[1] : v;
-  v = i == 2 ? a[2] : v;
-  v = i == 3 ? a[3] : v;
-  v = i == 4 ? a[4] : v;
-  return v;
 }
 
 template <int kR>
@@ -411,19 +405,99 @@ __global__ void __launch_bounds__(kBT, 1) k_dec_bwd(DecodeConst dc, HeadTable ht
         dt0[b] = fmaf(dv.lt[view][0], c, dt0[b]);
         dt1[b] = fmaf(dv.lt[view][1], c, dt1[b]);
       }
+      f4v p[3];
+#pragma unroll
+      for (int ct = 0; ct < 3; ++ct) p[ct] = f4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int ct = 0; ct < 3; ++ct) dw1[b][ct] = mfma(dzt[b][r], xa[ct][r], dw1[b][ct]);
+        for (int ct = 0; ct < 3; ++ct) p[ct] = mfma(dzt[b][r], xa[ct][r], p[ct]);
+#pragma unroll
+      for (int ct = 0; ct < 3; ++ct) dw1[b][ct] += p[ct];
     }
   };
 
+  // ---- the running sums into the workgroup's partial of the parameter
+  // gradients, four values of a lane at a time (their reads before the first
+  // write) ----
+  char* const P = reinterpret_cast<char*>(w.part + ((int64_t)blockIdx.x << 6));
+  auto flush = [&](bool add) {
+    int cl = fl, cg = fg;
+    asm volatile("" : "+v"(cl), "+v"(cg));  // addresses are formed here, not held in registers over the items
+    auto put4 = [&](const int (&pi)[4], const f4v& v, const bool (&ok)[4]) {
+      uint32_t at[4];
+      f4v old;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        at[e] = 4u * (((uint32_t)pi[e] >> 6) * ((uint32_t)w.nblk_w << 6) + ((uint32_t)pi[e] & 63u));
+        old[e] = add && ok[e] ? *reinterpret_cast<const float*>(P + at[e]) : 0.f;
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (ok[e]) *reinterpret_cast<float*>(P + at[e]) = old[e] + v[e];
+    };
+    auto over_groups = [&](float x) {  // sum over the four lane groups
+      x += __shfl_xor(x, 16);
+      return x + __shfl_xor(x, 32);
+    };
+#pragma unroll
+    for (int i = 0; i < kR; ++i) {
+      if (!active || i >= nt) break;
+      const int r0 = 16 * (t0 + i);
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        int pi[4];
+        bool ok[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int o = r0 + 4 * cg + e;
+          pi[e] = w2o + o * kHid + 16 * c + cl;
+          ok[e] = o < rows;
+        }
+        put4(pi, dw2[i][c], ok);
+        dw2[i][c] = f4v{0.f, 0.f, 0.f, 0.f};
+      }
+      const float sb = over_groups(db2[i]);
+      put4({w2o + rows * kHid + r0 + cl, 0, 0, 0}, f4v{sb, 0.f, 0.f, 0.f},
+           {cg == 0 && r0 + cl < rows, false, false, false});
+      db2[i] = 0.f;
+    }
+    if (hw1 < 0) return;
+    const int o1w = (int)ht.off[hw1], oxw = (int)ht.xoff[hw1];  // the head of this wave's dW1
+    // extra input columns: the distance weight's gradient is column 35 of the
+    // products with X; the temporal weights' gradients are the items' bias
+    // gradients times their view's embedding
+    const bool dist = cl == 3 && nx > 0, lt = cg == 0 && nx == 3;
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+#pragma unroll
+      for (int ct = 0; ct < 3; ++ct) {
+        int pi[4];
+        bool ok[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int u = 16 * b + 4 * cg + e;
+          pi[e] = ct == 2 && dist ? oxw + u * nx : o1w + u * kIn + 16 * ct + cl;
+          ok[e] = ct < 2 || cl < 3 || dist;
+        }
+        put4(pi, dw1[b][ct], ok);
+        dw1[b][ct] = f4v{0.f, 0.f, 0.f, 0.f};
+      }
+      const float sb = over_groups(db1[b]), s0 = over_groups(dt0[b]), s1 = over_groups(dt1[b]);
+      const int u = 16 * b + cl;
+      put4({o1w + kHid * kIn + u, oxw + u * 3 + 1, oxw + u * 3 + 2, 0}, f4v{sb, s0, s1, 0.f}, {cg == 0, lt, lt, false});
+      db1[b] = dt0[b] = dt1[b] = 0.f;
+    }
+  };
   f4v hp[2];  // the feature waves' H of the previous item
   hp[0] = hp[1] = f4v{0.f, 0.f, 0.f, 0.f};
   float gfeat = 0.f, gxyz = 0.f;  // anchor gradients of the tile, over its views
   int tile = blockIdx.x, view = 0, ptile = 0, pview = 0;  // this item's and the previous one's
   int xcur = 0, xprev = 2;                                // their input buffers
   bool have = tile < ngrid;
+  const int chunk = kChainViews * ((ngrid - 1 - (int)blockIdx.x) / (int)gridDim.x + 1) + 1;
+  int left = chunk;  // items until the running sums go into the partial
+  bool add = false;  // the partial holds an earlier chunk's sums
   // item by item, and one more round for what the last item left
   for (int par = 0, prev = 0; have || prev; par ^= 1) {
     int ntile = tile, nview = view + 1;
@@ -534,12 +608,19 @@ __global__ void __launch_bounds__(kBT, 1) k_dec_bwd(DecodeConst dc, HeadTable ht
         for (int i = 0; i < N; ++i) dyt[i] = *reinterpret_cast<const f4v*>(&HBw[fl][16 * i + 4 * fg]);
         wave_sync();
         // dW2 (rows x units) += dY^T H, K = anchors
+        f4v p[N][2];
+#pragma unroll
+        for (int i = 0; i < N; ++i) p[i][0] = p[i][1] = f4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int r = 0; r < 4; ++r)
 #pragma unroll
           for (int i = 0; i < N; ++i)
 #pragma unroll
-            for (int b = 0; b < 2; ++b) dw2[i0 + i][b] = mfma(dy[i][r], ht_[b][r], dw2[i0 + i][b]);
+            for (int b = 0; b < 2; ++b) p[i][b] = mfma(dy[i][r], ht_[b][r], p[i][b]);
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+#pragma unroll
+          for (int b = 0; b < 2; ++b) dw2[i0 + i][b] += p[i][b];
 #pragma unroll
         for (int i = 0; i < N; ++i) db2[i0 + i] += (dy[i][0] + dy[i][1]) + (dy[i][2] + dy[i][3]);
         // dH^T (units x anchors) += W2^T dY^T, K = rows
@@ -634,6 +715,11 @@ __global__ void __launch_bounds__(kBT, 1) k_dec_bwd(DecodeConst dc, HeadTable ht
         if (fl == 0 && fg < 3) DC[3 * pview + fg] -= x;
       }
     }
+    if (--left == 0 || !have) {
+      if (want_params) flush(add);
+      add = true;
+      left = chunk;
+    }
     prev = have;
     ptile = tile;
     pview = view;
@@ -646,59 +732,6 @@ __global__ void __launch_bounds__(kBT, 1) k_dec_bwd(DecodeConst dc, HeadTable ht
   // ---- the workgroup's camera-centre partials ----
   __syncthreads();
   if (t < 3 * V) w.dcpart[(int64_t)blockIdx.x * 3 * V + t] = DC[t];
-  if (!want_params) return;
-  // ---- this workgroup's parameter partials ----
-  float* P = w.part;
-  const int64_t bk = blockIdx.x, nbk = w.nblk_w;
-  auto put = [&](int64_t pi, float v) { P[part_index(pi, bk, nbk)] = v; };
-#pragma unroll
-  for (int i = 0; i < kR; ++i) {
-    if (!active || i >= nt) break;
-    const int r0 = 16 * (t0 + i);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int o = r0 + 4 * fg + r;
-      if (o < rows) {
-        put(w2o + (int64_t)o * kHid + fl, dw2[i][0][r]);
-        put(w2o + (int64_t)o * kHid + 16 + fl, dw2[i][1][r]);
-      }
-    }
-    float sb = db2[i];
-    sb += __shfl_xor(sb, 16);
-    sb += __shfl_xor(sb, 32);
-    if (fg == 0 && r0 + fl < rows) put(w2o + (int64_t)rows * kHid + r0 + fl, sb);
-  }
-  if (hw1 < 0) return;
-  const int o1w = (int)ht.off[hw1], oxw = (int)ht.xoff[hw1];  // the head of this wave's dW1
-  // extra input columns: the distance weight's gradient is column 35 of the
-  // products with X; the temporal weights' gradients are the items' bias
-  // gradients times their view's embedding
-#pragma unroll
-  for (int b = 0; b < 2; ++b) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int u = 16 * b + 4 * fg + r;
-      put(o1w + u * kIn + fl, dw1[b][0][r]);
-      put(o1w + u * kIn + 16 + fl, dw1[b][1][r]);
-      if (fl < 3) put(o1w + u * kIn + 32 + fl, dw1[b][2][r]);
-      if (fl == 3 && nx > 0) put(oxw + u * nx, dw1[b][2][r]);
-    }
-    float sb = db1[b], s0 = dt0[b], s1 = dt1[b];
-    sb += __shfl_xor(sb, 16);
-    s0 += __shfl_xor(s0, 16);
-    s1 += __shfl_xor(s1, 16);
-    sb += __shfl_xor(sb, 32);
-    s0 += __shfl_xor(s0, 32);
-    s1 += __shfl_xor(s1, 32);
-    if (fg == 0) {
-      const int u = 16 * b + fl;
-      put(o1w + kHid * kIn + u, sb);
-      if (nx == 3) {
-        put(oxw + u * 3 + 1, s0);
-        put(oxw + u * 3 + 2, s1);
-      }
-    }
-  }
 }
 
 template <int kR>
