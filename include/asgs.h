@@ -172,9 +172,12 @@ int asgs_ctx_status(const void* ctx, void* stream, int64_t* n_isect, int64_t* n_
  *  ASGS_CTX_NCONTRIB    uint32[P]   per pixel: list position + 1 of the last
  *                                   composited Gaussian of its tile
  *  ASGS_CTX_TFINAL      float[P]    per pixel final transmittance
- *  ASGS_CTX_GEOM        float[V*n][8] u, v, conic A, B, C, opacity, ln(alpha_min / o), 0;
- *                                   written for the (view, Gaussian) pairs whose radius
- *                                   entry is >= 0, undefined for the others
+ *  ASGS_CTX_GEOM        float[V*n][8] u, v, conic A, B, C, opacity, ln(alpha_min / o), and in
+ *                                   the bits of the eighth word two half-precision numbers, the
+ *                                   half extents (x low, y high) of a box around every pixel
+ *                                   that passes the alpha test; written for the (view,
+ *                                   Gaussian) pairs whose radius entry is >= 0, undefined for
+ *                                   the others
  *  ASGS_CTX_RADIUS      float[V*n][2] footprint half-widths r_x, r_y in whole pixels
  *                                   (ceil of sqrt(2 ln(o / alpha_min) Sigma'), Eq. 2),
  *                                   -1 for pairs culled before the footprint

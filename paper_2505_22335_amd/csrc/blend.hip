@@ -29,12 +29,13 @@ namespace {
 ASGS_DEV int tile_lx(int t) { return ((t >> 6) & 1) * 8 + (t & 7); }
 ASGS_DEV int tile_ly(int t) { return ((t >> 7) & 1) * 8 + ((t >> 3) & 7); }
 
-// Issue priority of a tile's waves by its rank in the blend order (longest
-// list first). The first workgroups of a launch spread over the compute units,
-// so the longest list on each unit gets the highest priority, the next one the
-// next level: the tiles on the critical path of the launch are preferred over
-// the shorter ones sharing their SIMDs (the order of the results does not
-// change).
+// Issue priority of a workgroup's waves by its rank in the launch: the blend
+// order (longest list first), in the backward behind the places of the split
+// lists' segments. The first workgroups of a launch spread over the compute
+// units, so the first on each unit gets the highest priority, the next one the
+// next level: they are preferred over the shorter ones sharing their SIMDs (the
+// order of the results does not change). With four views and more the segments' places,
+// used or not, take all levels of the backward.
 ASGS_DEV void prioritise(uint32_t rank, int n_cu) {
   const uint32_t band = rank / (uint32_t)(n_cu > 0 ? n_cu : 1);
   if (band == 0u) __builtin_amdgcn_s_setprio(3);

@@ -56,9 +56,9 @@ ASGS_DEV ScanBlock scan_block(const RenderConst& rc) {
 // ---------------------------------------------------------------------------
 // One workgroup: the tile ranges [start, end) from the list lengths, the
 // emission cursors (= starts), the totals and the blend order of the tiles
-// (per position: tile, start, end), longest list first (a counting sort on the length; lengths of 1023 and more
-// share one bucket, and the order within a bucket is arbitrary, which changes
-// no result). When the intersections exceed the capacity every range is left
+// (per position: tile, start, end), longest list first (a counting sort on the
+// length; lengths of 1023 and more share one bucket, and the order within a
+// bucket is arbitrary, which changes no result). When the intersections exceed the capacity every range is left
 // empty: nothing is blended and the overflow is recorded.
 // ---------------------------------------------------------------------------
 constexpr int kOrderBins = 1024;

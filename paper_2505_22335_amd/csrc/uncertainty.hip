@@ -179,10 +179,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
   const int plane = a.Hp * a.Wp;
   const TileCells tc = tile_cells(a, tx, ty);
   const int nslots = tc.ncy * tc.ncx;
-  // R at the lane's pixel (column 4 g + n % 4) of the wave's four rows,
-  // requested first (clamped into the view; pixels outside it are masked
-  // where used)
-  const int rr = n & 3;
+  const int rr = n & 3;  // the lane's pixel of a row: column 4 g + rr
   // ---- stage the patches' Z (zero past the tile's patches) and w2 ----
   for (int q = t; q < kSlots * kHid; q += 256) {
     const int sl = q / kHid, u = q - sl * kHid;
